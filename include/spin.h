@@ -60,7 +60,9 @@ enum spin_status {
 
 /* Kernel families; the chain (and so every bit of output) is the same. */
 enum spin_kernel {
-  SPIN_KERNEL_AUTO = 0,     /* library picks */
+  SPIN_KERNEL_AUTO = 0,     /* library picks; calls of several sweeps on lattices without a
+                               register-column kernel run k sweeps of a tile per launch (ping-pong
+                               buffers; spin_get_kernel still names what single sweeps run) */
   SPIN_KERNEL_GENERIC = 1,  /* per-site, global memory, any even L */
   SPIN_KERNEL_RESIDENT = 2, /* whole lattice in one workgroup's LDS, all sweeps in one launch */
   SPIN_KERNEL_TILED = 3,    /* LDS tile + halo per colour phase, needs L % 8 == 0 */

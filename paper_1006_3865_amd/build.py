@@ -12,6 +12,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libspin.so")
 
 SOURCES = ["spin_kernels.hip", "spin_stream2d.hip", "spin_stream3d.hip", "spin_stream_kernels.hip",
+           "spin_block_kernels.hip",
            "spin_coarse_kernels.hip", "spin_batch_kernels.hip", "spin_msc_kernels.hip", "spin_lcg_kernels.hip",
            "spin_heis_kernels.hip", "spin_probe_kernels.hip", "spin_noalloc.hip", "spin_runtime.cpp", "spin_batch.cpp", "spin_msc.cpp", "spin_heis.cpp"]
 

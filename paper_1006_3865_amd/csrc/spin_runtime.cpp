@@ -20,6 +20,7 @@
 
 #include "spin.h"
 #include "spin_batch.h"
+#include "spin_block.h"
 #include "spin_internal.h"
 #include "spin_lcg.h"
 
@@ -260,6 +261,10 @@ struct spin_lattice {
   uint32_t* jn;         // EA couplings as nibble words for that kernel (packed on first use)
   int rng;              // spin_rng
   uint64_t* lcg;        // LCG modes: one generator state per 8-site group
+  bool block;           // a family chosen by spin_autotune that runs its sweeps with k_block
+  bool plans_made;      // the plans below are filled in
+  BlockPlan plans[kBlockMaxK + 1];  // k_block launches of k sweeps (plans[k].k == 0: none)
+  double plan_us[kBlockMaxK + 1];   // and their estimated times
 };
 
 static const uint64_t kMaxSweepIndex = (uint64_t)1 << 32;
@@ -318,20 +323,22 @@ static uint32_t single_threads(const spin_lattice* h, const Tile& tile) {
 struct Tuned {
   int kernel;
   Tile tile;
+  bool block;  // several sweeps per launch (k_block) where a call has them
 };
 static std::mutex g_tune_mu;
 static std::map<std::tuple<int, int, int>, Tuned> g_tuned;
 
 static bool g_tuned_loaded = false;
 
-// Records "lattice <arch> model L d kernel x y z threads": the persisted choices of spin_autotune.
+// Records "lattice <arch> model L d kernel x y z threads [block]": the persisted choices of
+// spin_autotune (no block field: 0).
 static void load_tuned_locked() {
   if (g_tuned_loaded) return;
   g_tuned_loaded = true;
   for (const auto& v : tune_cache_read("lattice"))
     if (v.size() >= 8)
       g_tuned[std::make_tuple((int)v[0], (int)v[1], (int)v[2])] =
-          Tuned{(int)v[3], Tile{(int)v[4], (int)v[5], (int)v[6], (int)v[7]}};
+          Tuned{(int)v[3], Tile{(int)v[4], (int)v[5], (int)v[6], (int)v[7]}, v.size() > 8 && v[8] != 0};
 }
 
 static bool tuned_choice(const spin_lattice* h, Tuned* out) {
@@ -406,17 +413,19 @@ static bool family_ok(const spin_lattice* h, int kernel, const Tile& tile) {
   }
 }
 
-// Family and tile that the next sweep uses.
-static int resolve(const spin_lattice* h, Tile* tile) {
-  if (h->kernel != SPIN_KERNEL_AUTO) {
-    *tile = default_tile(h, h->kernel);
-    return h->kernel;
-  }
-  Tuned tc;
-  if (tuned_choice(h, &tc) && family_ok(h, tc.kernel, tc.tile)) {
-    *tile = tc.tile;
-    return tc.kernel;
-  }
+// Whether the automatic choice sweeps this lattice with k_block where it can: always but for the
+// shapes of the register-column and slab kernels, which are faster there (2D L = 4096 13.1 us a sweep
+// against 13.6 with k_block, L = 8192 36 against 55; 3D L = 512 79 against 150); at 3D L = 256, where
+// half their lanes repeat work, k_block takes 17.8 us and the column kernel 24.
+static bool auto_block(const spin_lattice* h, int kernel, const Tile& tile) {
+  if (kernel != SPIN_KERNEL_FUSED) return true;
+  if (h->d == 2) return tile.x != h->L || h->L < 4096;
+  return h->L == 256;
+}
+
+// The automatic choice by lattice shape alone.
+static int auto_family(const spin_lattice* h, Tile* tile, bool* block) {
+  *block = true;
   if (h->N <= kResidentAutoSites) {
     *tile = default_tile(h, SPIN_KERNEL_RESIDENT);
     return SPIN_KERNEL_RESIDENT;
@@ -429,11 +438,63 @@ static int resolve(const spin_lattice* h, Tile* tile) {
     Tile t = default_tile(h, k);
     if (family_ok(h, k, t)) {
       *tile = t;
+      *block = auto_block(h, k, t);
       return k;
     }
   }
   *tile = default_tile(h, SPIN_KERNEL_GENERIC);
   return SPIN_KERNEL_GENERIC;
+}
+
+// Family and tile that the next sweep uses; *block: calls of several sweeps may run them with
+// k_block instead (the family then still names what single sweeps run).
+static int resolve(const spin_lattice* h, Tile* tile, bool* block = nullptr) {
+  bool ignored;
+  if (!block) block = &ignored;
+  *block = h->block;
+  if (h->kernel != SPIN_KERNEL_AUTO) {
+    *tile = default_tile(h, h->kernel);
+    return h->kernel;
+  }
+  Tuned tc;
+  if (tuned_choice(h, &tc) && family_ok(h, tc.kernel, tc.tile)) {
+    *tile = tc.tile;
+    *block = tc.block;
+    return tc.kernel;
+  }
+  return auto_family(h, tile, block);
+}
+
+// Lattices k_block is offered: below 32^2 sites one workgroup's LDS (the resident kernels) is as fast.
+static bool block_offered(const spin_lattice* h) {
+  return h->N >= 1024 && h->L >= 8 && (h->N + 8) * (h->model == SPIN_EA_PMJ ? h->d : 1) < ((uint64_t)1 << 31);
+}
+
+// The plans of a lattice shape (a function of model, L and d alone), searched once per shape and
+// process: 10-30 us a search.
+struct Plans {
+  BlockPlan plan[kBlockMaxK + 1];
+  double us[kBlockMaxK + 1];
+};
+static std::mutex g_plans_mu;
+static std::map<std::tuple<int, int, int>, Plans> g_plans;
+
+static void make_plans(spin_lattice* h) {
+  if (h->plans_made) return;
+  const auto key = std::make_tuple(h->model, h->L, h->d);
+  std::lock_guard<std::mutex> lk(g_plans_mu);
+  auto it = g_plans.find(key);
+  if (it == g_plans.end()) {
+    if (g_plans.size() >= 256) g_plans.clear();
+    Plans p;
+    for (uint32_t k = 1; k <= kBlockMaxK; ++k) p.plan[k] = block_plan(lat_of(h), k, &p.us[k]);
+    it = g_plans.emplace(key, p).first;
+  }
+  for (uint32_t k = 1; k <= kBlockMaxK; ++k) {
+    h->plans[k] = it->second.plan[k];
+    h->plan_us[k] = it->second.us[k];
+  }
+  h->plans_made = true;
 }
 
 // Make room for nrec records of `parts` slots each.
@@ -468,6 +529,9 @@ static int take_parts(spin_lattice* h, const CallScratch* fx, uint32_t nrec, uin
   *out = h->part;
   return SPIN_OK;
 }
+
+// Bytes of a spin buffer: the last 8-site group whole.
+static size_t spin_bytes(const spin_lattice* h) { return (size_t)((h->N + 7) & ~(uint64_t)7); }
 
 static int64_t e_offset(const spin_lattice* h) { return -(int64_t)h->d * (int64_t)h->N; }
 
@@ -586,6 +650,79 @@ static int run_lcg(spin_lattice* h, int n, const Accept& acc, int every, int64_t
   return SPIN_OK;
 }
 
+// How n sweeps are cut into k_block launches: the number of launches (0: not at all) and the plan of
+// the longest; launch i runs n / launches sweeps, the first n % launches of them one more, all on
+// one tile shape.  The number has the parity that leaves the current buffer where the family's own
+// launches would (n for the ping-pong families, even for those in place), so that a captured
+// call can be replayed as before.
+static uint32_t block_launches(spin_lattice* h, int n, int kernel, BlockPlan* plan) {
+  make_plans(h);
+  const bool pingpong = kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM;
+  const uint32_t odd = pingpong ? (uint32_t)n & 1u : 0u;
+  uint32_t best = 0;
+  double best_us = 1e300;
+  for (uint32_t k = 1; k <= kBlockMaxK; ++k) {
+    if (h->plans[k].k == 0) continue;
+    uint32_t m = ((uint32_t)n + k - 1) / k;
+    if ((m & 1u) != odd) ++m;
+    if (m > (uint32_t)n) continue;
+    const uint32_t longest = ((uint32_t)n + m - 1) / m;
+    if (h->plans[longest].k == 0) continue;
+    const double us = (double)m * h->plan_us[longest];
+    if (us < best_us) {
+      best_us = us;
+      best = m;
+      *plan = h->plans[longest];
+    }
+  }
+  return best;
+}
+
+// n sweeps in k_block launches.  *ran = false (and nothing enqueued) where they cannot run: the caller
+// goes on with the family's own kernels.
+static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64_t* dE, int64_t* dM, int kernel,
+                     const CallScratch* fx, bool* ran) {
+  *ran = false;
+  if (!block_offered(h) || !block_lattice_ok(lat_of(h), acc)) return SPIN_OK;
+  BlockPlan plan;
+  const uint32_t m = block_launches(h, n, kernel, &plan);
+  if (m == 0) return SPIN_OK;
+  const uint32_t nrec = every > 0 ? (uint32_t)(n / every) : 0;
+  const uint32_t tiles = block_tiles(lat_of(h), plan);
+  if (fx && (!h->buf[1] || (size_t)nrec * tiles * 2 > fx->part_slots)) return SPIN_OK;
+  if (!h->buf[1]) {
+    h->buf[1] = (int8_t*)h->mem.get(spin_bytes(h));
+    if (!h->buf[1]) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
+  }
+  int64_t* part = nullptr;
+  if (int rc = take_parts(h, fx, nrec, tiles, &part)) return rc;
+  *ran = true;
+  uint32_t done = 0, rec = 0;
+  for (uint32_t i = 0; i < m; ++i) {
+    BlockPlan p = plan;
+    p.k = (uint32_t)n / m + (i < (uint32_t)n % m ? 1u : 0u);
+    uint32_t mask = 0, recs = 0;
+    for (uint32_t j = 0; every > 0 && j < p.k; ++j)
+      if ((done + j + 1) % (uint32_t)every == 0) {
+        mask |= 1u << j;
+        ++recs;
+      }
+    const Lat l = lat_of(h);
+    hipError_t e = launch_block(l, h->buf[h->cur], h->buf[1 - h->cur], (uint32_t)(h->t + done), acc, p, mask,
+                                part ? part + (size_t)rec * tiles * 2 : nullptr, h->stream);
+    if (e != hipSuccess) return hip_fail(e, "block sweep launch");
+    h->cur = 1 - h->cur;
+    done += p.k;
+    rec += recs;
+  }
+  if (nrec > 0) {
+    hipError_t e = launch_finalize(part, tiles, tiles, nrec, dE, dM, e_offset(h), (int64_t)h->N, h->stream);
+    if (e != hipSuccess) return hip_fail(e, "record finalize launch");
+  }
+  h->t += (uint64_t)n;
+  return SPIN_OK;
+}
+
 // Enqueue n sweeps; if every > 0 write records into device arrays dE, dM.
 static int run_sweeps(spin_lattice* h, int n, double beta, int every, int64_t* dE, int64_t* dM,
                       const CallScratch* fx = nullptr) {
@@ -598,7 +735,13 @@ static int run_sweeps(spin_lattice* h, int n, double beta, int every, int64_t* d
   if (h->rng != SPIN_RNG_PHILOX) return run_lcg(h, n, acc, every, dE, dM, fx);
   if (h->schedule == SPIN_SCHEDULE_COARSE) return run_coarse(h, n, acc, every, dE, dM, fx);
   Tile tile;
-  const int kernel = resolve(h, &tile);
+  bool block = false;
+  const int kernel = resolve(h, &tile, &block);
+  if (block) {
+    bool ran = false;
+    if (int rc = run_block(h, n, acc, every, dE, dM, kernel, fx, &ran)) return rc;
+    if (ran) return SPIN_OK;
+  }
   hipError_t e = hipSuccess;
   if (kernel == SPIN_KERNEL_RESIDENT && single_threads(h, tile)) {
     if (int rc = run_single(h, n, acc, every, dE, dM, single_threads(h, tile), fx)) return rc;
@@ -616,7 +759,7 @@ static int run_sweeps(spin_lattice* h, int n, double beta, int every, int64_t* d
     if (int rc = ensure_jn(h, fx)) return rc;
   if ((kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM) && !h->buf[1]) {
     if (fx) return fail(SPIN_ESTATE, "the second spin buffer of this lattice is not allocated yet");
-    h->buf[1] = (int8_t*)h->mem.get(h->N);
+    h->buf[1] = (int8_t*)h->mem.get(spin_bytes(h));
     if (!h->buf[1]) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
   }
   // records: partial counts per workgroup, reduced by one kernel at the end
@@ -681,11 +824,13 @@ static int prepare_buffers(spin_lattice* h) {
   if (h->rng != SPIN_RNG_PHILOX) return SPIN_OK;
   if (h->schedule == SPIN_SCHEDULE_COARSE) return ensure_jn(h);
   Tile tile;
-  const int kernel = resolve(h, &tile);
+  bool block = false;
+  const int kernel = resolve(h, &tile, &block);
+  if (block && block_offered(h)) make_plans(h);
   if ((kernel == SPIN_KERNEL_RESIDENT && single_threads(h, tile)) || kernel == SPIN_KERNEL_STREAM)
     if (int rc = ensure_jn(h)) return rc;
-  if ((kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM) && !h->buf[1]) {
-    h->buf[1] = (int8_t*)h->mem.get(h->N);
+  if ((kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM || (block && block_offered(h))) && !h->buf[1]) {
+    h->buf[1] = (int8_t*)h->mem.get(spin_bytes(h));
     if (!h->buf[1]) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
   }
   return SPIN_OK;
@@ -706,29 +851,37 @@ int spin::record_device(spin_lattice* h, int64_t* E, int64_t* M) {
 static std::vector<Tuned> tune_candidates(const spin_lattice* h) {
   std::vector<Tuned> c;
   const int L = h->L;
-  for (int th : {256, 512, 1024}) c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, th}});
-  c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, 512 + 64}});  // the per-site resident kernel
+  for (int th : {256, 512, 1024}) c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, th}, false});
+  c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, 512 + 64}, false});  // the per-site resident kernel
   if (h->d == 2) {
     for (int th : {256, 512, 1024})
-      for (int H : {8, 16, 32}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, H, 0, th}});
+      for (int H : {8, 16, 32}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, H, 0, th}, false});
     const int f2[7][3] = {{256, 32, 256}, {512, 32, 512}, {128, 16, 256}, {16, 8, 64},
                           {512, 16, 256}, {512, 32, 256}, {512, 64, 256}};
-    for (auto& f : f2) c.push_back({SPIN_KERNEL_FUSED, Tile{f[0], f[1], 0, f[2]}});
+    for (auto& f : f2) c.push_back({SPIN_KERNEL_FUSED, Tile{f[0], f[1], 0, f[2]}, false});
     const int t2[5][3] = {{256, 32, 256}, {128, 16, 256}, {512, 32, 512}, {64, 8, 64}, {16, 8, 64}};
-    for (auto& f : t2) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], 0, f[2]}});
+    for (auto& f : t2) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], 0, f[2]}, false});
     for (int th : {256, 512})
-      for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, 1, H, th}});
+      for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, 1, H, th}, false});
   } else {
     const int f3[5][2] = {{8, 640}, {8, 320}, {16, 576}, {16, 384}, {32, 704}};
     for (auto& f : f3)
-      for (int H : {8, 16, 32, 64}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, f[0], H, f[1]}});
+      for (int H : {8, 16, 32, 64}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, f[0], H, f[1]}, false});
     const int t3[4][4] = {{64, 8, 8, 256}, {32, 8, 4, 128}, {128, 8, 4, 256}, {16, 4, 4, 64}};
-    for (auto& f : t3) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], f[2], f[3]}});
+    for (auto& f : t3) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], f[2], f[3]}, false});
     for (int th : {256, 512})
       for (int TY : {4, 8, 16, 32})
-        for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, TY, H, th}});
+        for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, TY, H, th}, false});
   }
-  c.push_back({SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}});
+  c.push_back({SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, false});
+  // k_block, under the family that the automatic choice names for single sweeps
+  spin_lattice plain = *h;
+  plain.kernel = SPIN_KERNEL_AUTO;
+  plain.tile = Tile{0, 0, 0, 0};
+  Tile t;
+  bool block;
+  const int k = auto_family(&plain, &t, &block);
+  if (block && block_offered(h)) c.push_back({k, t, true});
   return c;
 }
 
@@ -809,7 +962,9 @@ spin_lattice* spin_create_config(const spin_config* cfg) {
   h->mem = Allocator{g_alloc, g_release, g_ctx};
   h->part = nullptr;
   h->part_slots = 0;
-  h->buf[0] = (int8_t*)h->mem.get(N);
+  h->block = false;
+  h->plans_made = false;
+  h->buf[0] = (int8_t*)h->mem.get(spin_bytes(h));
   h->em = (int64_t*)h->mem.get(2 * sizeof(int64_t));
   if (!h->buf[0] || !h->em) {
     fail(SPIN_ENOMEM, "device allocation of %llu bytes failed", (unsigned long long)N);
@@ -818,7 +973,7 @@ spin_lattice* spin_create_config(const spin_config* cfg) {
   }
   hipError_t e = hipSuccess;
   if (h->model == SPIN_EA_PMJ) {
-    h->J = (int8_t*)h->mem.get((size_t)cfg->d * N);
+    h->J = (int8_t*)h->mem.get((size_t)(cfg->d - 1) * N + spin_bytes(h));
     if (!h->J) {
       fail(SPIN_ENOMEM, "device allocation of couplings failed");
       destroy(h);
@@ -977,6 +1132,8 @@ int spin_set_kernel(spin_lattice* h, int kernel, int tile_x, int tile_y, int til
   if (kernel < SPIN_KERNEL_AUTO || kernel > SPIN_KERNEL_STREAM) return fail(SPIN_EINVAL, "unknown kernel family %d", kernel);
   const int old_kernel = h->kernel;
   const Tile old_tile = h->tile;
+  const bool old_block = h->block;
+  h->block = false;
   h->kernel = kernel;
   h->tile = Tile{tile_x, tile_y, tile_z, threads};
   if (kernel != SPIN_KERNEL_AUTO) {
@@ -984,6 +1141,7 @@ int spin_set_kernel(spin_lattice* h, int kernel, int tile_x, int tile_y, int til
     if (!family_ok(h, kernel, t)) {
       h->kernel = old_kernel;
       h->tile = old_tile;
+      h->block = old_block;
       return fail(SPIN_EINVAL, "kernel family %d with tile (%d,%d,%d,%d) cannot run L=%d d=%d model=%d",
                   kernel, t.x, t.y, t.z, t.threads, h->L, h->d, h->model);
     }
@@ -1019,10 +1177,11 @@ int spin_autotune(spin_lattice* h, double beta, int sweeps) {
     return hip_fail(hipGetLastError(), "autotune event");
   }
   float best_ms = 1e30f;
-  Tuned best{SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}};
+  Tuned best{SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, false};
   for (const Tuned& cand : tune_candidates(h)) {
     s->kernel = cand.kernel;
     s->tile = cand.tile;
+    s->block = cand.block;
     if (!family_ok(s, cand.kernel, default_tile(s, cand.kernel))) continue;
     if (run_sweeps(s, 1, beta, 0, nullptr, nullptr) != SPIN_OK) continue;
     if (hipEventRecord(e0, s->stream) != hipSuccess) continue;
@@ -1033,7 +1192,7 @@ int spin_autotune(spin_lattice* h, double beta, int sweeps) {
       continue;
     if (ms < best_ms) {
       best_ms = ms;
-      best = Tuned{cand.kernel, default_tile(s, cand.kernel)};
+      best = Tuned{cand.kernel, default_tile(s, cand.kernel), cand.block};
     }
   }
   (void)hipEventDestroy(e0);
@@ -1047,9 +1206,10 @@ int spin_autotune(spin_lattice* h, double beta, int sweeps) {
     g_tuned[std::make_tuple(h->model, h->L, h->d)] = best;
   }
   tune_cache_append("lattice", {h->model, h->L, h->d, best.kernel, best.tile.x, best.tile.y, best.tile.z,
-                                best.tile.threads});
+                                best.tile.threads, best.block ? 1 : 0});
   h->kernel = best.kernel;
   h->tile = best.tile;
+  h->block = best.block;
   if (int rc = prepare_buffers(h)) return rc;
   return best.kernel;
 }

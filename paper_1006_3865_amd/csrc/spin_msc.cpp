@@ -207,7 +207,7 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
   h->rec_cap = 0;
   h->stream = (hipStream_t)stream;
   if (!dalloc(&h->S, N * 4) || !dalloc(&h->J, (size_t)d * N * 4) ||
-      !dalloc(&h->part, (size_t)msc_count_parts(N) * 64 * sizeof(int64_t))) {
+      !dalloc(&h->part, (size_t)msc_count_parts((uint32_t)L, N) * 64 * sizeof(int64_t))) {
     mfail(SPIN_ENOMEM, "device allocation failed (%llu sites)", (unsigned long long)N);
     msc_destroy(h);
     return nullptr;

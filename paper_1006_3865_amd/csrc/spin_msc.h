@@ -43,8 +43,8 @@ bool msc_col_supported(uint32_t L, uint32_t d, uint32_t TY, uint32_t H);
 hipError_t launch_msc_col(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t d,
                           uint32_t TY, uint32_t H, hipStream_t stream);
 // Workgroups of the measurement (each writes 64 int64 partial counts).
-uint32_t msc_count_parts(uint64_t N);
-// E[b], M[b] (device int64[32] each) of the 32 systems; part: msc_count_parts(N) * 64 int64.
+uint32_t msc_count_parts(uint32_t L, uint64_t N);
+// E[b], M[b] (device int64[32] each) of the 32 systems; part: msc_count_parts(L, N) * 64 int64.
 hipError_t launch_msc_measure(const uint32_t* S, const uint32_t* J, uint32_t L, uint32_t d, uint64_t N, int64_t* part,
                               int64_t* E, int64_t* M, hipStream_t stream);
 

@@ -47,6 +47,7 @@
 #include "spin_block.h"
 #include "spin_device.h"
 #include "spin_lds.h"
+#include "spin_tile.h"
 
 namespace spin {
 
@@ -246,10 +247,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
   extern __shared__ __align__(16) char lds[];
   const uint32_t base = lds_addr(lds);
   const uint32_t L = a.L, NT = blockDim.x, tid = threadIdx.x;
-  // workgroups are dealt to the 8 XCDs round-robin: give each XCD a contiguous run of tiles, whose
-  // halos then come from one L2
-  const uint32_t nt = gridDim.x, q8 = nt >> 3, r8 = nt & 7u, xcd = blockIdx.x & 7u;
-  const uint32_t tile = xcd * q8 + (xcd < r8 ? xcd : r8) + (blockIdx.x >> 3);
+  const uint32_t nt = gridDim.x, tile = xcd_tile();
   const uint32_t bx = tile % a.nbx, by = tile / a.nbx;
   const uint32_t H = 2u * a.k;
   uint32_t x0 = 0, y0, z0 = 0, tx = a.TX, ty, tz = 1;
@@ -278,28 +276,10 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
   if (tid < 2u * kBlockMaxK) lds_store32(base + kBlkRec + 4u * tid, 0u);
   if (RAG)  // bytes around the rows are read (and masked later): keep them in the table's range
     for (uint32_t i = 4u * tid; i < a.plane * (EA ? 4u : 2u); i += 4u * NT) lds_store32(base + a.first + i, 0u);
-  // the row list, innermost first: shell s holds the rows s away from the edge of the region
+  // the row list (tile_row_rank)
   for (uint32_t lr = tid; lr < rows; lr += NT) {
     const uint32_t y = lr % Y, z = D == 3 ? lr / Y : 0u;
-    uint32_t s = y < Y - 1u - y ? y : Y - 1u - y;
-    uint32_t rank;
-    if (D == 3) {
-      const uint32_t sz = z < Z - 1u - z ? z : Z - 1u - z;
-      s = s < sz ? s : sz;
-      const uint32_t ny = Y - 2u * s, nz = Z - 2u * s;
-      const uint32_t inner = (ny > 2u ? ny - 2u : 0u) * (nz > 2u ? nz - 2u : 0u);
-      if (z == s)
-        rank = inner + (y - s);
-      else if (z == Z - 1u - s)
-        rank = inner + ny + (y - s);
-      else if (y == s)
-        rank = inner + 2u * ny + (z - s - 1u);
-      else
-        rank = inner + 2u * ny + (nz - 2u) + (z - s - 1u);
-    } else {
-      const uint32_t ny = Y - 2u * s;
-      rank = (ny > 2u ? ny - 2u : 0u) + (y == s ? 0u : 1u);
-    }
+    const uint32_t rank = tile_row_rank<D>(y, z, Y, Z);
     // lattice coordinates (the halo may be wider than the lattice)
     const uint32_t gy = (y0 + y + L * (H / L + 1u) - H) % L;
     const uint32_t gz = D == 3 ? (z0 + z + L * (H / L + 1u) - H) % L : 0u;
@@ -394,7 +374,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
   __syncthreads();
   BlockUnit un[M ? M : 1];
   if (M) {
-    const uint32_t most = D == 3 ? (Y - 2u) * (Z - 2u) : Y - 2u;
+    const uint32_t most = tile_rows<D>(Y, Z, 1u);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       const uint32_t idx = G.rl + m * G.rpt;
@@ -404,8 +384,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
   uint32_t rec = 0;
   for (uint32_t sweep = 0; sweep < a.k; ++sweep) {
     const uint32_t p = 2u * sweep + 1u;
-    const uint32_t n0 = D == 3 ? (Y - 2u * p) * (Z - 2u * p) : Y - 2u * p;
-    const uint32_t n1 = D == 3 ? (Y - 2u * p - 2u) * (Z - 2u * p - 2u) : Y - 2u * p - 2u;
+    const uint32_t n0 = tile_rows<D>(Y, Z, p), n1 = tile_rows<D>(Y, Z, p + 1u);
     uint32_t unsat2 = 0, neg = 0;
     blk_phase<D, EA, NEVER, RAG, false, M>(a, G, un, 0u, n0, philox_uniform(a.t + sweep, a.replica, 0u, a.keys), own_rows,
                                            own_g, unsat2, neg);

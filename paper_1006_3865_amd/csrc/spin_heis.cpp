@@ -1,10 +1,12 @@
 // spin_heis.cpp -- C ABI of the classical Heisenberg mode (spin_heis_*).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "spin.h"
@@ -29,6 +31,8 @@ struct spin_heis {
   uint32_t replica;
   uint64_t t;
   float4* S;        // [N] (x, y, z, 0)
+  float4* S2;       // second buffer of the sweeps with several colour phases per launch, or NULL
+  HeisPlan plan;    // their longest launch (k == 0: one launch per colour, in place)
   double* part;     // measurement partials: rec_cap records of heis_measure_blocks(N) x 4 doubles
   size_t rec_cap;
   hipStream_t stream;
@@ -38,6 +42,7 @@ static void heis_destroy(spin_heis* h) {
   if (!h) return;
   (void)hipStreamSynchronize(h->stream);
   device_free(h->S);
+  device_free(h->S2);
   device_free(h->part);
   delete h;
 }
@@ -57,7 +62,35 @@ static int reserve(spin_heis* h, size_t nrec) {
   return SPIN_OK;
 }
 
+// The launch shape by lattice size.  2D: the smallest tile of the list that needs no more tiles than
+// the chip has compute units (each then holds one), and up to 6 sweeps a launch (4 with the largest
+// tile, whose halo costs more); measured us a sweep against one launch per colour: L = 64 1.8 / 5.4,
+// 256 2.3 / 5.6, 512 3.2 / 6.8, 1024 7.0 / 13.7, 4096 96 / 155.  3D: two sweeps a launch up to L = 64
+// (L = 32 3.9 / 6.0, 64 6.8 / 7.4); above that the recomputed halo of a 3D tile costs more than the
+// launch and the traffic it saves (L = 100 18.0 / 14.0, 256 208 / 156).
+static HeisPlan heis_plan(uint32_t L, uint32_t d) {
+  HeisPlan p{0, 0, 0, 1, 0};
+  auto cut = [&](uint32_t k, uint32_t tx, uint32_t ty, uint32_t tz, uint32_t threads) {
+    return HeisPlan{k, std::min(tx, L), std::min(ty, L), d == 3 ? std::min(tz, L) : 1u, threads};
+  };
+  if (d == 2) {
+    const uint32_t side[7][2] = {{8, 4}, {8, 8}, {16, 8}, {16, 16}, {32, 16}, {32, 32}, {64, 32}};
+    for (auto& t : side) {
+      p = cut(t[0] == 64 ? 4 : 6, t[0], t[1], 1, t[0] * t[1] <= 64 ? 512 : 1024);
+      if (heis_block_tiles(L, d, p) <= 256) break;
+    }
+    return p;
+  }
+  if (L <= 16) return cut(2, 4, 4, 4, 512);
+  if (L <= 32) return cut(2, 8, 4, 4, 1024);
+  if (L <= 64) return cut(2, 16, 8, 8, 1024);
+  return p;
+}
+
 // Enqueue n sweeps; after every every-th sweep (every > 0) a measurement into record slot r.
+// With a plan, the sweeps between two records are cut into launches of at most plan.k sweeps; the
+// launches of a call are made even in number (one cut more, or the last sweep by the in-place
+// kernels), so that the call leaves the spins in the buffer it found them in.
 static int heis_run(spin_heis* h, int n, double beta, int every) {
   if (n < 0) return hfail(SPIN_EINVAL, "n must be >= 0");
   if (std::isnan(beta) || beta < 0) return hfail(SPIN_EINVAL, "beta must be >= 0 (got %g)", beta);
@@ -71,15 +104,47 @@ static int heis_run(spin_heis* h, int n, double beta, int every) {
   a.replica = h->replica;
   a.beta = (float)beta;
   const size_t stride = (size_t)heis_measure_blocks(h->N) * 4;
-  size_t rec = 0;
-  for (int i = 0; i < n; ++i) {
-    a.t = (uint32_t)(h->t + (uint64_t)i);
-    for (uint32_t c = 0; c < 2; ++c) {
-      a.colour = c;
-      hipError_t e = launch_heis_phase(h->S, (uint32_t)h->d, a, h->stream);
-      if (e != hipSuccess) return hfail(SPIN_EDEVICE, "Heisenberg phase launch: %s", hipGetErrorString(e));
+  const uint32_t kmax = h->S2 ? h->plan.k : 0;
+  const uint32_t seg = every > 0 ? (uint32_t)every : (uint32_t)n;  // sweeps between records
+  auto cuts = [&](uint32_t g) { return (g + kmax - 1) / kmax; };
+  bool one_more = false, last_in_place = false;
+  if (kmax && n > 0) {
+    const uint32_t whole = (uint32_t)n / seg, rest = (uint32_t)n % seg;
+    const uint32_t total = whole * cuts(seg) + (rest ? cuts(rest) : 0);
+    if (total & 1u) {
+      // one cut more where a launch has two sweeps, else the last sweep in place
+      one_more = (whole && cuts(seg) < seg) || (rest && cuts(rest) < rest);
+      last_in_place = !one_more;
     }
-    if (every > 0 && (i + 1) % every == 0) {
+  }
+  size_t rec = 0;
+  uint32_t i = 0;
+  while (i < (uint32_t)n) {
+    const uint32_t g = std::min<uint32_t>(seg, (uint32_t)n - i);
+    uint32_t m = kmax ? cuts(g) : g;
+    if (one_more && m < g) {
+      ++m;
+      one_more = false;
+    }
+    for (uint32_t q = 0; q < m; ++q) {
+      a.t = (uint32_t)(h->t + i);
+      const uint32_t k = g / m + (q < g % m ? 1u : 0u);
+      hipError_t e = hipSuccess;
+      if (kmax && !(last_in_place && i + k == (uint32_t)n)) {
+        HeisPlan p = h->plan;
+        p.k = k;
+        e = launch_heis_block(h->S, h->S2, (uint32_t)h->d, a, p, h->stream);
+        if (e == hipSuccess) std::swap(h->S, h->S2);
+      } else {
+        for (uint32_t c = 0; c < 2 && e == hipSuccess; ++c) {
+          a.colour = c;
+          e = launch_heis_phase(h->S, (uint32_t)h->d, a, h->stream);
+        }
+      }
+      if (e != hipSuccess) return hfail(SPIN_EDEVICE, "Heisenberg sweep launch: %s", hipGetErrorString(e));
+      i += k;
+    }
+    if (every > 0 && g == seg) {
       hipError_t e = launch_heis_measure(h->S, (uint32_t)h->L, (uint32_t)h->d, h->N, h->part + rec * stride, h->stream);
       if (e != hipSuccess) return hfail(SPIN_EDEVICE, "Heisenberg measure launch: %s", hipGetErrorString(e));
       ++rec;
@@ -128,6 +193,7 @@ spin_heis* spin_heis_create(int L, int d, uint64_t seed, uint32_t replica, void*
   h->replica = replica;
   h->t = 0;
   h->S = nullptr;
+  h->S2 = nullptr;
   h->part = nullptr;
   h->rec_cap = 0;
   h->stream = (hipStream_t)stream;
@@ -137,6 +203,9 @@ spin_heis* spin_heis_create(int L, int d, uint64_t seed, uint32_t replica, void*
     heis_destroy(h);
     return nullptr;
   }
+  // the second buffer is not needed to run: without it the sweeps run in place
+  h->plan = heis_plan((uint32_t)L, (uint32_t)d);
+  if (h->plan.k && heis_block_ok((uint32_t)L, (uint32_t)d, N, h->plan)) h->S2 = (float4*)device_alloc(N * sizeof(float4));
   hipError_t e = launch_heis_init(h->S, N, seed, replica, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) {

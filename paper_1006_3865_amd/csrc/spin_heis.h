@@ -19,6 +19,16 @@ struct HeisArgs {
 };
 
 hipError_t launch_heis_init(float4* S, uint64_t N, uint64_t seed, uint32_t replica, hipStream_t stream);
+// Shape of a k_heis_block launch: k sweeps of tiles of TX (even) by TY (by TZ) sites.
+struct HeisPlan {
+  uint32_t k, TX, TY, TZ, threads;
+};
+bool heis_block_ok(uint32_t L, uint32_t d, uint64_t N, const HeisPlan& p);
+uint32_t heis_block_tiles(uint32_t L, uint32_t d, const HeisPlan& p);
+size_t heis_block_lds(uint32_t d, const HeisPlan& p);
+// p.k sweeps from a.t on, from src into dst (a.colour is not used).
+hipError_t launch_heis_block(const float4* src, float4* dst, uint32_t d, const HeisArgs& a, const HeisPlan& p,
+                             hipStream_t stream);
 // One colour phase (d = 2 or 3), in place.
 hipError_t launch_heis_phase(float4* S, uint32_t d, const HeisArgs& a, hipStream_t stream);
 // heis_measure_blocks(N) workgroups each write (E, Mx, My, Mz) as 4 doubles into part.

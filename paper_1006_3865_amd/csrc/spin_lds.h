@@ -32,4 +32,15 @@ __device__ __forceinline__ void lds_store64(uint32_t at, uint2 v) {
   *(__attribute__((address_space(3))) lds_u2*)(uintptr_t)at = w;
 }
 
+__device__ __forceinline__ float4 lds_load128(uint32_t at) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4 v = *(__attribute__((address_space(3))) const f4*)(uintptr_t)at;
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void lds_store128(uint32_t at, const float4& v) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4 w = {v.x, v.y, v.z, v.w};
+  *(__attribute__((address_space(3))) f4*)(uintptr_t)at = w;
+}
+
 }  // namespace spin

@@ -33,4 +33,10 @@ BlockPlan block_plan(const Lat& lat, uint32_t k, double* us);
 hipError_t launch_block(const Lat& lat, const int8_t* src, int8_t* dst, uint32_t t, const Accept& acc,
                         const BlockPlan& p, uint32_t rec_mask, int64_t* part, hipStream_t stream);
 
+// n sweeps of a whole small lattice by one workgroup, in place (k_whole): its estimated time in
+// microseconds (< 0: it cannot run this lattice), and the launch; E, M: device arrays of n / every.
+double whole_us(const Lat& lat, const Accept& acc, uint32_t n);
+hipError_t launch_whole(const Lat& lat, uint32_t t, uint32_t n, const Accept& acc, uint32_t every, int64_t* E, int64_t* M,
+                        hipStream_t stream);
+
 }  // namespace spin

@@ -43,6 +43,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "spin_block.h"
 #include "spin_device.h"
@@ -91,6 +92,38 @@ __device__ __forceinline__ uint2 blk_join(uint32_t even, uint32_t odd) {
   return make_uint2(__builtin_amdgcn_perm(o, e, 0x05010400u), __builtin_amdgcn_perm(o, e, 0x07030602u));
 }
 
+// The entry of lattice row (gy, gz) whose LDS row begins at byte `at` of plane 0 (RAG: after a pad dword).
+template <int D, bool RAG>
+__device__ __forceinline__ uint2 blk_row(uint32_t at, uint32_t gy, uint32_t gz, uint32_t L, uint32_t GPR) {
+  const uint32_t row = gz * L + gy;
+  uint2 e;
+  e.x = (at + (RAG ? 4u : 0u)) | ((gy + gz) & 1u);
+  if (RAG) {
+    const uint32_t o2 = ((row * L) >> 1) & 3u;  // low bits of a product: no overflow matters
+    e.x |= o2 << 18;
+    const uint32_t nb[4] = {gz * L + (gy ? gy - 1u : L - 1u), gz * L + (gy + 1u < L ? gy + 1u : 0u),
+                            (gz ? gz - 1u : L - 1u) * L + gy, (gz + 1u < L ? gz + 1u : 0u) * L + gy};
+#pragma unroll
+    for (int i = 0; i < 2 * D - 2; ++i) e.x |= (((((nb[i] * L) >> 1) & 3u) - o2) & 7u) << (20 + 3 * i);
+    e.y = (uint32_t)(((uint64_t)row * L) >> 3);
+  } else {
+    e.y = row * GPR;
+  }
+  return e;
+}
+
+// The accept-bound pairs by v / 2 = n + 8 a of two sites, at LDS address base.
+template <int D>
+__device__ __forceinline__ void blk_fill_table(uint32_t base, const uint32_t (&bound)[8]) {
+  for (uint32_t i = threadIdx.x; i < 225u; i += blockDim.x) {
+    constexpr uint32_t z2 = 2u * (uint32_t)D;
+    const uint32_t i0 = i % 15u, i1 = i / 15u;
+    const uint32_t u0 = (i0 & 7u) > z2 ? 0u : ((i0 & 8u) ? z2 - (i0 & 7u) : (i0 & 7u));
+    const uint32_t u1 = (i1 & 7u) > z2 ? 0u : ((i1 & 8u) ? z2 - (i1 & 7u) : (i1 & 7u));
+    lds_store64(base + 8u * i, make_uint2(bound[u0], bound[u1]));
+  }
+}
+
 // What a thread keeps for the whole launch.
 struct BlockGeo {
   uint32_t base;        // LDS address of the workgroup's memory
@@ -120,16 +153,59 @@ __device__ __forceinline__ uint32_t lds_nb(uint32_t at, int sh) {
   return __builtin_amdgcn_alignbyte(lds_load32(lo + 4u), lds_load32(lo), (uint32_t)sh & 3u);
 }
 
+// An 8-site group as loaded (w[0]; with couplings w[1..D], a word per direction) into the planes.
+template <int D, bool EA, bool RAG>
+__device__ __forceinline__ void blk_put(const BlockArgs& a, const BlockGeo& G, uint32_t at, uint32_t ex,
+                                        const blk_u2 (&w)[EA ? D + 1 : 1]) {
+  const uint32_t vm = RAG ? rag_mask(G, row_o2(ex)) : 0xFFFFFFFFu;
+  const bool odd = (ex & 1u) != 0;  // colour-0 sites of the row are its odd x
+  const uint2 h = blk_split(w[0].x & kNeg, w[0].y & kNeg);
+  lds_store32(at, (odd ? h.y : h.x) & vm);
+  lds_store32(at + a.plane, (odd ? h.x : h.y) & vm);
+  if (EA) {
+    uint32_t lo = (w[1].x & kNeg) | (w[EA ? 2 : 0].x & (kNeg << 1)), hi = (w[1].y & kNeg) | (w[EA ? 2 : 0].y & (kNeg << 1));
+    if (D == 3) {
+      lo |= w[EA ? D : 0].x & (kNeg << 2);
+      hi |= w[EA ? D : 0].y & (kNeg << 2);
+    }
+    const uint2 j = blk_split(lo, hi);
+    lds_store32(at + a.jplane, (odd ? j.y : j.x) & vm);
+    lds_store32(at + a.jplane + a.plane, (odd ? j.x : j.y) & vm);
+  }
+}
+
 // A unit: the group of a listed row that a thread updates.
 struct BlockUnit {
   uint32_t at;   // LDS address of its dword in plane 0
   uint32_t ex;   // the row's list word (parity and RAG fields)
   uint32_t ctr;  // its Philox counter
+  uint32_t ym, yp, zm, zp;  // LDS bytes to the neighbour rows (the same for all units of a tile with halos)
 };
 
 __device__ __forceinline__ BlockUnit blk_unit(const BlockGeo& G, uint32_t idx) {
   const uint2 e = lds_load64(G.base + kBlkList + 8u * idx);
-  return BlockUnit{G.base + row_at(e.x) + G.g4, e.x, e.y + G.gx};
+  return BlockUnit{G.base + row_at(e.x) + G.g4, e.x, e.y + G.gx, 0u - G.sy, G.sy, 0u - G.sz, G.sz};
+}
+
+// A unit's group from the planes to the lattice.
+template <bool RAG>
+__device__ __forceinline__ void blk_get(const BlockArgs& a, const BlockGeo& G, const BlockUnit& u, int8_t* dst) {
+  const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc((void*)dst, 0, (int)a.nbytes, 0x00020000);
+  const uint32_t c0 = lds_load32(u.at), c1 = lds_load32(u.at + a.plane);
+  const bool odd = (u.ex & 1u) != 0;
+  const uint2 w = blk_join(odd ? c1 : c0, odd ? c0 : c1);
+  const uint32_t off = 8u * u.ctr;
+  const uint32_t vm = RAG ? rag_mask(G, row_o2(u.ex)) : 0xFFFFFFFFu;
+  if (vm == 0xFFFFFFFFu) {
+    const blk_u2 o = {w.x, w.y};
+    __builtin_amdgcn_raw_buffer_store_b64(o, rd, off, 0, 0);
+  } else {
+    // a group shared with the row before or after: only this row's site pairs
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i)
+      if ((vm >> (8u * i)) & 1u)
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)((i < 2 ? w.x : w.y) >> (16u * (i & 1u))), rd, off + 2u * i, 0, 0);
+  }
 }
 
 // Colour c of a unit with its draws.  MEAS: where own (the tile), adds twice the unsatisfied bonds
@@ -155,11 +231,11 @@ __device__ __forceinline__ void blk_update(const BlockArgs& a, const BlockGeo& G
     const uint32_t wrap = lds_load8(ao - G.g4 + (P ? b0 : b1));
     N = (N & ~wmask) | ((wrap << wsh) & wmask);
   }
-  const uint32_t ym = lds_nb<RAG>(ao - G.sy, row_shift<0>(u.ex)), yp = lds_nb<RAG>(ao + G.sy, row_shift<1>(u.ex));
+  const uint32_t ym = lds_nb<RAG>(ao + u.ym, row_shift<0>(u.ex)), yp = lds_nb<RAG>(ao + u.yp, row_shift<1>(u.ex));
   uint32_t zm = 0, zp = 0;
   if (D == 3) {
-    zm = lds_nb<RAG>(ao - G.sz, row_shift<2>(u.ex));
-    zp = lds_nb<RAG>(ao + G.sz, row_shift<3>(u.ex));
+    zm = lds_nb<RAG>(ao + u.zm, row_shift<2>(u.ex));
+    zp = lds_nb<RAG>(ao + u.zp, row_shift<3>(u.ex));
   }
   uint32_t nn;  // 2 n per byte
   if (EA) {
@@ -173,11 +249,11 @@ __device__ __forceinline__ void blk_update(const BlockArgs& a, const BlockGeo& G
       left = (left & ~wmask) | ((wrap << wsh) & wmask);  // used where P = 0 only
     }
     const uint32_t jI = P ? oth : own_j, jN = P ? own_j : left;
-    const uint32_t jym = lds_nb<RAG>(jo - G.sy, row_shift<0>(u.ex));
+    const uint32_t jym = lds_nb<RAG>(jo + u.ym, row_shift<0>(u.ex));
     nn = ((I ^ jI) & kNeg) + ((N ^ jN) & kNeg);
     nn += ((yp ^ (own_j >> 1)) & kNeg) + ((ym ^ (jym >> 1)) & kNeg);
     if (D == 3) {
-      const uint32_t jzm = lds_nb<RAG>(jo - G.sz, row_shift<2>(u.ex));
+      const uint32_t jzm = lds_nb<RAG>(jo + u.zm, row_shift<2>(u.ex));
       nn += ((zp ^ (own_j >> 2)) & kNeg) + ((zm ^ (jzm >> 2)) & kNeg);
     }
   } else {
@@ -265,14 +341,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
   const uint32_t Y = ty + 2u * H, Z = D == 3 ? tz + 2u * H : 1u;
   const uint32_t RS = 4u * GW + (RAG ? 8u : 0u);  // RAG: a dword before and after each row
   const uint32_t rows = Y * Z, own_rows = ty * tz;
-  // accept-bound pairs by v / 2 = n + 8 a of two sites
-  for (uint32_t i = tid; i < 225u; i += NT) {
-    constexpr uint32_t z2 = 2u * (uint32_t)D;
-    const uint32_t i0 = i % 15u, i1 = i / 15u;
-    const uint32_t u0 = (i0 & 7u) > z2 ? 0u : ((i0 & 8u) ? z2 - (i0 & 7u) : (i0 & 7u));
-    const uint32_t u1 = (i1 & 7u) > z2 ? 0u : ((i1 & 8u) ? z2 - (i1 & 7u) : (i1 & 7u));
-    lds_store64(base + 8u * i, make_uint2(a.bound[u0], a.bound[u1]));
-  }
+  blk_fill_table<D>(base, a.bound);
   if (tid < 2u * kBlockMaxK) lds_store32(base + kBlkRec + 4u * tid, 0u);
   if (RAG)  // bytes around the rows are read (and masked later): keep them in the table's range
     for (uint32_t i = 4u * tid; i < a.plane * (EA ? 4u : 2u); i += 4u * NT) lds_store32(base + a.first + i, 0u);
@@ -283,21 +352,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
     // lattice coordinates (the halo may be wider than the lattice)
     const uint32_t gy = (y0 + y + L * (H / L + 1u) - H) % L;
     const uint32_t gz = D == 3 ? (z0 + z + L * (H / L + 1u) - H) % L : 0u;
-    const uint32_t row = gz * L + gy;
-    uint2 e;
-    e.x = (a.first + lr * RS + (RAG ? 4u : 0u)) | ((gy + gz) & 1u);
-    if (RAG) {
-      const uint32_t o2 = ((row * L) >> 1) & 3u;  // low bits of a product: no overflow matters
-      e.x |= o2 << 18;
-      const uint32_t nb[4] = {gz * L + (gy ? gy - 1u : L - 1u), gz * L + (gy + 1u < L ? gy + 1u : 0u),
-                              (gz ? gz - 1u : L - 1u) * L + gy, (gz + 1u < L ? gz + 1u : 0u) * L + gy};
-#pragma unroll
-      for (int i = 0; i < 2 * D - 2; ++i) e.x |= (((((nb[i] * L) >> 1) & 3u) - o2) & 7u) << (20 + 3 * i);
-      e.y = (uint32_t)(((uint64_t)row * L) >> 3);
-    } else {
-      e.y = row * a.GPR;
-    }
-    lds_store64(base + kBlkList + 8u * rank, e);
+    lds_store64(base + kBlkList + 8u * rank, blk_row<D, RAG>(a.first + lr * RS, gy, gz, L, a.GPR));
   }
   keys_resident(a.keys);
   BlockGeo G;
@@ -351,22 +406,7 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
         if (i0 + u * G.rpt < rows) {
-          const uint32_t at = base + row_at(e[u].x) + G.g4;
-          const uint32_t vm = RAG ? rag_mask(G, row_o2(e[u].x)) : 0xFFFFFFFFu;
-          const bool odd = (e[u].x & 1u) != 0;  // colour-0 sites of the row are its odd x
-          const uint2 h = blk_split(w[u][0].x & kNeg, w[u][0].y & kNeg);
-          lds_store32(at, (odd ? h.y : h.x) & vm);
-          lds_store32(at + a.plane, (odd ? h.x : h.y) & vm);
-          if (EA) {
-            uint32_t lo = (w[u][1].x & kNeg) | (w[u][2].x & (kNeg << 1)), hi = (w[u][1].y & kNeg) | (w[u][2].y & (kNeg << 1));
-            if (D == 3) {
-              lo |= w[u][W - 1].x & (kNeg << 2);
-              hi |= w[u][W - 1].y & (kNeg << 2);
-            }
-            const uint2 j = blk_split(lo, hi);
-            lds_store32(at + a.jplane, (odd ? j.y : j.x) & vm);
-            lds_store32(at + a.jplane + a.plane, (odd ? j.x : j.y) & vm);
-          }
+          blk_put<D, EA, RAG>(a, G, G.base + row_at(e[u].x) + G.g4, e[u].x, w[u]);
         }
       }
     }
@@ -404,33 +444,109 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
     __syncthreads();
   }
   // the tile's rows to dst
-  const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc((void*)dst, 0, (int)a.nbytes, 0x00020000);
-  if (own_g) {
-    for (uint32_t idx = G.rl; idx < own_rows; idx += G.rpt) {
-      const uint2 e = lds_load64(base + kBlkList + 8u * idx);
-      const uint32_t at = base + row_at(e.x) + G.g4;
-      const uint32_t c0 = lds_load32(at), c1 = lds_load32(at + a.plane);
-      const bool odd = (e.x & 1u) != 0;
-      const uint2 w = blk_join(odd ? c1 : c0, odd ? c0 : c1);
-      const uint32_t off = 8u * (e.y + G.gx);
-      const uint32_t vm = RAG ? rag_mask(G, row_o2(e.x)) : 0xFFFFFFFFu;
-      if (vm == 0xFFFFFFFFu) {
-        const blk_u2 o = {w.x, w.y};
-        __builtin_amdgcn_raw_buffer_store_b64(o, rd, off, 0, 0);
-      } else {
-        // a group shared with the row before or after: only this row's site pairs
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i)
-          if ((vm >> (8u * i)) & 1u)
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)((i < 2 ? w.x : w.y) >> (16u * (i & 1u))), rd, off + 2u * i, 0, 0);
-      }
-    }
-  }
+  if (own_g)
+    for (uint32_t idx = G.rl; idx < own_rows; idx += G.rpt) blk_get<RAG>(a, G, blk_unit(G, idx), dst);
   if (tid < 2u * rec) {
     const uint32_t r = tid >> 1, s = tid & 1u;
     const uint32_t v = lds_load32(base + kBlkRec + 4u * tid);
     part[((uint64_t)r * nt + tile) * 2u + s] = (int64_t)(s ? v : v >> 1);
   }
+}
+
+// ---------------------------------------------------------------------------
+// n sweeps of a whole small lattice by one workgroup (k_whole), in place: the
+// planes of k_block without a halo (neighbour rows wrap), every thread with
+// at most M units whose places it keeps in registers, (E, M) written after
+// every every-th sweep.  A sweep is two phases of LDS and Philox latency and a
+// barrier each, with nothing else a launch would add, so it is the
+// fastest form while one compute unit's issue is not the bound: 2D L = 64 0.55 us
+// a sweep (k_block 0.96 in launches of 8 sweeps, the nibble kernel of the pool 2.2).
+template <int D, bool EA, bool NEVER, bool RAG, int M>
+__global__ __launch_bounds__(1024) void k_whole(int8_t* __restrict__ spins, const int8_t* __restrict__ J, BlockArgs a,
+                                                uint32_t n, uint32_t every, int64_t* __restrict__ E,
+                                                int64_t* __restrict__ Mg) {
+  extern __shared__ __align__(16) char lds[];
+  const uint32_t base = lds_addr(lds), tid = threadIdx.x, L = a.L, GW = a.TX;
+  const uint32_t rows = D == 3 ? L * L : L, RS = 4u * GW + (RAG ? 8u : 0u);
+  blk_fill_table<D>(base, a.bound);
+  if (tid < 4u) lds_store32(base + kBlkRec + 4u * tid, 0u);
+  if (RAG)
+    for (uint32_t i = 4u * tid; i < a.plane * (EA ? 4u : 2u); i += 4u * blockDim.x) lds_store32(base + a.first + i, 0u);
+  keys_resident(a.keys);
+  BlockGeo G;
+  G.base = base;
+  G.rpt = blockDim.x / GW;
+  G.rl = tid / GW;
+  G.gx = tid - G.rl * GW;
+  G.g4 = 4u * G.gx;
+  if (G.rl >= G.rpt) G.rl = 0x7FFFFFFFu;
+  G.adjm = RAG || G.gx ? 0u - 4u : 4u * (GW - 1u);
+  G.adjp = RAG || G.gx + 1u < GW ? 4u : 0u - 4u * (GW - 1u);
+  G.sy = RS;
+  G.sz = RS * L;
+  G.half = L / 2u;
+  __syncthreads();
+  BlockUnit un[M];
+  {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)spins, 0, (int)a.nbytes, 0x00020000);
+    const uint32_t jbytes = (D - 1) * a.jstride + a.nbytes;
+    const __amdgpu_buffer_rsrc_t rj = __builtin_amdgcn_make_buffer_rsrc((void*)J, 0, EA ? (int)jbytes : 0, 0x00020000);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const uint32_t row = G.rl + m * G.rpt;
+      if (row >= rows) continue;
+      const uint32_t z = D == 3 ? row / L : 0u, y = row - z * L;
+      const uint2 e = blk_row<D, RAG>(a.first + row * RS, y, z, L, a.GPR);
+      un[m] = BlockUnit{base + row_at(e.x) + G.g4,
+                        e.x,
+                        e.y + G.gx,
+                        y ? 0u - G.sy : G.sy * (L - 1u),
+                        y + 1u < L ? G.sy : 0u - G.sy * (L - 1u),
+                        z ? 0u - G.sz : G.sz * (L - 1u),
+                        z + 1u < L ? G.sz : 0u - G.sz * (L - 1u)};
+      blk_u2 w[EA ? D + 1 : 1];
+      w[0] = __builtin_amdgcn_raw_buffer_load_b64(rs, 8u * un[m].ctr, 0, 0);
+#pragma unroll
+      for (int dir = 0; dir < (EA ? D : 0); ++dir)
+        w[EA ? dir + 1 : 0] = __builtin_amdgcn_raw_buffer_load_b64(rj, 8u * un[m].ctr, dir * a.jstride, 0);
+      blk_put<D, EA, RAG>(a, G, un[m].at, e.x, w);
+    }
+  }
+  __syncthreads();
+  const int64_t N = D == 3 ? (int64_t)L * L * L : (int64_t)L * L;
+  uint32_t due = every, rec = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    uint32_t unsat2 = 0, neg = 0;
+    blk_phase<D, EA, NEVER, RAG, false, M>(a, G, un, 0u, rows, philox_uniform(a.t + i, a.replica, 0u, a.keys), rows, true,
+                                           unsat2, neg);
+    __syncthreads();
+    const PhiloxUniform U1 = philox_uniform(a.t + i, a.replica, 1u, a.keys);
+    if (every && --due == 0) {
+      due = every;
+      blk_phase<D, EA, NEVER, RAG, true, M>(a, G, un, 1u, rows, U1, rows, true, unsat2, neg);
+      const int64_t su = wave_count_dpp(unsat2), sn = wave_count_dpp(neg);
+      // two slots in turn: one is added to while thread 0 takes and clears the other
+      uint32_t* slot = reinterpret_cast<uint32_t*>(lds + kBlkRec) + 2u * (rec & 1u);
+      if ((tid & 63u) == 0) {
+        atomicAdd(slot, (uint32_t)su);
+        atomicAdd(slot + 1, (uint32_t)sn);
+      }
+      __syncthreads();
+      if (tid == 0) {
+        E[rec] = -(int64_t)D * N + (int64_t)slot[0];
+        Mg[rec] = N - 2 * (int64_t)slot[1];
+        slot[0] = 0;
+        slot[1] = 0;
+      }
+      ++rec;
+    } else {
+      blk_phase<D, EA, NEVER, RAG, false, M>(a, G, un, 1u, rows, U1, rows, true, unsat2, neg);
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+    if (G.rl + m * G.rpt < rows) blk_get<RAG>(a, G, un[m], spins);
 }
 
 // ------------------------------------------------------------------ host
@@ -582,6 +698,102 @@ static hipError_t go_block_m(uint32_t passes, const int8_t* src, int8_t* dst, co
   if (passes <= 2) return go_block<D, EA, NEVER, RAG, 2>(src, dst, J, a, tiles, threads, lds, part, stream);
   if (!RAG && passes <= 4) return go_block<D, EA, NEVER, false, RAG ? 0 : 4>(src, dst, J, a, tiles, threads, lds, part, stream);
   return go_block<D, EA, NEVER, RAG, 0>(src, dst, J, a, tiles, threads, lds, part, stream);
+}
+
+// k_whole: threads (whole rows of groups) and units a thread has; 0 where the lattice is too large.
+static uint32_t whole_passes(const Lat& lat, uint32_t* threads) {
+  const uint32_t GW = is_rag(lat) ? (lat.L + 13u) / 8u : lat.L / 8u;
+  const uint64_t rows = lat.N / lat.L;
+  if (lat.N > 65536 || GW > 1024) return 0;
+  const uint64_t units = rows * GW;
+  *threads = units <= 256 ? 256u : (units <= 512 ? 512u : 1024u);
+  const uint64_t m = (rows + *threads / GW - 1) / (*threads / GW);
+  if (m > (is_rag(lat) ? 2u : 4u)) {
+    *threads = 1024;
+    return 0;
+  }
+  return (uint32_t)m;
+}
+
+static BlockArgs whole_args(const Lat& lat, size_t* lds) {
+  BlockArgs a;
+  const bool rag = is_rag(lat);
+  a.keys = lat.keys;
+  a.L = lat.L;
+  a.GPR = lat.L / 8u;
+  a.k = 1;
+  a.replica = lat.replica;
+  a.TX = rag ? (lat.L + 13u) / 8u : a.GPR;
+  a.TY = a.TZ = a.nbx = a.hx = 0;
+  const uint32_t RS = 4u * a.TX + (rag ? 8u : 0u);
+  a.first = kBlkList;
+  a.plane = ((uint32_t)(lat.N / lat.L) * RS + 15u) & ~15u;
+  a.jplane = 2u * a.plane;
+  a.rec_mask = 0;
+  a.nbytes = (uint32_t)((lat.N + 7u) & ~(uint64_t)7u);
+  a.jstride = (uint32_t)lat.N;
+  *lds = (size_t)a.first + (size_t)a.plane * (lat.J ? 4u : 2u);
+  return a;
+}
+
+// Estimated microseconds of n sweeps, by the constants of block_us; < 0: k_whole cannot run it.
+double whole_us(const Lat& lat, const Accept& acc, uint32_t n) {
+  uint32_t threads = 0;
+  size_t lds = 0;
+  const uint32_t m = whole_passes(lat, &threads);
+  if (m == 0 || !block_lattice_ok(lat, acc)) return -1.0;
+  const BlockArgs a = whole_args(lat, &lds);
+  if (lds > 160u * 1024u) return -1.0;
+  const bool rag = is_rag(lat);
+  const double issue = (lat.d == 2 ? 0.1117 : 0.1339) * (lat.J ? 1.14 : 1.0) * (rag ? 1.67 : 1.0);
+  const double waves = (double)(lat.N / lat.L) * a.TX / 64.0;
+  return 3.57 + n * 2.0 * (0.121 + std::max(issue * waves / 4.0, 0.179 * m));
+}
+
+template <int D, bool EA, bool NEVER, bool RAG, int M>
+static hipError_t go_whole_m(int8_t* spins, const int8_t* J, const BlockArgs& a, uint32_t threads, size_t lds, uint32_t n,
+                             uint32_t every, int64_t* E, int64_t* Mg, hipStream_t stream) {
+  static bool attr = false;
+  if (!attr) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_whole<D, EA, NEVER, RAG, M>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  hipLaunchKernelGGL((k_whole<D, EA, NEVER, RAG, M>), dim3(1), dim3(threads), lds, stream, spins, J, a, n, every, E, Mg);
+  return hipGetLastError();
+}
+
+template <int D, bool EA, bool NEVER, bool RAG>
+static hipError_t go_whole(uint32_t m, int8_t* spins, const int8_t* J, const BlockArgs& a, uint32_t threads, size_t lds,
+                           uint32_t n, uint32_t every, int64_t* E, int64_t* Mg, hipStream_t stream) {
+  if (m <= 1) return go_whole_m<D, EA, NEVER, RAG, 1>(spins, J, a, threads, lds, n, every, E, Mg, stream);
+  if (m <= 2) return go_whole_m<D, EA, NEVER, RAG, 2>(spins, J, a, threads, lds, n, every, E, Mg, stream);
+  return go_whole_m<D, EA, NEVER, RAG, RAG ? 2 : 4>(spins, J, a, threads, lds, n, every, E, Mg, stream);
+}
+
+// n sweeps t .. t+n-1 in place, (E, M) after every every-th (0: none) into E, M.
+hipError_t launch_whole(const Lat& lat, uint32_t t, uint32_t n, const Accept& acc, uint32_t every, int64_t* E, int64_t* Mg,
+                        hipStream_t stream) {
+  uint32_t threads = 0;
+  size_t lds = 0;
+  const uint32_t m = whole_passes(lat, &threads);
+  if (m == 0 || !block_lattice_ok(lat, acc)) return hipErrorInvalidValue;
+  BlockArgs a = whole_args(lat, &lds);
+  if (lds > 160u * 1024u) return hipErrorInvalidValue;
+  for (int i = 0; i < 8; ++i) a.bound[i] = acc.bound[i];
+  a.t = t;
+  const bool never = acc.never_level > 0, rag = is_rag(lat), ea = lat.J != nullptr;
+  auto go = [&](auto d, auto j, auto v, auto r) {
+    return go_whole<decltype(d)::value, decltype(j)::value, decltype(v)::value, decltype(r)::value>(
+        m, lat.spins, lat.J, a, threads, lds, n, every, E, Mg, stream);
+  };
+  using std::false_type;
+  using std::true_type;
+  auto go_r = [&](auto d, auto j, auto v) { return rag ? go(d, j, v, true_type{}) : go(d, j, v, false_type{}); };
+  auto go_v = [&](auto d, auto j) { return never ? go_r(d, j, true_type{}) : go_r(d, j, false_type{}); };
+  auto go_j = [&](auto d) { return ea ? go_v(d, true_type{}) : go_v(d, false_type{}); };
+  return lat.d == 2 ? go_j(std::integral_constant<int, 2>{}) : go_j(std::integral_constant<int, 3>{});
 }
 
 template <int D, bool EA>

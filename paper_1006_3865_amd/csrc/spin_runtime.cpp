@@ -247,6 +247,8 @@ struct spin_lattice {
   int64_t* em;       // 2 int64: spin_measure's output
   int64_t* part;     // partial counts of records (grown on demand)
   size_t part_slots; // capacity in int64
+  int64_t* rec;      // spin_sweep_record's device records (grown on demand): E, then M
+  size_t rec_cap;    // capacity in records
   uint64_t seed;
   uint32_t replica;
   uint64_t t;
@@ -301,6 +303,7 @@ static void destroy(spin_lattice* h) {
   h->mem.put(h->J);
   h->mem.put(h->em);
   h->mem.put(h->part);
+  h->mem.put(h->rec);
   h->mem.put(h->single);
   h->mem.put(h->jn);
   h->mem.put(h->lcg);
@@ -465,7 +468,7 @@ static int resolve(const spin_lattice* h, Tile* tile, bool* block = nullptr) {
   return auto_family(h, tile, block);
 }
 
-// Lattices k_block is offered: below 32^2 sites one workgroup's LDS (the resident kernels) is as fast.
+// Lattices k_block is offered: below 32^2 sites one workgroup is always faster.
 static bool block_offered(const spin_lattice* h) {
   return h->N >= 1024 && h->L >= 8 && (h->N + 8) * (h->model == SPIN_EA_PMJ ? h->d : 1) < ((uint64_t)1 << 31);
 }
@@ -655,12 +658,13 @@ static int run_lcg(spin_lattice* h, int n, const Accept& acc, int every, int64_t
 // one tile shape.  The number has the parity that leaves the current buffer where the family's own
 // launches would (n for the ping-pong families, even for those in place), so that a captured
 // call can be replayed as before.
-static uint32_t block_launches(spin_lattice* h, int n, int kernel, BlockPlan* plan) {
+static uint32_t block_launches(spin_lattice* h, int n, int kernel, BlockPlan* plan, double* us_out) {
   make_plans(h);
   const bool pingpong = kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM;
   const uint32_t odd = pingpong ? (uint32_t)n & 1u : 0u;
   uint32_t best = 0;
-  double best_us = 1e300;
+  double& best_us = *us_out;
+  best_us = 1e300;
   for (uint32_t k = 1; k <= kBlockMaxK; ++k) {
     if (h->plans[k].k == 0) continue;
     uint32_t m = ((uint32_t)n + k - 1) / k;
@@ -678,14 +682,27 @@ static uint32_t block_launches(spin_lattice* h, int n, int kernel, BlockPlan* pl
   return best;
 }
 
-// n sweeps in k_block launches.  *ran = false (and nothing enqueued) where they cannot run: the caller
-// goes on with the family's own kernels.
+// n sweeps in k_block launches, or by one workgroup in one launch (k_whole) where that is estimated to
+// be faster.  *ran = false (and nothing enqueued) where neither runs: the caller goes on with the
+// family's own kernels.
 static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64_t* dE, int64_t* dM, int kernel,
                      const CallScratch* fx, bool* ran) {
   *ran = false;
-  if (!block_offered(h) || !block_lattice_ok(lat_of(h), acc)) return SPIN_OK;
+  if (!block_lattice_ok(lat_of(h), acc)) return SPIN_OK;
   BlockPlan plan;
-  const uint32_t m = block_launches(h, n, kernel, &plan);
+  double us = 0;
+  const uint32_t m = block_offered(h) ? block_launches(h, n, kernel, &plan, &us) : 0;
+  const double w_us = whole_us(lat_of(h), acc, (uint32_t)n);
+  // without a k_block plan (a single sweep in place) the resident family is slower at any size that
+  // fits one workgroup, the two launches of the others take about 8 us
+  if (w_us >= 0 && (m ? w_us <= us : kernel == SPIN_KERNEL_RESIDENT || w_us < 8.0)) {
+    hipError_t e = launch_whole(lat_of(h), (uint32_t)h->t, (uint32_t)n, acc, every > 0 && n >= every ? (uint32_t)every : 0u,
+                                dE, dM, h->stream);
+    if (e != hipSuccess) return hip_fail(e, "whole-lattice sweep launch");
+    *ran = true;
+    h->t += (uint64_t)n;
+    return SPIN_OK;
+  }
   if (m == 0) return SPIN_OK;
   const uint32_t nrec = every > 0 ? (uint32_t)(n / every) : 0;
   const uint32_t tiles = block_tiles(lat_of(h), plan);
@@ -962,6 +979,8 @@ spin_lattice* spin_create_config(const spin_config* cfg) {
   h->mem = Allocator{g_alloc, g_release, g_ctx};
   h->part = nullptr;
   h->part_slots = 0;
+  h->rec = nullptr;
+  h->rec_cap = 0;
   h->block = false;
   h->plans_made = false;
   h->buf[0] = (int8_t*)h->mem.get(spin_bytes(h));
@@ -1036,26 +1055,32 @@ int spin_sweep_record(spin_lattice* h, int n, double beta, int every, int64_t* E
   if (n < 0) return fail(SPIN_EINVAL, "n must be >= 0");
   const int nrec = n / every;
   if (nrec > 0 && (!E || !M)) return fail(SPIN_EINVAL, "NULL record arrays");
-  int64_t* d = nullptr;
-  if (nrec > 0) {
-    d = (int64_t*)h->mem.get(2 * sizeof(int64_t) * (size_t)nrec);
-    if (!d) return fail(SPIN_ENOMEM, "record buffer allocation failed");
-  }
-  int rc = run_sweeps(h, n, beta, every, d, d ? d + nrec : nullptr);
-  if (rc == SPIN_OK && nrec > 0) {
-    hipError_t e = hipMemcpyAsync(E, d, sizeof(int64_t) * nrec, hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(M, d + nrec, sizeof(int64_t) * nrec, hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) rc = hip_fail(e, "record copy");
-  } else if (rc == SPIN_OK) {
-    hipError_t e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) rc = hip_fail(e, "synchronize");
-  }
-  if (d) {
+  if ((size_t)nrec > h->rec_cap) {
     (void)hipStreamSynchronize(h->stream);
-    h->mem.put(d);
+    h->mem.put(h->rec);
+    h->rec_cap = 0;
+    h->rec = (int64_t*)h->mem.get(2 * sizeof(int64_t) * (size_t)nrec);
+    if (!h->rec) return fail(SPIN_ENOMEM, "record buffer allocation failed");
+    h->rec_cap = (size_t)nrec;
   }
-  return rc;
+  if (int rc = run_sweeps(h, n, beta, every, h->rec, h->rec + nrec)) return rc;
+  hipError_t e = hipSuccess;
+  if (nrec > 0) {
+    // both arrays in one copy
+    std::vector<int64_t> both((size_t)nrec * 2);
+    e = hipMemcpyAsync(both.data(), h->rec, 2 * sizeof(int64_t) * (size_t)nrec, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(h->stream);  // the copy may not outlive its target
+      return hip_fail(e, "record copy");
+    }
+    std::memcpy(E, both.data(), sizeof(int64_t) * (size_t)nrec);
+    std::memcpy(M, both.data() + nrec, sizeof(int64_t) * (size_t)nrec);
+  } else {
+    e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return hip_fail(e, "synchronize");
+  }
+  return SPIN_OK;
 }
 
 int spin_measure(spin_lattice* h, int64_t* E, int64_t* M) {

@@ -1,4 +1,4 @@
-"""Several sweeps per launch (k_block): AUTO handles whose calls of several sweeps run tiles with
+"""Several sweeps per launch (k_block; k_whole for the smallest lattices): AUTO handles whose calls of several sweeps run tiles with
 halos in LDS, against the oracle bit for bit, at the edges of the tiles (narrow last tiles, rows of
 one or a few groups, halos wider than the lattice), for rows of L % 8 != 0, and at the bounds where
 the call falls back to single sweeps (n = 1 in place, a class with T = 1 beside one with T = 0)."""
@@ -51,13 +51,13 @@ SCHED = [(9, 0.44, 1), (1, 0.3, 1), (2, 0.5, 0), (8, 0.0, 3), (5, math.inf, 1), 
 
 
 @pytest.mark.parametrize("model", [0, 1])
-@pytest.mark.parametrize("L", [32, 40, 72, 136, 264, 520, 34, 36, 38, 46, 100, 250, 510])
+@pytest.mark.parametrize("L", [8, 16, 32, 40, 64, 72, 96, 136, 264, 520, 10, 12, 14, 34, 36, 38, 46, 62, 100, 250, 510])
 def test_2d(oracle_mod, L, model):
     compare(oracle_mod, model, L, 2, SCHED + [(4, 5.45, 1)])
 
 
 @pytest.mark.parametrize("model", [0, 1])
-@pytest.mark.parametrize("L", [16, 24, 40, 72, 12, 18, 20, 22, 26, 50])
+@pytest.mark.parametrize("L", [8, 16, 24, 32, 40, 72, 10, 12, 14, 18, 20, 22, 26, 50])
 def test_3d(oracle_mod, L, model):
     compare(oracle_mod, model, L, 3, SCHED + [(4, 2.73, 1)])
 

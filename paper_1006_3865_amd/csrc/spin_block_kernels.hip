@@ -3,7 +3,7 @@
 // launch per sweep is bound by its own latency (loads, two dependent colour
 // phases, stores) and not by arithmetic or memory.  Microseconds a sweep, one
 // launch per sweep (or two) before and k_block now: 2D Ising L = 1024 5.6 ->
-// 1.55, L = 1000 14.5 -> 1.55, 3D Ising
+// 1.5, L = 1000 14.5 -> 1.5; 3D Ising
 // L = 64 7.3 -> 2.4, L = 100 30 -> 5.1, L = 256 24 -> 17.8; 3D +-J L = 128 13.5 -> 5.7.
 //
 // A workgroup owns a tile and loads it with a halo of 2k sites on every open
@@ -208,90 +208,135 @@ __device__ __forceinline__ void blk_get(const BlockArgs& a, const BlockGeo& G, c
   }
 }
 
-// Colour c of a unit with its draws.  MEAS: where own (the tile), adds twice the unsatisfied bonds
-// of the colour-c sites after the update to unsat2 and the negative sites of both colours to neg.
-template <int D, bool EA, bool NEVER, bool RAG, bool MEAS>
-__device__ __forceinline__ void blk_update(const BlockArgs& a, const BlockGeo& G, const BlockUnit& u, uint32_t c,
-                                           const uint32_t (&draw)[4], bool own, uint32_t& unsat2, uint32_t& neg) {
-  const uint32_t po = c ? 0u : a.plane, pm = c ? a.plane : 0u;  // the other colour's plane, this one's
-  const bool P = ((u.ex ^ c) & 1u) != 0;                        // active sites: odd x
-  const uint32_t ao = u.at + po, am = u.at + pm;
-  const uint32_t A = lds_load32(am);
-  const uint32_t I = lds_load32(ao);
-  // N: the row neighbours on the other side, the other plane moved by a byte
-  const uint32_t adj = P ? G.adjp : G.adjm;
-  uint32_t N = __builtin_amdgcn_perm(I, lds_load32(ao + adj), P ? 0x00070605u : 0x06050403u);
-  uint32_t wmask = 0, wsh = 0;
-  if (RAG) {
-    // the row's first (P = 0) or last (P = 1) site takes the site at the other end
-    const uint32_t o2 = row_o2(u.ex), b0 = o2, b1 = G.half - 1u + o2;
-    const uint32_t b = P ? b1 : b0;
-    wsh = 8u * (b & 3u);
-    wmask = (b & ~3u) == G.g4 ? 0xFFu << wsh : 0u;
-    const uint32_t wrap = lds_load8(ao - G.g4 + (P ? b0 : b1));
-    N = (N & ~wmask) | ((wrap << wsh) & wmask);
-  }
-  const uint32_t ym = lds_nb<RAG>(ao + u.ym, row_shift<0>(u.ex)), yp = lds_nb<RAG>(ao + u.yp, row_shift<1>(u.ex));
-  uint32_t zm = 0, zp = 0;
-  if (D == 3) {
-    zm = lds_nb<RAG>(ao + u.zm, row_shift<2>(u.ex));
-    zp = lds_nb<RAG>(ao + u.zp, row_shift<3>(u.ex));
-  }
-  uint32_t nn;  // 2 n per byte
-  if (EA) {
-    // coupling bytes: bit 1 the bond to x+1, bit 2 to y+1, bit 3 to z+1.  The bond to I is the
-    // site's own when I is to its right (P = 0), else I's; the bond to N the other one
-    const uint32_t jm = a.jplane + am, jo = a.jplane + ao;
-    const uint32_t own_j = lds_load32(jm), oth = lds_load32(jo);
-    uint32_t left = __builtin_amdgcn_perm(oth, lds_load32(jo + G.adjm), 0x06050403u);  // of the sites to the left
-    if (RAG) {
-      const uint32_t wrap = lds_load8(jo - G.g4 + G.half - 1u + row_o2(u.ex));
-      left = (left & ~wmask) | ((wrap << wsh) & wmask);  // used where P = 0 only
-    }
-    const uint32_t jI = P ? oth : own_j, jN = P ? own_j : left;
-    const uint32_t jym = lds_nb<RAG>(jo + u.ym, row_shift<0>(u.ex));
-    nn = ((I ^ jI) & kNeg) + ((N ^ jN) & kNeg);
-    nn += ((yp ^ (own_j >> 1)) & kNeg) + ((ym ^ (jym >> 1)) & kNeg);
+// The colour-c update of a unit in steps, so that a caller can put the draws' rounds of arithmetic
+// between the LDS reads and their use.
+template <int D, bool EA, bool RAG>
+struct BlockStep {
+  uint32_t A, I, W, ym, yp, zm, zp;     // own dword, the other colour's, its neighbour, the neighbour rows'
+  uint32_t own_j, oth, left, jym, jzm;  // couplings
+  uint32_t wrap, jwrap;                 // RAG: the byte at the row's other end
+  uint32_t nn, v;
+  uint2 b01, b23;
+
+  // LDS reads
+  __device__ __forceinline__ void read(const BlockArgs& a, const BlockGeo& G, const BlockUnit& u, uint32_t c) {
+    const uint32_t po = c ? 0u : a.plane, pm = c ? a.plane : 0u;  // the other colour's plane, this one's
+    const bool P = ((u.ex ^ c) & 1u) != 0;                        // active sites: odd x
+    const uint32_t ao = u.at + po, am = u.at + pm;
+    I = lds_load32(ao);
+    W = lds_load32(ao + (P ? G.adjp : G.adjm));
+    ym = lds_nb<RAG>(ao + u.ym, row_shift<0>(u.ex));
+    yp = lds_nb<RAG>(ao + u.yp, row_shift<1>(u.ex));
     if (D == 3) {
-      const uint32_t jzm = lds_nb<RAG>(jo + u.zm, row_shift<2>(u.ex));
-      nn += ((zp ^ (own_j >> 2)) & kNeg) + ((zm ^ (jzm >> 2)) & kNeg);
+      zm = lds_nb<RAG>(ao + u.zm, row_shift<2>(u.ex));
+      zp = lds_nb<RAG>(ao + u.zp, row_shift<3>(u.ex));
     }
-  } else {
-    nn = I + N + ym + yp;
-    if (D == 3) nn += zm + zp;
+    if (RAG) wrap = lds_load8(ao - G.g4 + row_o2(u.ex) + (P ? 0u : G.half - 1u));
+    if (EA) {
+      const uint32_t jm = a.jplane + am, jo = a.jplane + ao;
+      own_j = lds_load32(jm);
+      oth = lds_load32(jo);
+      left = lds_load32(jo + G.adjm);
+      jym = lds_nb<RAG>(jo + u.ym, row_shift<0>(u.ex));
+      if (D == 3) jzm = lds_nb<RAG>(jo + u.zm, row_shift<2>(u.ex));
+      if (RAG) jwrap = lds_load8(jo - G.g4 + G.half - 1u + row_o2(u.ex));
+    }
+    A = lds_load32(am);
   }
-  const uint32_t v = (A << 3) + nn;
-  const uint2 b01 = lds_load64(__builtin_amdgcn_udot4(v, 0x00003C04u, G.base, false));
-  const uint2 b23 = lds_load64(__builtin_amdgcn_udot4(v, 0x3C040000u, G.base, false));
-  uint32_t r[4] = {draw[0], draw[1], draw[2], draw[3]};
-  if (NEVER) {
-    // T = 0 classes hold bound 0 and no class has T = 1 (bound 0 as well), so a draw of 0, the only
-    // one those would accept, may count as 1 everywhere
+
+  // the neighbour sums, and the reads of the bounds
+  __device__ __forceinline__ void sums(const BlockGeo& G, const BlockUnit& u, uint32_t c) {
+    const bool P = ((u.ex ^ c) & 1u) != 0;
+    // N: the row neighbours on the other side, the other plane moved by a byte
+    uint32_t N = __builtin_amdgcn_perm(I, W, P ? 0x00070605u : 0x06050403u);
+    uint32_t wmask = 0, wsh = 0;
+    if (RAG) {
+      // the row's first (P = 0) or last (P = 1) site takes the site at the other end
+      const uint32_t b = (P ? G.half - 1u : 0u) + row_o2(u.ex);
+      wsh = 8u * (b & 3u);
+      wmask = (b & ~3u) == G.g4 ? 0xFFu << wsh : 0u;
+      N = (N & ~wmask) | ((wrap << wsh) & wmask);
+    }
+    if (EA) {
+      // coupling bytes: bit 1 the bond to x+1, bit 2 to y+1, bit 3 to z+1.  The bond to I is the
+      // site's own when I is to its right (P = 0), else I's; the bond to N the other one
+      uint32_t lj = __builtin_amdgcn_perm(oth, left, 0x06050403u);  // of the sites to the left
+      if (RAG) lj = (lj & ~wmask) | ((jwrap << wsh) & wmask);       // used where P = 0 only
+      const uint32_t jI = P ? oth : own_j, jN = P ? own_j : lj;
+      nn = ((I ^ jI) & kNeg) + ((N ^ jN) & kNeg);
+      nn += ((yp ^ (own_j >> 1)) & kNeg) + ((ym ^ (jym >> 1)) & kNeg);
+      if (D == 3) nn += ((zp ^ (own_j >> 2)) & kNeg) + ((zm ^ (jzm >> 2)) & kNeg);
+    } else {
+      nn = I + N + ym + yp;
+      if (D == 3) nn += zm + zp;
+    }
+    v = (A << 3) + nn;
+    b01 = lds_load64(__builtin_amdgcn_udot4(v, 0x00003C04u, G.base, false));
+    b23 = lds_load64(__builtin_amdgcn_udot4(v, 0x3C040000u, G.base, false));
+  }
+
+  // the decisions with draws r; MEAS: where own (the tile), adds twice the unsatisfied bonds of the
+  // colour-c sites after the update to unsat2 and the negative sites of both colours to neg
+  template <bool NEVER, bool MEAS>
+  __device__ __forceinline__ void decide(const BlockArgs& a, const BlockGeo& G, const BlockUnit& u, uint32_t c,
+                                         uint32_t (&r)[4], bool own, uint32_t& unsat2, uint32_t& neg) {
+    if (NEVER) {
+      // T = 0 classes hold bound 0 and no class has T = 1 (bound 0 as well), so a draw of 0, the only
+      // one those would accept, may count as 1 everywhere
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = __builtin_elementwise_max(r[i], 1u);
-  }
-  uint32_t F = xor3(r[0] <= b01.x ? 0x02u : 0u, r[1] <= b01.y ? 0x0200u : 0u, r[2] <= b23.x ? 0x020000u : 0u) ^
-               (r[3] <= b23.y ? 0x02000000u : 0u);
-  uint32_t vm = 0xFFFFFFFFu;
-  if (RAG) {
-    vm = rag_mask(G, row_o2(u.ex));
-    F &= vm;
-  }
-  const uint32_t An = A ^ F;
-  lds_store32(am, An);
-  if (MEAS) {
-    if (own) {
-      constexpr uint32_t kZ = 0x01010101u * (4u * (uint32_t)D);   // 2 * (2D) per byte
-      const uint32_t h = An >> 1, full = (h << 8) - h;            // 0xFF where the site is negative
-      const uint32_t u2 = (nn ^ ((nn ^ (kZ - nn)) & full)) & vm;  // negative: 2 (2D - n), else 2 n
-      unsat2 = __builtin_amdgcn_sad_u8(u2, 0u, unsat2);
-      neg += __popc(An & vm) + __popc(I & vm);
+      for (int i = 0; i < 4; ++i) r[i] = __builtin_elementwise_max(r[i], 1u);
+    }
+    uint32_t F = xor3(r[0] <= b01.x ? 0x02u : 0u, r[1] <= b01.y ? 0x0200u : 0u, r[2] <= b23.x ? 0x020000u : 0u) ^
+                 (r[3] <= b23.y ? 0x02000000u : 0u);
+    uint32_t vm = 0xFFFFFFFFu;
+    if (RAG) {
+      vm = rag_mask(G, row_o2(u.ex));
+      F &= vm;
+    }
+    const uint32_t An = A ^ F;
+    lds_store32(u.at + (c ? a.plane : 0u), An);
+    if (MEAS) {
+      if (own) {
+        constexpr uint32_t kZ = 0x01010101u * (4u * (uint32_t)D);   // 2 * (2D) per byte
+        const uint32_t h = An >> 1, full = (h << 8) - h;            // 0xFF where the site is negative
+        const uint32_t u2 = (nn ^ ((nn ^ (kZ - nn)) & full)) & vm;  // negative: 2 (2D - n), else 2 n
+        unsat2 = __builtin_amdgcn_sad_u8(u2, 0u, unsat2);
+        neg += __popc(An & vm) + __popc(I & vm);
+      }
     }
   }
+};
+
+// One unit.  ORDERED: its LDS reads, half the rounds of its draws, the sums and bound reads, the other
+// rounds, the decisions, held in this order, so that the rounds cover both latencies (left to itself
+// the compiler puts the reads late and waits for each table entry by itself; 2D L = 64 whole 0.75 ->
+// 0.61 us a sweep, L = 1024 in launches of 8 sweeps 1.59 -> 1.48).  Not in the loop over many units,
+// where other wavefronts cover them (3D L = 100 2 % slower).
+template <int D, bool EA, bool NEVER, bool RAG, bool MEAS, bool ORDERED>
+__device__ __forceinline__ void blk_update(const BlockArgs& a, const BlockGeo& G, const BlockUnit& u, uint32_t c,
+                                           const PhiloxUniform& U, bool own, uint32_t& unsat2, uint32_t& neg) {
+  BlockStep<D, EA, RAG> s;
+  uint32_t r[4];
+  if (ORDERED) {
+    s.read(a, G, u, c);
+    __builtin_amdgcn_sched_barrier(0);
+    philox_head((uint64_t)kPhiloxM0 * u.ctr, U, a.keys, r);
+    philox_rounds<3, 6>(r, a.keys);
+    __builtin_amdgcn_sched_barrier(0);
+    s.sums(G, u, c);
+    __builtin_amdgcn_sched_barrier(0);
+    philox_rounds<6, 10>(r, a.keys);
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    philox_lane(u.ctr, U, a.keys, r);
+    s.read(a, G, u, c);
+    s.sums(G, u, c);
+  }
+  s.template decide<NEVER, MEAS>(a, G, u, c, r, own, unsat2, neg);
 }
 
 // One colour phase over the first `count` listed rows.  M > 0: a thread has at most M units, whose
-// first rows it keeps in registers (they are the same in every phase); M == 0: any number.
+// rows it keeps in registers (they are the same in every phase); M == 0: any number.
 template <int D, bool EA, bool NEVER, bool RAG, bool MEAS, int M>
 __device__ __forceinline__ void blk_phase(const BlockArgs& a, const BlockGeo& G, const BlockUnit (&un)[M ? M : 1],
                                           uint32_t c, uint32_t count, const PhiloxUniform& U, uint32_t own_rows,
@@ -300,19 +345,12 @@ __device__ __forceinline__ void blk_phase(const BlockArgs& a, const BlockGeo& G,
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       const uint32_t idx = G.rl + m * G.rpt;
-      if (idx < count) {
-        uint32_t rnd[4];
-        philox_lane(un[m].ctr, U, a.keys, rnd);
-        blk_update<D, EA, NEVER, RAG, MEAS>(a, G, un[m], c, rnd, idx < own_rows && own_g, unsat2, neg);
-      }
+      if (idx < count)
+        blk_update<D, EA, NEVER, RAG, MEAS, true>(a, G, un[m], c, U, idx < own_rows && own_g, unsat2, neg);
     }
   } else {
-    for (uint32_t idx = G.rl; idx < count; idx += G.rpt) {
-      const BlockUnit u = blk_unit(G, idx);
-      uint32_t rnd[4];
-      philox_lane(u.ctr, U, a.keys, rnd);
-      blk_update<D, EA, NEVER, RAG, MEAS>(a, G, u, c, rnd, idx < own_rows && own_g, unsat2, neg);
-    }
+    for (uint32_t idx = G.rl; idx < count; idx += G.rpt)
+      blk_update<D, EA, NEVER, RAG, MEAS, false>(a, G, blk_unit(G, idx), c, U, idx < own_rows && own_g, unsat2, neg);
   }
 }
 
@@ -459,8 +497,8 @@ __global__ __launch_bounds__(1024) void k_block(const int8_t* __restrict__ src, 
 // at most M units whose places it keeps in registers, (E, M) written after
 // every every-th sweep.  A sweep is two phases of LDS and Philox latency and a
 // barrier each, with nothing else a launch would add, so it is the
-// fastest form while one compute unit's issue is not the bound: 2D L = 64 0.55 us
-// a sweep (k_block 0.96 in launches of 8 sweeps, the nibble kernel of the pool 2.2).
+// fastest form while one compute unit's issue is not the bound: 2D L = 64 0.61 us
+// a sweep (k_block 0.87 in launches of 8 sweeps, the pool's nibble kernel 1.09).
 template <int D, bool EA, bool NEVER, bool RAG, int M>
 __global__ __launch_bounds__(1024) void k_whole(int8_t* __restrict__ spins, const int8_t* __restrict__ J, BlockArgs a,
                                                 uint32_t n, uint32_t every, int64_t* __restrict__ E,
@@ -493,8 +531,7 @@ __global__ __launch_bounds__(1024) void k_whole(int8_t* __restrict__ spins, cons
     const __amdgpu_buffer_rsrc_t rj = __builtin_amdgcn_make_buffer_rsrc((void*)J, 0, EA ? (int)jbytes : 0, 0x00020000);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const uint32_t row = G.rl + m * G.rpt;
-      if (row >= rows) continue;
+      const uint32_t mine = G.rl + m * G.rpt, row = mine < rows ? mine : 0u;  // no row: any valid place
       const uint32_t z = D == 3 ? row / L : 0u, y = row - z * L;
       const uint2 e = blk_row<D, RAG>(a.first + row * RS, y, z, L, a.GPR);
       un[m] = BlockUnit{base + row_at(e.x) + G.g4,
@@ -504,12 +541,14 @@ __global__ __launch_bounds__(1024) void k_whole(int8_t* __restrict__ spins, cons
                         y + 1u < L ? G.sy : 0u - G.sy * (L - 1u),
                         z ? 0u - G.sz : G.sz * (L - 1u),
                         z + 1u < L ? G.sz : 0u - G.sz * (L - 1u)};
-      blk_u2 w[EA ? D + 1 : 1];
-      w[0] = __builtin_amdgcn_raw_buffer_load_b64(rs, 8u * un[m].ctr, 0, 0);
+      if (mine < rows) {
+        blk_u2 w[EA ? D + 1 : 1];
+        w[0] = __builtin_amdgcn_raw_buffer_load_b64(rs, 8u * un[m].ctr, 0, 0);
 #pragma unroll
-      for (int dir = 0; dir < (EA ? D : 0); ++dir)
-        w[EA ? dir + 1 : 0] = __builtin_amdgcn_raw_buffer_load_b64(rj, 8u * un[m].ctr, dir * a.jstride, 0);
-      blk_put<D, EA, RAG>(a, G, un[m].at, e.x, w);
+        for (int dir = 0; dir < (EA ? D : 0); ++dir)
+          w[EA ? dir + 1 : 0] = __builtin_amdgcn_raw_buffer_load_b64(rj, 8u * un[m].ctr, dir * a.jstride, 0);
+        blk_put<D, EA, RAG>(a, G, un[m].at, e.x, w);
+      }
     }
   }
   __syncthreads();
@@ -524,12 +563,14 @@ __global__ __launch_bounds__(1024) void k_whole(int8_t* __restrict__ spins, cons
     if (every && --due == 0) {
       due = every;
       blk_phase<D, EA, NEVER, RAG, true, M>(a, G, un, 1u, rows, U1, rows, true, unsat2, neg);
-      const int64_t su = wave_count_dpp(unsat2), sn = wave_count_dpp(neg);
+      // both counts in one reduction: of a wavefront's M <= 4 units a lane, 2 u sums to at most
+      // 64 * 4 * 48 and the negative sites to 64 * 4 * 8, below 2^16 each
+      const uint32_t both = (uint32_t)wave_count_dpp(unsat2 << 16 | neg);
       // two slots in turn: one is added to while thread 0 takes and clears the other
       uint32_t* slot = reinterpret_cast<uint32_t*>(lds + kBlkRec) + 2u * (rec & 1u);
       if ((tid & 63u) == 0) {
-        atomicAdd(slot, (uint32_t)su);
-        atomicAdd(slot + 1, (uint32_t)sn);
+        atomicAdd(slot, both >> 16);
+        atomicAdd(slot + 1, both & 0xFFFFu);
       }
       __syncthreads();
       if (tid == 0) {
@@ -624,21 +665,21 @@ static double block_us(const Lat& lat, const BlockPlan& p) {
   const uint64_t tiles = block_tiles(lat, p);
   const uint64_t by_lds = 160u * 1024u / block_lds_bytes(lat, p), by_threads = 2048u / p.threads;
   const uint64_t per_cu = std::min<uint64_t>(8, std::min(by_lds, by_threads)), slots = 256u * per_cu;
-  const double issue = (lat.d == 2 ? 0.1117 : 0.1339) * (ea ? 1.14 : 1.0) * (rag ? 1.67 : 1.0);
+  const double issue = (lat.d == 2 ? 0.1071 : 0.1336) * (ea ? 1.13 : 1.0) * (rag ? 1.66 : 1.0);
   auto rows_at = [&](uint32_t m) { return (a.TY + 2u * m) * (lat.d == 3 ? TZ + 2u * m : 1u); };
   const uint32_t most = (rows_at(H - 1u) + rpt - 1u) / rpt;
-  const double pass = most <= (rag ? 2u : 4u) ? 0.179 : 0.323;  // units in registers, or listed per pass
+  const double pass = most <= (rag ? 2u : 4u) ? 0.114 : 0.254;  // units in registers, or listed per pass
   auto round_us = [&](uint64_t n) {
     const double q = (double)((n + 255u) / 256u);  // workgroups a compute unit holds
-    double us = 0.000235 * rows_at(H) * GW * q * (ea ? 1.0 + lat.d : 1.0);
+    double us = 0.000238 * rows_at(H) * GW * q * (ea ? 1.0 + lat.d : 1.0);
     for (uint32_t m = 0; m < H; ++m) {
       const uint32_t rows = rows_at(m), passes = (rows + rpt - 1u) / rpt;
       const uint32_t wu = (passes - 1u) * waves + ((rows - (passes - 1u) * rpt) * GW + 63u) / 64u;
-      us += 0.121 + std::max(issue * wu * q / 4.0, pass * passes);
+      us += 0.120 + std::max(issue * wu * q / 4.0, pass * passes);
     }
     return us;
   };
-  double us = 3.57 + (double)(tiles / slots) * round_us(slots);
+  double us = 3.47 + (double)(tiles / slots) * round_us(slots);
   if (tiles % slots) us += round_us(tiles % slots);
   return us;
 }
@@ -745,9 +786,9 @@ double whole_us(const Lat& lat, const Accept& acc, uint32_t n) {
   const BlockArgs a = whole_args(lat, &lds);
   if (lds > 160u * 1024u) return -1.0;
   const bool rag = is_rag(lat);
-  const double issue = (lat.d == 2 ? 0.1117 : 0.1339) * (lat.J ? 1.14 : 1.0) * (rag ? 1.67 : 1.0);
+  const double issue = (lat.d == 2 ? 0.1071 : 0.1336) * (lat.J ? 1.13 : 1.0) * (rag ? 1.66 : 1.0);
   const double waves = (double)(lat.N / lat.L) * a.TX / 64.0;
-  return 3.57 + n * 2.0 * (0.121 + std::max(issue * waves / 4.0, 0.179 * m));
+  return 3.47 + n * 2.0 * (0.120 + std::max(issue * waves / 4.0, 0.114 * m));
 }
 
 template <int D, bool EA, bool NEVER, bool RAG, int M>

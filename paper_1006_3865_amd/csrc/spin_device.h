@@ -73,10 +73,25 @@ __device__ __forceinline__ void keys_resident(const RoundKeys& K) {
   for (int i = 0; i < 10; ++i) asm volatile("" ::"s"(K.k0[i]), "s"(K.k1[i]));
 }
 
-// Philox4x32-10 of counter (c0, c1, c2, c3) given U = philox_uniform(c1, c2, c3)
-// and the first product p0 = M0 * c0.
-__device__ __forceinline__ void philox_from_p0(uint64_t p0, const PhiloxUniform& U, const RoundKeys& K,
-                                               uint32_t r[4]) {
+// Rounds FIRST .. LAST-1 (counted from 0) on the state d.
+template <int FIRST, int LAST>
+__device__ __forceinline__ void philox_rounds(uint32_t d[4], const RoundKeys& K) {
+#pragma unroll
+  for (int i = FIRST; i < LAST; ++i) {
+    const uint64_t q0 = (uint64_t)kPhiloxM0 * d[0];
+    const uint64_t q1 = (uint64_t)kPhiloxM1 * d[2];
+    const uint32_t n0 = xor3((uint32_t)(q1 >> 32), d[1], K.k0[i]);
+    const uint32_t n2 = xor3((uint32_t)(q0 >> 32), d[3], K.k1[i]);
+    d[1] = (uint32_t)q1;
+    d[3] = (uint32_t)q0;
+    d[0] = n0;
+    d[2] = n2;
+  }
+}
+
+// The state after round 3 of Philox4x32-10 of counter (c0, c1, c2, c3) given U =
+// philox_uniform(c1, c2, c3) and the first product p0 = M0 * c0.
+__device__ __forceinline__ void philox_head(uint64_t p0, const PhiloxUniform& U, const RoundKeys& K, uint32_t d[4]) {
   // round 1
   const uint32_t a2 = (uint32_t)(p0 >> 32) ^ U.x1;
   const uint32_t a3 = (uint32_t)p0;
@@ -88,23 +103,18 @@ __device__ __forceinline__ void philox_from_p0(uint64_t p0, const PhiloxUniform&
   // round 3 (c3 after round 2 is uniform: folded with its key into x4)
   const uint64_t p2 = (uint64_t)kPhiloxM0 * b0;
   const uint64_t p3 = (uint64_t)kPhiloxM1 * b2;
-  uint32_t d0 = xor3((uint32_t)(p3 >> 32), b1, K.k0[2]);
-  uint32_t d1 = (uint32_t)p3;
-  uint32_t d2 = (uint32_t)(p2 >> 32) ^ U.x4;
-  uint32_t d3 = (uint32_t)p2;
-  // rounds 4..10
-#pragma unroll
-  for (int i = 3; i < 10; ++i) {
-    const uint64_t q0 = (uint64_t)kPhiloxM0 * d0;
-    const uint64_t q1 = (uint64_t)kPhiloxM1 * d2;
-    const uint32_t n0 = xor3((uint32_t)(q1 >> 32), d1, K.k0[i]);
-    const uint32_t n2 = xor3((uint32_t)(q0 >> 32), d3, K.k1[i]);
-    d1 = (uint32_t)q1;
-    d3 = (uint32_t)q0;
-    d0 = n0;
-    d2 = n2;
-  }
-  r[0] = d0; r[1] = d1; r[2] = d2; r[3] = d3;
+  d[0] = xor3((uint32_t)(p3 >> 32), b1, K.k0[2]);
+  d[1] = (uint32_t)p3;
+  d[2] = (uint32_t)(p2 >> 32) ^ U.x4;
+  d[3] = (uint32_t)p2;
+}
+
+// Philox4x32-10 of counter (c0, c1, c2, c3) given U = philox_uniform(c1, c2, c3)
+// and the first product p0 = M0 * c0.
+__device__ __forceinline__ void philox_from_p0(uint64_t p0, const PhiloxUniform& U, const RoundKeys& K,
+                                               uint32_t r[4]) {
+  philox_head(p0, U, K, r);
+  philox_rounds<3, 10>(r, K);
 }
 
 // Philox4x32-10 of counter (c0, c1, c2, c3) given U = philox_uniform(c1, c2, c3).

@@ -183,11 +183,14 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
       }
     }
     // 3D L = 128, 256, 512: the register-column kernel with one workgroup per compute unit: slabs of
-    // 4 rows at L = 512 and 8 below, strips of L^2 / (rows * CUs) planes (measured against the
-    // plane-streaming kernel: L = 512 8430 vs 5370, 256 6610 vs 4550, 128 3050 vs 2020 attempts/ns)
+    // 8 rows at L = 256 and 4 at 128 and 512, 512 / L strips side by side in a wavefront, of
+    // L^3 / (512 * rows * CUs) planes.  us a sweep with the best shapes: L = 256 8 rows x 16 planes 64.8
+    // (4 x 32 70.9, 8 x 32 101), L = 128 4 x 4 14.7 (8 x 2 15.4); with one strip a wavefront, the
+    // further lanes repeating the row, 79.4 and 22.0.  The plane-streaming kernel: L = 512 5370 against
+    // 8500 attempts/ns here, 256 4550 against 8280, 128 2020 against 4570.
     {
-      const uint32_t ty = L == 512 ? 4u : 8u;
-      uint32_t H = std::max(2u, (uint32_t)L * (uint32_t)L / (ty * (uint32_t)cus));
+      const uint32_t ty = L == 256 ? 8u : 4u;
+      uint32_t H = (uint32_t)std::max<uint64_t>(2, h->N / ((uint64_t)512 * ty * (uint64_t)cus));
       while (H > 2 && ((uint32_t)L % H != 0 || H % 2 != 0)) --H;
       if (msc_col_supported((uint32_t)L, 3, ty, H)) {
         h->col = true;

@@ -90,12 +90,19 @@ __device__ __forceinline__ void load8(const uint32_t* p, uint32_t (&v)[8]) {
   v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// Mask of the systems whose unsatisfied count u (bit-sliced u2 u1 u0) is at least us.
-__device__ __forceinline__ uint32_t at_least(uint32_t u0, uint32_t u1, uint32_t u2, uint32_t us) {
-  uint32_t m = 0xFFFFFFFFu;                         // us == 0
-  m = us >= 1 ? (u0 | u1 | u2) : m;
-  m = us >= 2 ? (u1 | u2) : m;
-  m = us >= 3 ? (u2 | (u1 & u0)) : m;
+// Flips of a site's 32 systems: those whose unsatisfied count u (bit-sliced u2
+// u1 u0) is at least u*(r).  The thresholds grow with u, so r reaches them in
+// order and each one reached replaces the mask by the next narrower one: a
+// compare and a select each (counting u* first and comparing it cost three more
+// operations a threshold).  A threshold of 2^32 is reached by no r (its high word
+// is the same for the whole launch, so that test is a scalar one).
+template <int D>
+__device__ __forceinline__ uint32_t msc_flips(uint32_t u0, uint32_t u1, uint32_t u2, uint32_t r,
+                                              const uint64_t (&thr)[3]) {
+  uint32_t m = 0xFFFFFFFFu;
+  m = (r >= (uint32_t)thr[0]) & ((uint32_t)(thr[0] >> 32) == 0u) ? (u0 | u1 | u2) : m;
+  m = (r >= (uint32_t)thr[1]) & ((uint32_t)(thr[1] >> 32) == 0u) ? (u1 | u2) : m;
+  if (D == 3) m = (r >= (uint32_t)thr[2]) & ((uint32_t)(thr[2] >> 32) == 0u) ? (u2 | (u1 & u0)) : m;
   return m;
 }
 
@@ -133,11 +140,7 @@ __device__ __forceinline__ void msc_update8(uint32_t (&c)[8], uint32_t lw, uint3
       u1 = c1 ^ t;
       u2 = c1 & t;
     }
-    // u*(r): thresholds of u = 0 .. d-1 at or below r
-    const uint64_t ri = r[i];
-    uint32_t us = (ri >= a.thr[0] ? 1u : 0u) + (ri >= a.thr[1] ? 1u : 0u);
-    if (D == 3) us += ri >= a.thr[2] ? 1u : 0u;
-    c[j] = s ^ at_least(u0, u1, u2, us);
+    c[j] = s ^ msc_flips<D>(u0, u1, u2, r[i], a.thr);
   }
 }
 
@@ -502,16 +505,27 @@ hipError_t launch_msc_stream(const uint32_t* src, uint32_t* dst, const uint32_t*
 }
 
 // ------------------------------------------------------------ register columns
-// 3D, L = 512: one whole sweep per launch with each row's z column in
-// registers, and every coupling word read from HBM once per sweep (the plane
+// 3D, L = 512, 256 or 128: one whole sweep per launch with each row's z column
+// in registers, and every coupling word read from HBM once per sweep (the plane
 // streaming kernel above reads the couplings of a site once per colour).
+//
+// Bound by memory at 20 B a site (3 coupling words, the site's word read and
+// written): 500 us a sweep at L = 512 (5.4 TB/s) and 65 at L = 256 (5.2 TB/s, as
+// a large copy reaches).  A row of L = 256 or 128 fills half or a quarter of a
+// wavefront's lanes; the others take the same row of other strips, 79 -> 69 us
+// at L = 256 and 22 -> 14.7 at L = 128 against repeating the row in them.  Sweeps
+// march up and down in turn, so that a sweep begins where the last one ended,
+// in the planes the memory-side cache still holds: 69 -> 65 us at L = 256 (320
+// MB a sweep against a 256 MB cache), L = 512 and 128 as before.
 //
 // A workgroup owns the TY rows [y0, y0+TY) of the planes [z0, z0+H) and has
 // TY + 2 waves; wave w keeps slab row r = w + 1 (y = y0 - 2 + r) for the
 // whole launch: rows 2..TY+1 are owned, 1 and TY+2 a ring whose colour 0 is
 // recomputed here (colour 1 of the owned edge rows needs it), and 0 and TY+3
 // a halo that the ring's colour 0 reads.  Lane l holds the group of sites
-// x = 8l .. 8l+7 of its row (a 512-site row is one wavefront).
+// x = 8l .. 8l+7 of its row (a 512-site row is one wavefront; struct Planes
+// has the smaller ones).  Planes are counted along the march here; with REV it
+// goes down from z0 + H - 1 and "above" is below.
 // Step i = 0..H+1 with a = z0-1+i, b = a-1.  Both colour units of a step
 // have active sites of x parity P = (y + a) & 1 (colour 0 on plane a,
 // colour 1 on plane b):
@@ -552,26 +566,64 @@ __device__ __forceinline__ v4u half(const G8& g) {
   return v4u{g.lo[P], g.lo[2 + P], g.hi[P], g.hi[2 + P]};
 }
 
-__device__ __forceinline__ G8 ld_group(__amdgpu_buffer_rsrc_t r, uint32_t row, uint32_t lane) {
+// Where a plane's rows lie for the lanes.  A row has GPR = L/8 groups: with
+// GPR < 64 the wavefront's 64/GPR parts each hold the row of another plane, the
+// same row y of planes zc = L/C apart (C parts; with C < 64/GPR the further
+// parts repeat the first ones and store what those store).  The scalar part of
+// an address takes the plane modulo zc, the lanes' part the rest, modulo C.
+template <uint32_t L>
+struct Planes {
+  static constexpr uint32_t GPR = L / 8;
+  static constexpr bool kParts = GPR < 64;
+  uint32_t zc, tz;      // planes of a part, log2 of it
+  uint32_t unit, mask;  // groups of a part's planes, (C - 1) times that
+  uint32_t part, lane;  // this lane's part times unit; its group of the row
+  __device__ __forceinline__ uint32_t row(uint32_t z, uint32_t y) const {  // first group of the row, scalar part
+    return ((kParts ? (z & (zc - 1u)) : z) * L + y) * GPR;
+  }
+  __device__ __forceinline__ uint32_t rest(uint32_t z) const {  // groups to add to it in this lane
+    return kParts ? ((part + (z >> tz) * unit) & mask) : 0u;
+  }
+};
+
+template <uint32_t L>
+__device__ __forceinline__ G8 ld_group(__amdgpu_buffer_rsrc_t r, const Planes<L>& p, uint32_t z, uint32_t y) {
+  const uint32_t v = 32u * (p.rest(z) | p.lane), row = 32u * p.row(z, y);
   G8 g;
-  g.lo = __builtin_amdgcn_raw_buffer_load_b128(r, 32u * lane, row, 0);
-  g.hi = __builtin_amdgcn_raw_buffer_load_b128(r, 32u * lane + 16u, row, 0);
+  g.lo = __builtin_amdgcn_raw_buffer_load_b128(r, v, row, 0);
+  g.hi = __builtin_amdgcn_raw_buffer_load_b128(r, v + 16u, row, 0);
   return g;
 }
 
 template <uint32_t L>
-__device__ __forceinline__ H8 ld_split(__amdgpu_buffer_rsrc_t r, uint32_t row, uint32_t lane) {
+__device__ __forceinline__ H8 ld_split(__amdgpu_buffer_rsrc_t r, const Planes<L>& p, uint32_t z, uint32_t y) {
+  const uint32_t v = 32u * p.rest(z) | 16u * p.lane, row = 32u * p.row(z, y);
   H8 g;
-  g.h[0] = __builtin_amdgcn_raw_buffer_load_b128(r, 16u * lane, row, 0);
-  g.h[1] = __builtin_amdgcn_raw_buffer_load_b128(r, 2u * L + 16u * lane, row, 0);  // the odd-x half
+  g.h[0] = __builtin_amdgcn_raw_buffer_load_b128(r, v, row, 0);
+  g.h[1] = __builtin_amdgcn_raw_buffer_load_b128(r, v + 2u * L, row, 0);  // the odd-x half
   return g;
 }
 
-__device__ __forceinline__ uint32_t ror1(uint32_t v) {  // lane l gets lane l-1's value (periodic)
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x13C, 0xF, 0xF, false);
+// Lane l gets the value of the lane of the group left (ror1) or right (rol1) of its own in the
+// periodic row of GPR lanes: a rotate of the wavefront, with two rows in it the two ends exchanged, with
+// four a rotate of each 16 lanes.
+template <uint32_t GPR>
+__device__ __forceinline__ uint32_t ror1(uint32_t v) {
+  if (GPR == 16) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, false);
+  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x13C, 0xF, 0xF, false);
+  if (GPR == 64) return t;
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 31), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+  const uint32_t l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  return l == 0u ? a : (l == 32u ? b : t);
 }
-__device__ __forceinline__ uint32_t rol1(uint32_t v) {  // lane l gets lane l+1's value (periodic)
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x134, 0xF, 0xF, false);
+template <uint32_t GPR>
+__device__ __forceinline__ uint32_t rol1(uint32_t v) {
+  if (GPR == 16) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x12F, 0xF, 0xF, false);
+  const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x134, 0xF, 0xF, false);
+  if (GPR == 64) return t;
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
+  const uint32_t l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  return l == 31u ? a : (l == 63u ? b : t);
 }
 
 // One colour unit on the active sites j = 2i + P of group g: nb is the x
@@ -599,9 +651,7 @@ __device__ __forceinline__ void unit(G8& g, uint32_t nb, const G8& jx, uint32_t 
     const uint32_t s2 = xor3(b3, b4, b5), c2 = maj3(b3, b4, b5);
     const uint32_t u0 = s1 ^ s2, t = s1 & s2;
     const uint32_t u1 = xor3(c1, c2, t), u2 = maj3(c1, c2, t);
-    const uint64_t ri = r[i];
-    const uint32_t us = (ri >= thr[0] ? 1u : 0u) + (ri >= thr[1] ? 1u : 0u) + (ri >= thr[2] ? 1u : 0u);
-    w[j] = s ^ at_least(u0, u1, u2, us);
+    w[j] = s ^ msc_flips<3>(u0, u1, u2, r[i], thr);
   }
   g.lo = v4u{w[0], w[1], w[2], w[3]};
   g.hi = v4u{w[4], w[5], w[6], w[7]};
@@ -617,13 +667,20 @@ struct Role {
   static constexpr bool OWN = ROLE != TOP && ROLE != BOT;
 };
 
+template <uint32_t L>
 struct Ctx {
   __amdgpu_buffer_rsrc_t src, dst, jx, jy, jz;
+  Planes<L> pl;
   uint32_t* ls;  // spin slices: 3 x (TY+4) rows
   uint32_t* lj;  // y-bond slices: 3 x (TY+3) rows
   const RoundKeys* keys;
   PhiloxUniform U0, U1;
   uint64_t thr[3];
+  // m-th plane of the strip's march (m = -2 ..): upwards from z0, or with REV downwards from z0 + H - 1
+  template <bool REV>
+  __device__ __forceinline__ uint32_t plane(uint32_t m) const {
+    return (REV ? z0 + H - 1u - m : z0 + m) & (L - 1u);
+  }
   uint32_t z0, H, lane, r, y, yh;  // yh: the halo row this wave loads (TOP, JH: row 0; BOT: row TY+3)
 };
 
@@ -639,20 +696,20 @@ struct Regs {
   uint32_t sA, sB, sN;  // LDS slots of planes a, b, a+1
 };
 
-template <uint32_t L>
-__device__ __forceinline__ uint32_t row_off(uint32_t z, uint32_t y) { return (z * L + y) * L * 4u; }
+// An LDS row is a wavefront's: 64 groups, their even-x words (the 4 of lane l at 4 l), then the odd-x ones.
+constexpr uint32_t RW = 512, HW = 256;
 
-template <uint32_t L, int TY, int ROLE, uint32_t Q, bool C1>
-__device__ __forceinline__ void step(const Ctx& c, Regs& R, uint32_t i) {
+template <uint32_t L, int TY, int ROLE, bool REV, uint32_t Q, bool C1>
+__device__ __forceinline__ void step(const Ctx<L>& c, Regs& R, uint32_t i) {
   using RL = Role<ROLE>;
-  constexpr uint32_t RW = L, HW = L / 2, GPR = L / 8;  // words per LDS row and parity half, groups per row
+  constexpr uint32_t GPR = L / 8;
   constexpr uint32_t SS = (TY + 4) * RW, JS = (TY + 3) * RW;  // words per spin / y-bond slice
-  constexpr uint32_t P = (RL::RP + Q + 1u) & 1u;
+  constexpr uint32_t F = Q + 1u + (REV ? 1u : 0u);  // parity of plane a
+  constexpr uint32_t P = (RL::RP + F) & 1u;
   const uint32_t lane = c.lane, r = c.r, y = c.y;
-  const uint32_t a = (c.z0 + i + L - 1u) & (L - 1u);
-  const uint32_t b = (a + L - 1u) & (L - 1u);
+  const uint32_t a = c.template plane<REV>(i - 1u), b = c.template plane<REV>(i - 2u);
   const uint32_t ic = i <= c.H ? i : c.H;  // loads past the strip's needs reload a plane already read
-  const uint32_t zs = (c.z0 + 1u + ic) & (L - 1u), zx = (c.z0 + ic) & (L - 1u);
+  const uint32_t zs = c.template plane<REV>(ic + 1u), zx = c.template plane<REV>(ic);
   // plane a+1 into slot N (free since the last barrier: it held plane b-1)
   {
     uint32_t* sN = c.ls + R.sN * SS;
@@ -661,11 +718,11 @@ __device__ __forceinline__ void step(const Ctx& c, Regs& R, uint32_t i) {
     *reinterpret_cast<v4u*>(jN + r * RW + 4u * lane) = R.jy1.h[0];
     *reinterpret_cast<v4u*>(jN + r * RW + HW + 4u * lane) = R.jy1.h[1];
     if (ROLE == TOP) {
-      constexpr uint32_t PH = (0u + Q + 1u) & 1u;
+      constexpr uint32_t PH = F & 1u;
       *reinterpret_cast<v4u*>(sN + PH * HW + 4u * lane) = half<PH>(R.hs);
     }
     if (ROLE == BOT) {
-      constexpr uint32_t PH = ((uint32_t)TY + 3u + Q + 1u) & 1u;
+      constexpr uint32_t PH = ((uint32_t)TY + 3u + F) & 1u;
       *reinterpret_cast<v4u*>(sN + (TY + 3) * RW + PH * HW + 4u * lane) = half<PH>(R.hs);
     }
     if (ROLE == JH) {
@@ -674,26 +731,26 @@ __device__ __forceinline__ void step(const Ctx& c, Regs& R, uint32_t i) {
     }
   }
   // loads for the next step
-  R.s2 = ld_group(c.src, row_off<L>(zs, y), lane);
-  R.jy1 = ld_split<L>(c.jy, row_off<L>(zs, y), lane);
-  R.jxn = ld_group(c.jx, row_off<L>(zx, y), lane);
-  R.jzn = ld_split<L>(c.jz, row_off<L>(zx, y), lane);
-  if (ROLE == TOP || ROLE == BOT) R.hs = ld_group(c.src, row_off<L>(zs, c.yh), lane);
-  if (ROLE == JH) R.hj = ld_split<L>(c.jy, row_off<L>(zs, c.yh), lane);
+  R.s2 = ld_group(c.src, c.pl, zs, y);
+  R.jy1 = ld_split(c.jy, c.pl, zs, y);
+  R.jxn = ld_group(c.jx, c.pl, zx, y);
+  R.jzn = ld_split(c.jz, c.pl, REV ? (zx + L - 1u) & (L - 1u) : zx, y);
+  if (ROLE == TOP || ROLE == BOT) R.hs = ld_group(c.src, c.pl, zs, c.yh);
+  if (ROLE == JH) R.hj = ld_split(c.jy, c.pl, zs, c.yh);
   // colour 0 on plane a
   const uint32_t* sA = c.ls + R.sA * SS;
   const uint32_t* jA = c.lj + R.sA * JS;
   const uint32_t o = P * HW + 4u * lane;
   uint32_t rnd[4];
-  philox_lane((a * L + y) * GPR + lane, c.U0, *c.keys, rnd);
+  philox_lane(c.pl.row(a, y) + (c.pl.rest(a) | c.pl.lane), c.U0, *c.keys, rnd);
   G8 na = R.sa;
   {
     const v4u ym = *reinterpret_cast<const v4u*>(sA + (r - 1) * RW + o);
     const v4u yp = *reinterpret_cast<const v4u*>(sA + (r + 1) * RW + o);
     const v4u jy = *reinterpret_cast<const v4u*>(jA + r * RW + o);
     const v4u jym = *reinterpret_cast<const v4u*>(jA + (r - 1) * RW + o);
-    const uint32_t nb = P == 0 ? ror1(R.sa.hi.w) : rol1(R.sa.lo.x);
-    const uint32_t jl = P == 0 ? ror1(R.jxa.hi.w) : 0u;
+    const uint32_t nb = P == 0 ? ror1<GPR>(R.sa.hi.w) : rol1<GPR>(R.sa.lo.x);
+    const uint32_t jl = P == 0 ? ror1<GPR>(R.jxa.hi.w) : 0u;
     unit<P>(na, nb, R.jxa, jl, ym, yp, half<P>(R.sb), half<P>(R.s1), jym, jy, R.jzb.h[P], R.jza.h[P], rnd, c.thr);
     *reinterpret_cast<v4u*>(c.ls + R.sA * SS + r * RW + o) = half<P>(na);
   }
@@ -701,17 +758,18 @@ __device__ __forceinline__ void step(const Ctx& c, Regs& R, uint32_t i) {
   if (C1 && RL::OWN) {
     const uint32_t* sB = c.ls + R.sB * SS;
     const uint32_t* jB = c.lj + R.sB * JS;
-    philox_lane((b * L + y) * GPR + lane, c.U1, *c.keys, rnd);
+    const uint32_t gb = c.pl.rest(b) | c.pl.lane, rb = c.pl.row(b, y);
+    philox_lane(rb + gb, c.U1, *c.keys, rnd);
     const v4u ym = *reinterpret_cast<const v4u*>(sB + (r - 1) * RW + o);
     const v4u yp = *reinterpret_cast<const v4u*>(sB + (r + 1) * RW + o);
     const v4u jy = *reinterpret_cast<const v4u*>(jB + r * RW + o);
     const v4u jym = *reinterpret_cast<const v4u*>(jB + (r - 1) * RW + o);
-    const uint32_t nb = P == 0 ? ror1(R.sb.hi.w) : rol1(R.sb.lo.x);
-    const uint32_t jl = P == 0 ? ror1(R.jxb.hi.w) : 0u;
+    const uint32_t nb = P == 0 ? ror1<GPR>(R.sb.hi.w) : rol1<GPR>(R.sb.lo.x);
+    const uint32_t jl = P == 0 ? ror1<GPR>(R.jxb.hi.w) : 0u;
     G8 nbk = R.sb;
     unit<P>(nbk, nb, R.jxb, jl, ym, yp, R.sbb, half<P>(na), jym, jy, R.jzbb, R.jzb.h[P], rnd, c.thr);
-    __builtin_amdgcn_raw_buffer_store_b128(nbk.lo, c.dst, 32u * lane, row_off<L>(b, y), 0);
-    __builtin_amdgcn_raw_buffer_store_b128(nbk.hi, c.dst, 32u * lane + 16u, row_off<L>(b, y), 0);
+    __builtin_amdgcn_raw_buffer_store_b128(nbk.lo, c.dst, 32u * gb, 32u * rb, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(nbk.hi, c.dst, 32u * gb + 16u, 32u * rb, 0);
   }
   // the next step's registers (its active half is 1 - P)
   R.sbb = half<P ^ 1u>(R.sb);
@@ -730,49 +788,47 @@ __device__ __forceinline__ void step(const Ctx& c, Regs& R, uint32_t i) {
   __syncthreads();
 }
 
-template <uint32_t L, int TY, int ROLE>
-__device__ __forceinline__ void run(const Ctx& c) {
+template <uint32_t L, int TY, int ROLE, bool REV>
+__device__ __forceinline__ void run(const Ctx<L>& c) {
   using RL = Role<ROLE>;
-  constexpr uint32_t RW = L, HW = L / 2;
   constexpr uint32_t SS = (TY + 4) * RW, JS = (TY + 3) * RW;
   const uint32_t lane = c.lane, r = c.r, y = c.y;
-  const uint32_t zm2 = (c.z0 + L - 2u) & (L - 1u), zm1 = (c.z0 + L - 1u) & (L - 1u);
+  const uint32_t zm2 = c.template plane<REV>(0u - 2u), zm1 = c.template plane<REV>(0u - 1u);
+  const uint32_t zf = c.template plane<REV>(0u);
+  constexpr uint32_t F = REV ? 1u : 0u;  // half of an even row that step 0 reads of its neighbours
   Regs R;
   // prologue: plane z0-1 into slot 0 (spins half P(r, step -1) = r & 1, all y bonds); registers for step 0
-  R.sb = ld_group(c.src, row_off<L>(zm2, y), lane);
-  R.sa = ld_group(c.src, row_off<L>(zm1, y), lane);
-  R.s1 = ld_group(c.src, row_off<L>(c.z0, y), lane);
-  R.jxa = ld_group(c.jx, row_off<L>(zm1, y), lane);
-  R.jza = ld_split<L>(c.jz, row_off<L>(zm1, y), lane);
-  R.jzb = ld_split<L>(c.jz, row_off<L>(zm2, y), lane);
-  const H8 jy0 = ld_split<L>(c.jy, row_off<L>(zm1, y), lane);
-  R.jy1 = ld_split<L>(c.jy, row_off<L>(c.z0, y), lane);
+  R.sb = ld_group(c.src, c.pl, zm2, y);
+  R.sa = ld_group(c.src, c.pl, zm1, y);
+  R.s1 = ld_group(c.src, c.pl, zf, y);
+  R.jxa = ld_group(c.jx, c.pl, zm1, y);
+  R.jza = ld_split(c.jz, c.pl, REV ? zf : zm1, y);
+  R.jzb = ld_split(c.jz, c.pl, REV ? zm1 : zm2, y);
+  const H8 jy0 = ld_split(c.jy, c.pl, zm1, y);
+  R.jy1 = ld_split(c.jy, c.pl, zf, y);
   R.jxb = R.jxa;
   R.sbb = v4u{0u, 0u, 0u, 0u};
   R.jzbb = v4u{0u, 0u, 0u, 0u};
   R.hs.lo = R.hs.hi = v4u{0u, 0u, 0u, 0u};
   R.hj.h[0] = R.hj.h[1] = v4u{0u, 0u, 0u, 0u};
-  if (RL::RP)
-    *reinterpret_cast<v4u*>(c.ls + r * RW + HW + 4u * lane) = half<1>(R.sa);
-  else
-    *reinterpret_cast<v4u*>(c.ls + r * RW + 4u * lane) = half<0>(R.sa);
+  *reinterpret_cast<v4u*>(c.ls + r * RW + ((RL::RP + F) & 1u) * HW + 4u * lane) = half<(RL::RP + F) & 1u>(R.sa);
   *reinterpret_cast<v4u*>(c.lj + r * RW + 4u * lane) = jy0.h[0];
   *reinterpret_cast<v4u*>(c.lj + r * RW + HW + 4u * lane) = jy0.h[1];
-  if (ROLE == TOP) {  // row 0: half 0
-    const G8 h = ld_group(c.src, row_off<L>(zm1, c.yh), lane);
-    *reinterpret_cast<v4u*>(c.ls + 4u * lane) = half<0>(h);
-    R.hs = ld_group(c.src, row_off<L>(c.z0, c.yh), lane);
+  if (ROLE == TOP) {  // row 0: half F
+    const G8 h = ld_group(c.src, c.pl, zm1, c.yh);
+    *reinterpret_cast<v4u*>(c.ls + F * HW + 4u * lane) = half<F>(h);
+    R.hs = ld_group(c.src, c.pl, zf, c.yh);
   }
-  if (ROLE == BOT) {  // row TY+3: half (TY+3) & 1 = 1
-    const G8 h = ld_group(c.src, row_off<L>(zm1, c.yh), lane);
-    *reinterpret_cast<v4u*>(c.ls + (TY + 3) * RW + HW + 4u * lane) = half<1>(h);
-    R.hs = ld_group(c.src, row_off<L>(c.z0, c.yh), lane);
+  if (ROLE == BOT) {  // row TY+3: half (TY + 3 + F) & 1
+    const G8 h = ld_group(c.src, c.pl, zm1, c.yh);
+    *reinterpret_cast<v4u*>(c.ls + (TY + 3) * RW + (1u - F) * HW + 4u * lane) = half<1u - F>(h);
+    R.hs = ld_group(c.src, c.pl, zf, c.yh);
   }
   if (ROLE == JH) {
-    const H8 h = ld_split<L>(c.jy, row_off<L>(zm1, c.yh), lane);
+    const H8 h = ld_split(c.jy, c.pl, zm1, c.yh);
     *reinterpret_cast<v4u*>(c.lj + 4u * lane) = h.h[0];
     *reinterpret_cast<v4u*>(c.lj + HW + 4u * lane) = h.h[1];
-    R.hj = ld_split<L>(c.jy, row_off<L>(c.z0, c.yh), lane);
+    R.hj = ld_split(c.jy, c.pl, zf, c.yh);
   }
   (void)SS;
   (void)JS;
@@ -780,26 +836,26 @@ __device__ __forceinline__ void run(const Ctx& c) {
   R.sN = 1;
   R.sB = 2;
   __syncthreads();
-  step<L, TY, ROLE, 0, false>(c, R, 0u);
-  step<L, TY, ROLE, 1, false>(c, R, 1u);
+  step<L, TY, ROLE, REV, 0, false>(c, R, 0u);
+  step<L, TY, ROLE, REV, 1, false>(c, R, 1u);
   for (uint32_t i0 = 2; i0 < c.H + 2u; i0 += 2) {
-    step<L, TY, ROLE, 0, true>(c, R, i0);
-    step<L, TY, ROLE, 1, true>(c, R, i0 + 1u);
+    step<L, TY, ROLE, REV, 0, true>(c, R, i0);
+    step<L, TY, ROLE, REV, 1, true>(c, R, i0 + 1u);
   }
 }
 
 }  // namespace col
 
-template <uint32_t L, int TY>
+template <uint32_t L, int TY, bool REV>
 __global__ __launch_bounds__(64 * (TY + 2)) void k_msc_col(const uint32_t* __restrict__ src,
                                                            uint32_t* __restrict__ dst,
                                                            const uint32_t* __restrict__ J, MscArgs a,
-                                                           uint32_t H) {
+                                                           uint32_t H, uint32_t parts) {
   using namespace col;
   extern __shared__ __align__(16) uint32_t lds[];
   constexpr uint32_t Nw = L * L * L;
-  constexpr uint32_t RW = L, GPR = L / 8;
-  Ctx c;
+  constexpr uint32_t GPR = L / 8;
+  Ctx<L> c;
   c.src = __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, (int)(Nw * 4u), 0x00020000);
   c.dst = __builtin_amdgcn_make_buffer_rsrc((void*)dst, 0, (int)(Nw * 4u), 0x00020000);
   c.jx = __builtin_amdgcn_make_buffer_rsrc((void*)J, 0, (int)(Nw * 4u), 0x00020000);
@@ -818,48 +874,63 @@ __global__ __launch_bounds__(64 * (TY + 2)) void k_msc_col(const uint32_t* __res
   const uint32_t nslab = L / TY, nblk = gridDim.x, bk = blockIdx.x;
   const uint32_t tile = (nblk % 8u == 0u) ? (bk % 8u) * (nblk / 8u) + bk / 8u : bk;
   const uint32_t y0 = (tile % nslab) * TY;
-  c.z0 = (tile / nslab) * H;
+  c.z0 = (tile / nslab) * H;  // of part 0; part q's strip begins q L / parts planes on
   c.H = H;
-  // a row has GPR <= 64 groups: with GPR < 64 the wavefront holds 64 / GPR copies of the row, lane l
-  // working on group l mod GPR; the copies load, compute and store the same values, and the
-  // wavefront rotates give every lane its periodic neighbour within the row
-  c.lane = threadIdx.x & (GPR - 1u);
+  c.lane = threadIdx.x & 63u;
+  c.pl.zc = L / parts;
+  c.pl.tz = 31u - (uint32_t)__builtin_clz(c.pl.zc);
+  c.pl.unit = c.pl.zc * L * GPR;
+  c.pl.mask = (parts - 1u) * c.pl.unit;
+  c.pl.lane = c.lane & (GPR - 1u);
+  c.pl.part = ((c.lane / GPR) & (parts - 1u)) * c.pl.unit;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   c.r = wave + 1u;
   c.y = (y0 + L - 2u + c.r) & (L - 1u);
   c.yh = (wave == (uint32_t)TY + 1u) ? (y0 + TY + 1u) & (L - 1u) : (y0 + L - 2u) & (L - 1u);
   if (wave == 0)
-    run<L, TY, TOP>(c);
+    run<L, TY, TOP, REV>(c);
   else if (wave == 1)
-    run<L, TY, JH>(c);
+    run<L, TY, JH, REV>(c);
   else if (wave == (uint32_t)TY + 1u)
-    run<L, TY, BOT>(c);
+    run<L, TY, BOT, REV>(c);
   else if (c.r & 1u)
-    run<L, TY, ODD>(c);
+    run<L, TY, ODD, REV>(c);
   else
-    run<L, TY, EVEN>(c);
+    run<L, TY, EVEN, REV>(c);
 }
 
-size_t msc_col_lds(uint32_t TY, uint32_t L) { return (size_t)(3 * (TY + 4) + 3 * (TY + 3)) * L * 4; }
+constexpr size_t msc_col_lds(uint32_t TY) { return (size_t)(3 * (TY + 4) + 3 * (TY + 3)) * col::RW * 4; }
 
 bool msc_col_supported(uint32_t L, uint32_t d, uint32_t TY, uint32_t H) {
   return d == 3 && (L == 128 || L == 256 || L == 512) && (TY == 4 || TY == 8) && H >= 2 && H % 2 == 0 &&
          L % H == 0;
 }
 
-template <uint32_t L, int TY>
-static hipError_t go_msc_col(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t H,
+template <uint32_t L, int TY, bool REV>
+static hipError_t go_msc_dir(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t H,
                              hipStream_t stream) {
   static bool attr = false;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_msc_col<L, TY>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)msc_col_lds(TY, L));
+    hipError_t e = hipFuncSetAttribute((const void*)k_msc_col<L, TY, REV>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)msc_col_lds(TY));
     if (e != hipSuccess) return e;
     attr = true;
   }
-  const dim3 grid((L / TY) * (L / H));
-  hipLaunchKernelGGL((k_msc_col<L, TY>), grid, dim3(64 * (TY + 2)), msc_col_lds(TY, L), stream, src, dst, J, a, H);
+  // strips side by side in a wavefront: as many as the row leaves lanes for, each L / parts planes
+  // after the last, where that is a whole number of strips
+  uint32_t parts = 512u / L;
+  while (parts > 1 && (L / parts) % H != 0) parts >>= 1;
+  const dim3 grid((L / TY) * (L / (H * parts)));
+  hipLaunchKernelGGL((k_msc_col<L, TY, REV>), grid, dim3(64 * (TY + 2)), msc_col_lds(TY), stream, src, dst, J, a, H, parts);
   return hipGetLastError();
+}
+
+// Every other sweep marches down: it begins with the planes that the last one wrote and read last.
+template <uint32_t L, int TY>
+static hipError_t go_msc_col(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t H,
+                             hipStream_t stream) {
+  return (a.t & 1u) ? go_msc_dir<L, TY, true>(src, dst, J, a, H, stream)
+                    : go_msc_dir<L, TY, false>(src, dst, J, a, H, stream);
 }
 
 hipError_t launch_msc_col(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t d,

@@ -8,158 +8,271 @@
 // tiles of the other parity, which this launch does not write, so the
 // update is in place and race-free.
 //
-// LDS holds spins as nibble words (spin_nibble.h): a tile row of T sites is
-// T/8 words plus one pad word on each side (the whole neighbouring words,
-// so that the boundary site sits in the pad's edge nibble); rows y0-1 ..
-// y0+T (and in 3D planes z0-1 .. z0+T).  For the +-J glass the packed
-// couplings of the same region are staged the same way, once per launch,
-// and reused by all k hits.  Hit h of sweep t draws from Philox counter
-// (s>>3, t*k + h, replica, colour), as the oracle's coarse mode does.
+// A workgroup holds T^d / 8 units a tile, a unit being an 8-site group, and as many tiles
+// as make at least one wavefront (8 of edge 8, 2 of edge 16 in 2D), so that every lane has one unit
+// in either colour; with a wavefront to itself an edge-16 tile left half its lanes idle, an edge-8
+// one seven eighths.
+//
+// A launch is as long as its chain: load, then 2 k colour phases of an LDS read, the
+// neighbour sums, the decision and an LDS write, then the store; 2D L = 1024 has one or two wavefronts
+// a SIMD to hide any of it.  So the draws leave the chain: those of up to 4 hits
+// are made while the tile's loads are in flight and kept as thresholds, one byte a site (0x80 -
+// 2 u*, u* the smallest count of unsatisfied bonds that accepts), and a phase adds to them twice the
+// unsatisfied bonds and flips where bit 7 comes up.  LDS keeps a byte per site, 0x00 (+1) or 0x02
+// (-1), in two planes by colour: plane c holds the four colour-c sites of a group as one dword, so the
+// active sites and the row and plane neighbours of a phase are dwords as they stand.  For the +-J
+// glass two more planes hold the couplings (bit 1 the bond to x+1, bit 2 to y+1, bit 3 to z+1 of
+// each site), staged once per launch and reused by all k hits.  Hit h of sweep t draws from Philox
+// counter (s>>3, t*k + h, replica, colour), as the oracle's coarse mode does.
+// us a launch of 4 hits, before (nibble words, bounds looked up in each phase) and now, 2D Ising L = 1024: T = 8
+// 11.1 -> 4.7, 16 5.6 -> 4.3, 32 5.8 -> 4.8, 64 6.9 -> 5.2; L = 4096, T = 8 120 -> 26, T = 32, where issue
+// bounds it, 21.2 -> 20.1; 3D L = 256, T = 16 25.8 -> 24.4.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "spin_internal.h"
+#include "spin_device.h"
+#include "spin_lds.h"
 #include "spin_nibble.h"
 #include "spin_packed.h"
+#include "spin_tile.h"
 
 namespace spin {
 
 struct CoarseArgs {
   RoundKeys keys;
   uint32_t bound[8];
-  uint32_t never4;   // 4 * never_level
+  uint32_t never;    // never_level
   uint32_t L;
+  uint32_t tiles;    // tiles of one parity
   uint32_t t;        // sweep index
   uint32_t k;        // hits per tile load
   uint32_t replica;
   uint32_t q;        // tile parity of this launch
 };
 
-// nib_flips with the bounds from the pair table (spin_packed.h): the active
-// nibbles' counts 2u, shifted to 8u per byte, give the byte offsets of two
-// 8-byte entries (sites 0 and 1, sites 2 and 3) in two operations where four
-// extractions were; never8 = 8 never_level.
-template <bool NEVER>
-__device__ __forceinline__ uint32_t nib_flips_pair(uint32_t S, uint32_t p, const uint32_t r[4], const char* pair,
-                                                   uint32_t never8) {
-  const uint32_t T = ((S >> (4u * p)) & 0x0F0F0F0Fu) << 2;  // byte i: 8u of active nibble i
-  const uint4 b = lookup_pair(T, pair);
-  bool a0 = r[0] <= b.x, a1 = r[1] <= b.y, a2 = r[2] <= b.z, a3 = r[3] <= b.w;
-  if (NEVER) {
-    a0 = a0 && (T & 0xFFu) >= never8;
-    a1 = a1 && __builtin_amdgcn_perm(0u, T, 0x0C0C0C01u) >= never8;
-    a2 = a2 && __builtin_amdgcn_ubfe(T, 16u, 8u) >= never8;
-    a3 = a3 && (T >> 24) >= never8;
-  }
-  return (xor3(a0 ? 0xEu : 0u, a1 ? 0xE00u : 0u, a2 ? 0xE0000u : 0u) ^ (a3 ? 0xE000000u : 0u)) << (4u * p);
-}
+constexpr uint32_t kCoarseNeg = 0x02020202u;
+constexpr uint32_t kCoarseAhead = 4;  // hits drawn at a time
 
 __device__ __forceinline__ uint32_t wrap_m1(uint32_t v, uint32_t n) {  // (v - 1) mod n for v < 2n
   uint32_t w = v + n - 1u;
   return w >= n ? (w >= 2u * n ? w - 2u * n : w - n) : w;
 }
 
-template <int D, int T, bool EA, bool NEVER, int NT>
-__global__ __launch_bounds__(NT) void k_coarse(int8_t* __restrict__ spins, const uint32_t* __restrict__ Jraw,
-                                               CoarseArgs a) {
-  constexpr uint32_t TW = T / 8;                     // words per tile row
-  constexpr uint32_t RW = TW + 2;                    // words per LDS row
-  constexpr uint32_t RR = T + 2;                     // LDS rows per plane
-  constexpr uint32_t PL = (D == 3) ? T + 2 : 1;      // LDS planes
-  constexpr uint32_t PW = RR * RW;                   // words per LDS plane
-  constexpr uint32_t NWL = PL * PW;                  // words of the LDS block
-  constexpr uint32_t U = (D == 3) ? T * T * TW : T * TW;  // units (tile words) per colour step
-  // accept bounds: the pair table (8 KB) for 2D tiles of edge 32 and 64, the per-u table otherwise
-  // (with the small workgroups of smaller tiles, or the 12 KB table of 3D, LDS would cost
-  // workgroups per CU: 2D T = 16 lost 25 % at k = 1 with it)
-  constexpr bool PAIR = D == 2 && T >= 32;
-  __shared__ __align__(16) uint32_t bound[PAIR ? pair_words(4) : 8];
-  __shared__ uint32_t sp[NWL];
-  __shared__ uint32_t jl[EA ? D * NWL : 1];
+// Thresholds of a unit's four sites: byte i is 0x80 - 2 u*, u* = the classes u < D that draw i does
+// not accept (the bounds grow with u, and u >= D always accepts).
+template <int D, bool NEVER>
+__device__ __forceinline__ uint32_t coarse_draw(const CoarseArgs& a, uint32_t w, uint32_t hit, uint32_t c) {
+  const PhiloxUniform U = philox_uniform(hit, a.replica, c, a.keys);
+  uint32_t r[4], k = 0;
+  philox_lane(w, U, a.keys, r);
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    if (i < 3) k <<= 8;
+#pragma unroll
+    for (uint32_t u = 0; u < (uint32_t)D; ++u) k += (r[i] > a.bound[u]) | (NEVER && u < a.never) ? 1u : 0u;
+  }
+  return 0x80808080u - (k << 1);
+}
+
+// Tile `first + slot` of the launch's parity (bx + by (+ bz) = q mod 2): word column, row and plane of its first
+// site.  first is uniform: the divisions are done once for the workgroup.
+template <int D, int T>
+__device__ __forceinline__ void coarse_tile(const CoarseArgs& a, uint32_t first, uint32_t slot, uint32_t& x0w,
+                                            uint32_t& y0, uint32_t& z0) {
+  const uint32_t B = a.L / T, nbx = B / 2u;
+  uint32_t bxh = first % nbx + slot, byz = first / nbx;
+  if (slot) {  // (always 0 where a tile fills the workgroup)
+    const uint32_t last = a.tiles - 1u - first;  // a slot past the last tile repeats that
+    if (slot > last) bxh += last - slot;
+    while (bxh >= nbx) {
+      bxh -= nbx;
+      ++byz;
+    }
+  }
+  const uint32_t by = D == 3 ? byz % B : byz, bz = D == 3 ? byz / B : 0u;
+  x0w = (2u * bxh + ((by + bz + a.q) & 1u)) * (T / 8u);
+  y0 = by * T;
+  z0 = bz * T;
+}
+
+template <int D, int T, bool EA, bool NEVER>
+struct CoarseShape {
+  static constexpr uint32_t TW = T / 8;                       // groups per tile row
+  static constexpr uint32_t U = (D == 3 ? T : 1) * T * TW;    // units of a tile
+  static constexpr uint32_t NT = U < 64 ? 64 : U;             // threads: a unit each
+  static constexpr uint32_t TPW = NT / U;                     // tiles of a workgroup
+  static constexpr uint32_t RW = TW + 2;                      // groups per LDS row: one more on either side
+  static constexpr uint32_t RR = T + 2;                       // rows per LDS plane
+  static constexpr uint32_t NG = (D == 3 ? T + 2 : 1) * RR * RW;  // groups of a tile's region
+  static constexpr uint32_t PB = 4 * NG;                      // bytes of a colour plane
+  static constexpr uint32_t TB = PB * (EA ? 4 : 2);           // bytes of a tile
+  // Groups read, NL a thread.  2D: its own and those left and right of the tile's rows; 3D, where a tile's
+  // row is one or two groups, whole rows with both (a wavefront's loads of the sides alone touch as many
+  // lines again: +-J L = 256, T = 8, k = 1 47.8 us a launch so, 34.7 by rows).  Both: the rows
+  // around the tile's.  Edges and corners are not read.
+  static constexpr bool OWN = D == 2;
+  static constexpr uint32_t CX = OWN ? 2 : RW;                // of a tile's row
+  static constexpr uint32_t RX = CX * (D == 3 ? T * T : T);
+  static constexpr uint32_t RG = RX + (D == 3 ? 4 * T : 2) * TW;
+  static constexpr uint32_t NL = (TPW * RG + NT - 1) / NT;
+  // group number e of a tile: LDS plane p, row r and column wi, counted from the boundary
+  __device__ static __forceinline__ void place(uint32_t e, uint32_t& p, uint32_t& r, uint32_t& wi) {
+    if (e < RX) {
+      const uint32_t row = e / CX;
+      wi = e - row * CX;
+      if (OWN) wi = wi ? TW + 1u : 0u;
+      r = row % T + 1u;
+      p = D == 3 ? row / T + 1u : 0u;
+    } else {
+      const uint32_t f = e - RX, row = f / TW, side = D == 3 ? row / T : row, i = row % T + 1u;
+      wi = f % TW + 1u;
+      const uint32_t out = (side & 1u) ? T + 1u : 0u;
+      r = side < 2u ? out : i;
+      p = D == 2 ? 0u : (side < 2u ? i : out);
+    }
+  }
+};
+
+template <int D, int T, bool EA, bool NEVER>
+__global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(int8_t* __restrict__ spins,
+                                                                              const uint32_t* __restrict__ Jraw,
+                                                                              CoarseArgs a) {
+  using S = CoarseShape<D, T, EA, NEVER>;
+  constexpr uint32_t RS = 4 * S::RW, PS = RS * S::RR;  // LDS bytes of a row, of a z plane
+  __shared__ __align__(16) char lds[S::TPW * S::TB];
+  const uint32_t base = lds_addr(lds), tid = threadIdx.x;
   const uint32_t L = a.L, GPR = L / 8;
-  const uint32_t NW = (D == 3) ? L * L * GPR : L * GPR;  // words of one direction of couplings
-  // Workgroups are dealt to the 8 XCDs round-robin; renumber them so that each XCD takes a
-  // contiguous run of tiles in (x, y, z) order: neighbouring tiles share the 128-byte lines of their
-  // rows and their boundary rows, and then they share one L2.
-  const uint32_t nbx = gridDim.x, nby = gridDim.y, nblk = gridDim.x * gridDim.y * gridDim.z;
-  uint32_t blk = blockIdx.x + nbx * (blockIdx.y + nby * blockIdx.z);
-  if ((nblk & 7u) == 0) blk = (blk & 7u) * (nblk >> 3) + (blk >> 3);
-  const uint32_t bxh = blk % nbx, byz = blk / nbx;
-  // tile coordinates: the launch covers the tiles with bx + by (+ bz) = q (mod 2)
-  const uint32_t by = byz % nby, bz = (D == 3) ? byz / nby : 0u;
-  const uint32_t bx = 2u * bxh + ((by + bz + a.q) & 1u);
-  const uint32_t x0w = bx * TW, y0 = by * T, z0 = bz * T;  // first word column, row, plane
-  if (PAIR)
-    fill_pair<4>(bound, a.bound, threadIdx.x);
-  else if (threadIdx.x < 8)
-    bound[threadIdx.x] = a.bound[threadIdx.x];
+  const uint32_t first = xcd_tile() * S::TPW;  // neighbouring tiles share the lines of their rows: one L2
   gu32* Jn = as_global(Jraw);
-  // load the tile and its boundary layer
-  for (uint32_t i = threadIdx.x; i < NWL; i += NT) {
-    const uint32_t p = i / PW, rem = i - p * PW, r = rem / RW, wi = rem - r * RW;
-    const uint32_t y = wrap_m1(y0 + r, L);
-    const uint32_t z = (D == 3) ? wrap_m1(z0 + p, L) : 0u;
-    const uint32_t xw = wrap_m1(x0w + wi, GPR);
-    const uint32_t w = (D == 3) ? (z * L + y) * GPR + xw : y * GPR + xw;
-    const uint2 b = reinterpret_cast<const uint2*>(spins)[w];
-    sp[i] = pack_nibbles(b.x, b.y);
+  const uint32_t NW = (D == 3) ? L * L * GPR : L * GPR;  // words of one direction of couplings
+  // this thread's unit: group cw of row ry, plane rz of tile `slot` (a tile past the last one repeats
+  // that: loaded, updated, not stored)
+  const uint32_t slot = S::TPW > 1 ? tid / S::U : 0u, u = tid - slot * S::U;
+  const uint32_t cw = u % S::TW, rows = u / S::TW;
+  const uint32_t ry = rows % T, rz = (D == 3) ? rows / T : 0u;
+  uint32_t x0w, y0, z0;
+  coarse_tile<D, T>(a, first, slot, x0w, y0, z0);
+  const uint32_t w = ((z0 + rz) * L + y0 + ry) * GPR + x0w + cw;
+  const uint32_t at = base + slot * S::TB + (D == 3 ? (rz + 1u) * PS : 0u) + (ry + 1u) * RS + 4u * (cw + 1u);
+  const bool odd = ((ry + rz) & 1u) != 0;  // colour-0 sites of the row are its odd x (tile edges are even)
+  uint2 sp[S::NL + 1];
+  uint32_t jw[S::NL + 1][EA ? D : 1];
+  auto load = [&](uint32_t n, uint32_t g) {
+    sp[n] = reinterpret_cast<const uint2*>(spins)[g];
     if (EA) {
 #pragma unroll
-      for (int dir = 0; dir < D; ++dir) jl[dir * NWL + i] = Jn[dir * NW + w];
+      for (int dir = 0; dir < D; ++dir) jw[n][dir] = Jn[dir * NW + g];
+    }
+  };
+  if (S::OWN) load(S::NL, w);
+#pragma unroll
+  for (uint32_t n = 0; n < S::NL; ++n) {
+    const uint32_t i = tid + n * S::NT;
+    if (S::TPW * S::RG % S::NT == 0 || i < S::TPW * S::RG) {
+      const uint32_t sl = S::TPW > 1 ? i / S::RG : 0u;
+      uint32_t p, r, wi, xw, y, z;
+      S::place(i - sl * S::RG, p, r, wi);
+      coarse_tile<D, T>(a, first, sl, xw, y, z);
+      y = wrap_m1(y + r, L);
+      xw = wrap_m1(xw + wi, GPR);
+      z = (D == 3) ? wrap_m1(z + p, L) : 0u;
+      load(n, (z * L + y) * GPR + xw);
+    }
+  }
+  uint32_t th[kCoarseAhead][2];
+#pragma unroll
+  for (uint32_t j = 0; j < kCoarseAhead; ++j)
+    if (j < a.k) {
+      th[j][0] = coarse_draw<D, NEVER>(a, w, a.t * a.k + j, 0u);
+      th[j][1] = coarse_draw<D, NEVER>(a, w, a.t * a.k + j, 1u);
+    }
+  __builtin_amdgcn_sched_barrier(0);
+  auto put = [&](uint32_t n, uint32_t o, bool po) {
+    const uint2 h = split_group(sp[n].x & kCoarseNeg, sp[n].y & kCoarseNeg);
+    lds_store32(o, po ? h.y : h.x);
+    lds_store32(o + S::PB, po ? h.x : h.y);
+    if (EA) {
+      // nibble j of a word is site j's coupling (0x1 or 0xF): its even and its odd nibbles are the two planes' bytes
+      uint32_t je = jw[n][0] & kCoarseNeg, jo = (jw[n][0] >> 4) & kCoarseNeg;
+#pragma unroll
+      for (int dir = 1; dir < D; ++dir) {
+        je |= (jw[n][EA ? dir : 0] & kCoarseNeg) << dir;
+        jo |= ((jw[n][EA ? dir : 0] >> 4) & kCoarseNeg) << dir;
+      }
+      lds_store32(o + 2u * S::PB, po ? jo : je);
+      lds_store32(o + 3u * S::PB, po ? je : jo);
+    }
+  };
+  if (S::OWN) put(S::NL, at, odd);
+#pragma unroll
+  for (uint32_t n = 0; n < S::NL; ++n) {
+    const uint32_t i = tid + n * S::NT;
+    if (S::TPW * S::RG % S::NT == 0 || i < S::TPW * S::RG) {
+      const uint32_t sl = S::TPW > 1 ? i / S::RG : 0u;
+      uint32_t p, r, wi;
+      S::place(i - sl * S::RG, p, r, wi);
+      // rows count from the boundary row, planes from its plane
+      put(n, base + sl * S::TB + p * PS + r * RS + 4u * wi, ((r + (D == 3 ? p : 1u)) & 1u) != 0);
     }
   }
   __syncthreads();
-  for (uint32_t h = 0; h < a.k; ++h) {
-    const uint32_t hit = a.t * a.k + h;
-#pragma unroll 1
-    for (uint32_t c = 0; c < 2; ++c) {
-      const PhiloxUniform Uph = philox_uniform(hit, a.replica, c, a.keys);
-      for (uint32_t u = threadIdx.x; u < U; u += NT) {
-        // unit u: tile row ry, plane rz, word column cw
-        const uint32_t cw = u % TW, rows = u / TW;
-        const uint32_t ry = (D == 3) ? rows % T : rows, rz = (D == 3) ? rows / T : 0u;
-        const uint32_t o = ((D == 3) ? (rz + 1) * PW : 0u) + (ry + 1) * RW + 1 + cw;
-        const uint32_t cv = sp[o];
-        uint32_t nb[2 * D - 2];
-        nb[0] = sp[o - RW];
-        nb[1] = sp[o + RW];
-        if (D == 3) {
-          nb[2] = sp[o - PW];
-          nb[3] = sp[o + PW];
-        }
-        uint32_t jn[2 * D];
-        if (EA) {
-          jn[0] = __builtin_amdgcn_alignbit(jl[o], jl[o - 1], 28);  // bond (x-1, x) of each site
-          jn[1] = jl[o];
-          jn[2] = jl[NWL + o - RW];
-          jn[3] = jl[NWL + o];
-          if (D == 3) {
-            jn[4] = jl[2 * NWL + o - PW];
-            jn[5] = jl[2 * NWL + o];
-          }
-        }
-        const uint32_t S = nib_unsat<D, EA>(cv, sp[o - 1], sp[o + 1], nb, jn);
-        const uint32_t y = y0 + ry, z = z0 + rz;
-        const uint32_t w = (D == 3) ? (z * L + y) * GPR + x0w + cw : y * GPR + x0w + cw;
-        uint32_t rnd[4];
-        philox_lane(w, Uph, a.keys, rnd);
-        const uint32_t p = (c + y + z) & 1u;
-        sp[o] = cv ^ (PAIR ? nib_flips_pair<NEVER>(S, p, rnd, (const char*)bound, 2u * a.never4)
-                           : nib_flips<NEVER>(S, p, rnd, bound, a.never4));
+  // colour c of a hit with thresholds t
+  auto phase = [&](uint32_t c, uint32_t t) {
+    const uint32_t am = at + (c ? S::PB : 0u), ao = at + (c ? 0u : S::PB);
+    const bool P = odd == (c != 0);  // active sites: even x (row parity and colour the same)
+    const uint32_t A = lds_load32(am), I = lds_load32(ao), W = lds_load32(P ? ao - 4u : ao + 4u);
+    const uint32_t ym = lds_load32(ao - RS), yp = lds_load32(ao + RS);
+    const uint32_t zm = D == 3 ? lds_load32(ao - PS) : 0u, zp = D == 3 ? lds_load32(ao + PS) : 0u;
+    // the row neighbours on the other side: the other plane moved by a byte
+    const uint32_t N = __builtin_amdgcn_perm(I, W, P ? 0x06050403u : 0x00070605u);
+    uint32_t X = t;
+    if (EA) {
+      const uint32_t jm = am + 2u * S::PB, jo = ao + 2u * S::PB;
+      const uint32_t own = lds_load32(jm), oth = lds_load32(jo), left = lds_load32(jo - 4u), jym = lds_load32(jo - RS);
+      const uint32_t lj = __builtin_amdgcn_perm(oth, left, 0x06050403u);  // x bonds of the sites to the left
+      X += ((I ^ (P ? own : oth)) & kCoarseNeg) ^ A;
+      X += ((N ^ (P ? lj : own)) & kCoarseNeg) ^ A;
+      X += ((yp ^ (own >> 1)) & kCoarseNeg) ^ A;
+      X += ((ym ^ (jym >> 1)) & kCoarseNeg) ^ A;
+      if (D == 3) {
+        X += ((zp ^ (own >> 2)) & kCoarseNeg) ^ A;
+        X += ((zm ^ (lds_load32(jo - PS) >> 2)) & kCoarseNeg) ^ A;
       }
-      __syncthreads();
+    } else {
+      X += I ^ A;
+      X += N ^ A;
+      X += ym ^ A;
+      X += yp ^ A;
+      if (D == 3) {
+        X += zm ^ A;
+        X += zp ^ A;
+      }
     }
+    lds_store32(am, A ^ ((X >> 6) & kCoarseNeg));
+    __syncthreads();
+  };
+  for (uint32_t h = 0;;) {
+#pragma unroll
+    for (uint32_t j = 0; j < kCoarseAhead; ++j)
+      if (h + j < a.k) {
+        phase(0u, th[j][0]);
+        phase(1u, th[j][1]);
+      }
+    h += kCoarseAhead;
+    if (h >= a.k) break;
+#pragma unroll
+    for (uint32_t j = 0; j < kCoarseAhead; ++j)
+      if (h + j < a.k) {
+        th[j][0] = coarse_draw<D, NEVER>(a, w, a.t * a.k + h + j, 0u);
+        th[j][1] = coarse_draw<D, NEVER>(a, w, a.t * a.k + h + j, 1u);
+      }
   }
-  // write the tile back
-  for (uint32_t u = threadIdx.x; u < U; u += NT) {
-    const uint32_t cw = u % TW, rows = u / TW;
-    const uint32_t ry = (D == 3) ? rows % T : rows, rz = (D == 3) ? rows / T : 0u;
-    const uint32_t o = ((D == 3) ? (rz + 1) * PW : 0u) + (ry + 1) * RW + 1 + cw;
-    const uint32_t y = y0 + ry, z = z0 + rz;
-    const uint32_t w = (D == 3) ? (z * L + y) * GPR + x0w + cw : y * GPR + x0w + cw;
-    uint2 b;
-    unpack_nibbles(sp[o], b.x, b.y);
-    reinterpret_cast<uint2*>(spins)[w] = b;
+  // write the tile back: 0x00 -> 0x01, 0x02 -> 0xFF by v_perm as a table of two bytes
+  if (first + slot < a.tiles) {
+    const uint32_t c0 = __builtin_amdgcn_perm(0u, 0x00FF0001u, lds_load32(at));
+    const uint32_t c1 = __builtin_amdgcn_perm(0u, 0x00FF0001u, lds_load32(at + S::PB));
+    reinterpret_cast<uint2*>(spins)[w] = join_group(odd ? make_uint2(c1, c0) : make_uint2(c0, c1));
   }
 }
 
@@ -170,17 +283,21 @@ bool coarse_supported(const Lat& lat, int T) {
   return T == 8 || T == 16;
 }
 
-template <int D, int T, int NT>
-static hipError_t go_coarse(const Lat& lat, const uint32_t* Jn, const CoarseArgs& a, bool never, hipStream_t stream) {
-  const uint32_t B = lat.L / T;
-  const dim3 grid(B / 2, B, D == 3 ? B : 1);
-  const bool ea = lat.J != nullptr;
-  if (ea && never) hipLaunchKernelGGL((k_coarse<D, T, true, true, NT>), grid, dim3(NT), 0, stream, lat.spins, Jn, a);
-  if (ea && !never) hipLaunchKernelGGL((k_coarse<D, T, true, false, NT>), grid, dim3(NT), 0, stream, lat.spins, Jn, a);
-  if (!ea && never) hipLaunchKernelGGL((k_coarse<D, T, false, true, NT>), grid, dim3(NT), 0, stream, lat.spins, Jn, a);
-  if (!ea && !never)
-    hipLaunchKernelGGL((k_coarse<D, T, false, false, NT>), grid, dim3(NT), 0, stream, lat.spins, Jn, a);
+template <int D, int T, bool EA, bool NEVER>
+static hipError_t run_coarse(const Lat& lat, const uint32_t* Jn, const CoarseArgs& a, hipStream_t stream) {
+  using S = CoarseShape<D, T, EA, NEVER>;
+  hipLaunchKernelGGL((k_coarse<D, T, EA, NEVER>), dim3((a.tiles + S::TPW - 1) / S::TPW), dim3(S::NT), 0, stream,
+                     lat.spins, Jn, a);
   return hipGetLastError();
+}
+
+template <int D, int T>
+static hipError_t go_coarse(const Lat& lat, const uint32_t* Jn, CoarseArgs a, bool never, hipStream_t stream) {
+  const uint32_t B = lat.L / T;
+  a.tiles = B / 2 * B * (D == 3 ? B : 1);
+  if (lat.J != nullptr)
+    return never ? run_coarse<D, T, true, true>(lat, Jn, a, stream) : run_coarse<D, T, true, false>(lat, Jn, a, stream);
+  return never ? run_coarse<D, T, false, true>(lat, Jn, a, stream) : run_coarse<D, T, false, false>(lat, Jn, a, stream);
 }
 
 hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, uint32_t k, uint32_t q,
@@ -190,7 +307,7 @@ hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, u
   CoarseArgs a;
   a.keys = lat.keys;
   for (int i = 0; i < 8; ++i) a.bound[i] = acc.bound[i];
-  a.never4 = 4u * acc.never_level;
+  a.never = acc.never_level;
   a.L = lat.L;
   a.t = t;
   a.k = k;
@@ -198,13 +315,13 @@ hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, u
   a.q = q;
   const bool never = acc.never_level > 0;
   if (lat.d == 2) {
-    if (T == 8) return go_coarse<2, 8, 64>(lat, Jn, a, never, stream);
-    if (T == 16) return go_coarse<2, 16, 64>(lat, Jn, a, never, stream);
-    if (T == 32) return go_coarse<2, 32, 128>(lat, Jn, a, never, stream);
-    return go_coarse<2, 64, 256>(lat, Jn, a, never, stream);
+    if (T == 8) return go_coarse<2, 8>(lat, Jn, a, never, stream);
+    if (T == 16) return go_coarse<2, 16>(lat, Jn, a, never, stream);
+    if (T == 32) return go_coarse<2, 32>(lat, Jn, a, never, stream);
+    return go_coarse<2, 64>(lat, Jn, a, never, stream);
   }
-  if (T == 8) return go_coarse<3, 8, 64>(lat, Jn, a, never, stream);
-  return go_coarse<3, 16, 256>(lat, Jn, a, never, stream);
+  if (T == 8) return go_coarse<3, 8>(lat, Jn, a, never, stream);
+  return go_coarse<3, 16>(lat, Jn, a, never, stream);
 }
 
 }  // namespace spin

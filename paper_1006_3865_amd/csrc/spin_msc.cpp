@@ -36,7 +36,6 @@ struct spin_msc {
   uint32_t TY, H, NT, XW;  // streaming shape; NT == 0: the per-colour phase kernel
   bool col;          // the register-column kernel (3D L = 512; shape TY, H)
   uint32_t* J;       // [d][N] (measurement)
-  uint32_t* J6;      // [N/8][2][4][2d]: bonds of the active sites of each group and colour (phase kernel, on first use)
   int64_t* part;     // measurement partial counts
   int64_t* rec;      // records staging (2 * 32 * rec_cap)
   size_t rec_cap;
@@ -49,7 +48,6 @@ static void msc_destroy(spin_msc* h) {
   device_free(h->S);
   device_free(h->S2);
   device_free(h->J);
-  device_free(h->J6);
   device_free(h->part);
   device_free(h->rec);
   delete h;
@@ -82,11 +80,6 @@ static int msc_run(spin_msc* h, int n, double beta, int every, int64_t* dE, int6
   MscArgs a = msc_args(h, beta);
   const bool streamed = h->NT || h->col;
   if (streamed && !h->S2 && n > 0 && !dalloc(&h->S2, h->N * 4)) return mfail(SPIN_ENOMEM, "second spin buffer");
-  if (!streamed && !h->J6 && n > 0) {
-    if (!dalloc(&h->J6, (size_t)2 * h->d * h->N * 4)) return mfail(SPIN_ENOMEM, "coupling copy");
-    hipError_t e = launch_msc_bonds(h->J, h->J6, (uint32_t)h->L, (uint32_t)h->d, h->N, h->stream);
-    if (e != hipSuccess) return mfail(SPIN_EDEVICE, "coupling copy: %s", hipGetErrorString(e));
-  }
   uint32_t rec = 0;
   for (int i = 0; i < n; ++i) {
     a.t = (uint32_t)(h->t + (uint64_t)i);
@@ -101,7 +94,7 @@ static int msc_run(spin_msc* h, int n, double beta, int every, int64_t* dE, int6
     } else {
       for (uint32_t c = 0; c < 2; ++c) {
         a.colour = c;
-        hipError_t e = launch_msc_phase(h->S, h->J6, a, (uint32_t)h->d, h->stream);
+        hipError_t e = launch_msc_phase(h->S, h->J, a, (uint32_t)h->d, h->stream);
         if (e != hipSuccess) return mfail(SPIN_EDEVICE, "multi-spin phase launch: %s", hipGetErrorString(e));
       }
     }
@@ -154,8 +147,7 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
   h->S = nullptr;
   h->S2 = nullptr;
   h->J = nullptr;
-  h->J6 = nullptr;
-  // streaming shape, from measured rates: 3D whole rows in slabs of 16 rows (from L = 256 up, where
+  // streaming shape, from measured rates (used where neither rule below takes another kernel): 3D whole rows in slabs of 16 rows (from L = 256 up, where
   // the ring fits LDS), else 8, else 4, and strips of planes sized so that the grid holds about one
   // workgroup per compute unit (at least 4 planes); 512 threads from L = 256 up, else 256.  2D rows
   // cut into segments of at most 2048 sites, strips of 16 rows, 256 threads.  Else the phase kernel.
@@ -205,6 +197,12 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
     h->H = 16;
     if (msc_stream_supported((uint32_t)L, 2, 1, h->H, 256, h->XW)) h->NT = 256;
   }
+  // While spins and couplings stay in the 256 MB memory-side cache the phase kernel, which has every load in
+  // flight at once, beats the planes' march (a barrier and a round of loads a step): us a sweep 2D L =
+  // 64 7.3 against 33.5, 1024 9.1 against 32.6, 2048 25 against 45; 3D L = 64 8.1 against 18.9, 160 32
+  // against 55, 200 55 against 101, 256 100 against 118.  Beyond, reading the couplings twice a
+  // sweep costs more: 2D L = 3072 54 against 48, 4096 87 against 68; 3D L = 320 337 against 250.
+  if (N * 4 * (uint64_t)(d + 1) <= (uint64_t)(d == 3 ? 288 : 100) << 20) h->NT = 0;
   h->part = nullptr;
   h->rec = nullptr;
   h->rec_cap = 0;

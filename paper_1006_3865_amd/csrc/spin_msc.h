@@ -24,10 +24,8 @@ hipError_t launch_msc_init(uint32_t* S, uint64_t N, uint64_t seed, uint32_t p0, 
 // split by x parity (even-x words first).
 hipError_t launch_msc_couplings(uint32_t* J, uint64_t N, uint32_t L, uint32_t d, uint64_t cseed, uint32_t r0,
                                 hipStream_t stream);
-// J6: per 8-site group and colour, the 2d coupling words of each of the 4
-// active sites (-x, +x, -y, +y, -z, +z), 2d*N words, built from J.
-hipError_t launch_msc_bonds(const uint32_t* J, uint32_t* J6, uint32_t L, uint32_t d, uint64_t N, hipStream_t stream);
-hipError_t launch_msc_phase(uint32_t* S, const uint32_t* J6, const MscArgs& a, uint32_t d, hipStream_t stream);
+// One colour phase, in place.
+hipError_t launch_msc_phase(uint32_t* S, const uint32_t* J, const MscArgs& a, uint32_t d, hipStream_t stream);
 // One sweep per launch, streamed over planes (both colours; ping-pong
 // src -> dst): TY rows per workgroup (3D, divides L, <= 32), H planes per
 // strip, NT = 256 or 512 threads, XW sites of each row per workgroup (a

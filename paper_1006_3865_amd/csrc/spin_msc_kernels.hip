@@ -21,8 +21,12 @@
 #include "spin_device.h"
 #include "spin_internal.h"
 #include "spin_msc.h"
+#include "spin_tile.h"
 
 namespace spin {
+
+// A register vector: copies of uint4 structs are lowered to memcpy and left in scratch.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
@@ -144,27 +148,6 @@ __device__ __forceinline__ void msc_update8(uint32_t (&c)[8], uint32_t lw, uint3
   }
 }
 
-// Couplings of the active sites of group g in colour c: J6 holds, per group
-// and colour, 4 x 2d words (site i's bonds -x, +x, -y, +y(, -z, +z)).
-template <int D>
-__device__ __forceinline__ void load_bonds(const uint32_t* __restrict__ J6, uint64_t g, uint32_t c,
-                                           uint32_t (&jb)[4][2 * D]) {
-  const uint4* p = reinterpret_cast<const uint4*>(J6 + (g * 2 + c) * (8 * D));
-  uint32_t w[8 * D];
-#pragma unroll
-  for (int q = 0; q < 2 * D; ++q) {
-    const uint4 v = p[q];
-    w[4 * q] = v.x;
-    w[4 * q + 1] = v.y;
-    w[4 * q + 2] = v.z;
-    w[4 * q + 3] = v.w;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int k = 0; k < 2 * D; ++k) jb[i][k] = w[i * 2 * D + k];
-}
-
 // The couplings of the four active sites of a group in the order of
 // msc_update8: x bonds from the group's x-bond words jx (jl: the word left of
 // the group), y and z bonds from the parity-P halves jy/jym (rows y, y-1) and
@@ -187,78 +170,100 @@ __device__ __forceinline__ void bonds_split(const uint32_t (&jx)[8], uint32_t jl
   }
 }
 
-// Build J6 from the [dir][site] couplings: thread = (group, colour).
+// The four active sites A of a group after their update: o the other colour's sites of the group, of which
+// each is a neighbour on one side, and N the neighbours on the other; ym, yp, zm, zp those in the
+// neighbouring rows and planes; jo, jn, jym, jy, jzm, jz the bonds to them; r the shared draws.
 template <int D>
-__global__ void k_msc_bonds(const uint32_t* __restrict__ J, uint32_t* __restrict__ J6, uint32_t L, uint64_t N) {
-  const uint32_t GPR = L / 8;
-  const uint64_t row = L, plane = (uint64_t)L * L;
-  for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < N / 4; q += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t g = q >> 1;
-    const uint32_t c = (uint32_t)(q & 1);
-    const uint64_t rowi = g / GPR;
-    const uint32_t x0 = (uint32_t)(g - rowi * GPR) * 8u;
-    const uint32_t y = (uint32_t)(rowi % L), z = (D == 3) ? (uint32_t)(rowi / L) : 0u;
-    const uint32_t P = (c + y + z) & 1u;
-    uint32_t* out = J6 + q * (8 * D);
-    for (uint32_t i = 0; i < 4; ++i) {
-      const uint32_t x = x0 + 2 * i + P;
-      const uint64_t s = g * 8 + 2 * i + P;
-      const uint64_t sxm = x ? s - 1 : s + L - 1;
-      const uint64_t sym = y ? s - row : s + (L - 1) * row;
-      out[i * 2 * D + 0] = J[sxm];
-      out[i * 2 * D + 1] = J[s];
-      out[i * 2 * D + 2] = J[N + msc_split(sym, L)];
-      out[i * 2 * D + 3] = J[N + msc_split(s, L)];
-      if (D == 3) {
-        const uint64_t szm = z ? s - plane : s + (L - 1) * plane;
-        out[i * 2 * D + 4] = J[2 * N + msc_split(szm, L)];
-        out[i * 2 * D + 5] = J[2 * N + msc_split(s, L)];
-      }
+__device__ __forceinline__ u32x4 msc_update4(u32x4 A, u32x4 o, u32x4 N, u32x4 ym, u32x4 yp, u32x4 zm, u32x4 zp, u32x4 jo,
+                                             u32x4 jn, u32x4 jym, u32x4 jy, u32x4 jzm, u32x4 jz, const uint32_t (&r)[4],
+                                             const uint64_t (&thr)[3]) {
+  u32x4 out;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t s = A[i];
+    const uint32_t b0 = xor3(s, o[i], jo[i]), b1 = xor3(s, N[i], jn[i]);
+    const uint32_t b2 = xor3(s, ym[i], jym[i]), b3 = xor3(s, yp[i], jy[i]);
+    const uint32_t s1 = xor3(b0, b1, b2), c1 = maj3(b0, b1, b2);
+    uint32_t u0, u1, u2;
+    if (D == 3) {
+      const uint32_t b4 = xor3(s, zm[i], jzm[i]), b5 = xor3(s, zp[i], jz[i]);
+      const uint32_t s2 = xor3(b3, b4, b5), c2 = maj3(b3, b4, b5);
+      u0 = s1 ^ s2;
+      const uint32_t t = s1 & s2;
+      u1 = xor3(c1, c2, t);
+      u2 = maj3(c1, c2, t);
+    } else {
+      u0 = s1 ^ b3;
+      const uint32_t t = s1 & b3;
+      u1 = c1 ^ t;
+      u2 = c1 & t;
     }
+    out[i] = s ^ msc_flips<D>(u0, u1, u2, r[i], thr);
   }
+  return out;
 }
 
-// One colour phase: thread = 8-site group g (sites 8g .. 8g+7 of one row);
-// its four sites of colour c (offset P = (c + y + z) & 1 inside the group).
-template <int D, int P>
-__device__ __forceinline__ void msc_group(uint32_t* __restrict__ S, const uint32_t* __restrict__ J6,
-                                          const MscArgs& a, uint64_t s0, uint32_t x0, uint32_t y, uint32_t z,
-                                          const uint32_t (&r)[4]) {
-  const uint32_t L = a.L;
-  const uint64_t row = (uint64_t)L, plane = (uint64_t)L * L;
-  uint32_t c[8], ym[8], yp[8], zm[8], zp[8];
-  load8(S + s0, c);
-  load8(S + (y ? s0 - row : s0 + (L - 1) * row), ym);
-  load8(S + ((y + 1 < L) ? s0 + row : s0 - (L - 1) * row), yp);
-  if (D == 3) {
-    load8(S + (z ? s0 - plane : s0 + (L - 1) * plane), zm);
-    load8(S + ((z + 1 < L) ? s0 + plane : s0 - (L - 1) * plane), zp);
-  }
-  uint32_t jb[4][2 * D];
-  load_bonds<D>(J6, s0 >> 3, a.colour, jb);
-  const uint64_t sl = x0 ? s0 - 1 : s0 + L - 1;     // site left of the group
-  const uint64_t sr = (x0 + 8 < L) ? s0 + 8 : s0 + 8 - L;
-  msc_update8<D, P>(c, S[sl], S[sr], ym, yp, zm, zp, jb, r, a);
-  reinterpret_cast<uint4*>(S + s0)[0] = make_uint4(c[0], c[1], c[2], c[3]);
-  reinterpret_cast<uint4*>(S + s0)[1] = make_uint4(c[4], c[5], c[6], c[7]);
+__device__ __forceinline__ u32x4 sel4(bool c, u32x4 x, u32x4 y) {
+  return u32x4{c ? x.x : y.x, c ? x.y : y.y, c ? x.z : y.z, c ? x.w : y.w};
 }
 
+// One colour phase, in place: thread = 8-site group, its four sites of colour c (offset P = (c + y +
+// z) & 1 inside the group).  Bound by its own latency (one round of loads) while the lattice is small, by
+// memory above: the row and plane neighbours come from cache, so a phase reads the spins and the
+// couplings once and writes the spins.  Consecutive workgroups of an XCD take consecutive groups, whose
+// neighbour rows are then in its L2.  P differs between the rows of a wavefront: halves are selected, the
+// arithmetic is not branched over.  us a sweep (two phases), with a copy of the couplings by colour, twice
+// their size, and a branch on P before: 2D L = 64 8.6 -> 7.3, 1024 16.0 -> 9.1, 2048 54 -> 25; 3D L = 64 13.2 ->
+// 8.1, 160 61 -> 32, 256 251 -> 100.
 template <int D>
-__global__ __launch_bounds__(256) void k_msc_phase(uint32_t* __restrict__ S, const uint32_t* __restrict__ J6,
+__global__ __launch_bounds__(256) void k_msc_phase(uint32_t* __restrict__ S, const uint32_t* __restrict__ J,
                                                    MscArgs a) {
   const uint32_t L = a.L, GPR = L / 8;
   const PhiloxUniform U = philox_uniform(a.t, a.p0, 4u + a.colour, a.keys);
-  for (uint64_t g = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; g < a.N / 8;
-       g += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t rowi = g / GPR;
-    const uint32_t x0 = (uint32_t)(g - rowi * GPR) * 8u;
-    const uint32_t y = (uint32_t)(rowi % L), z = (D == 3) ? (uint32_t)(rowi / L) : 0u;
+  const uint64_t row = L, plane = (uint64_t)L * L, N = a.N;
+  for (uint64_t g = xcd_tile() * (uint64_t)256 + threadIdx.x; g < N / 8; g += (uint64_t)gridDim.x * 256) {
+    const uint32_t rowi = (uint32_t)g / GPR, gx = (uint32_t)g - rowi * GPR;  // N / 8 < 2^32
+    const uint32_t z = D == 3 ? rowi / L : 0u, y = rowi - z * L;
+    const uint64_t r0 = (uint64_t)rowi * L, s0 = r0 + 8u * gx;
+    const uint64_t dym = y ? 0 - row : (L - 1) * row, dyp = y + 1 < L ? row : 0 - (L - 1) * row;
+    const uint64_t dzm = z ? 0 - plane : (L - 1) * plane, dzp = z + 1 < L ? plane : 0 - (L - 1) * plane;
+    const bool P = ((a.colour + y + z) & 1u) != 0;
+    const uint64_t sl = gx ? s0 - 1 : r0 + L - 1, sr = gx + 1 < GPR ? s0 + 8 : r0;  // left and right of the group
+    auto ld = [&](const uint32_t* p) { return *reinterpret_cast<const u32x4*>(p); };
+    const u32x4 c0 = ld(S + s0), c1 = ld(S + s0 + 4), m0 = ld(S + s0 + dym), m1 = ld(S + s0 + dym + 4),
+                p0 = ld(S + s0 + dyp), p1 = ld(S + s0 + dyp + 4);
+    const uint32_t w = S[P ? sr : sl];
+    u32x4 q0{}, q1{}, t0{}, t1{};
+    if (D == 3) {
+      q0 = ld(S + s0 + dzm);
+      q1 = ld(S + s0 + dzm + 4);
+      t0 = ld(S + s0 + dzp);
+      t1 = ld(S + s0 + dzp + 4);
+    }
+    const u32x4 x0 = ld(J + s0), x1 = ld(J + s0 + 4);
+    const uint32_t xl = J[sl];
+    const uint64_t h = N + r0 + (P ? L / 2 : 0) + 4u * gx;  // the active sites' y bonds
+    const u32x4 jy = ld(J + h), jym = ld(J + h + dym);
+    u32x4 jz{}, jzm{};
+    if (D == 3) {
+      jz = ld(J + N + h);
+      jzm = ld(J + N + h + dzm);
+    }
     uint32_t r[4];
     philox_lane((uint32_t)g, U, a.keys, r);
-    if (((a.colour + y + z) & 1u) == 0)
-      msc_group<D, 0>(S, J6, a, g * 8, x0, y, z, r);
-    else
-      msc_group<D, 1>(S, J6, a, g * 8, x0, y, z, r);
+    auto even = [](u32x4 v0, u32x4 v1) { return u32x4{v0.x, v0.z, v1.x, v1.z}; };
+    auto oddw = [](u32x4 v0, u32x4 v1) { return u32x4{v0.y, v0.w, v1.y, v1.w}; };
+    auto half = [&](u32x4 v0, u32x4 v1) { return sel4(P, oddw(v0, v1), even(v0, v1)); };
+    const u32x4 ev = even(c0, c1), od = oddw(c0, c1), jo = oddw(x0, x1);
+    // the bond to the other site of a pair is the even site's either way; the one on the other side its
+    // own (P = 1) or that of the site to its left
+    const u32x4 Nb = sel4(P, u32x4{ev.y, ev.z, ev.w, w}, u32x4{w, od.x, od.y, od.z});
+    const u32x4 jn = sel4(P, jo, u32x4{xl, jo.x, jo.y, jo.z});
+    const u32x4 n = msc_update4<D>(sel4(P, od, ev), sel4(P, ev, od), Nb, half(m0, m1), half(p0, p1), half(q0, q1),
+                                   half(t0, t1), even(x0, x1), jn, jym, jy, jzm, jz, r, a.thr);
+    const u32x4 e1 = sel4(P, ev, n), o1 = sel4(P, n, od);
+    *reinterpret_cast<u32x4*>(S + s0) = u32x4{e1.x, o1.x, e1.y, o1.y};
+    *reinterpret_cast<u32x4*>(S + s0 + 4) = u32x4{e1.z, o1.z, e1.w, o1.w};
   }
 }
 
@@ -277,9 +282,6 @@ __global__ __launch_bounds__(256) void k_msc_phase(uint32_t* __restrict__ S, con
 // on plane a-2 over the owned rows and groups, written to dst with both
 // colours; store the fetched plane; barrier.  Couplings come from HBM.
 constexpr int kMscFetch = 4;  // slice groups per thread
-// A register vector: copies of uint4 structs are lowered to memcpy and left in scratch.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ uint32_t msc_wrap2(uint32_t v, uint32_t L) {  // (v - 2) mod L, v < 2L + 2
   uint32_t w = v + L - 2u;
   if (w >= L) w -= L;
@@ -1123,20 +1125,12 @@ hipError_t launch_msc_couplings(uint32_t* J, uint64_t N, uint32_t L, uint32_t d,
   return hipGetLastError();
 }
 
-hipError_t launch_msc_bonds(const uint32_t* J, uint32_t* J6, uint32_t L, uint32_t d, uint64_t N, hipStream_t stream) {
-  if (d == 3)
-    hipLaunchKernelGGL(k_msc_bonds<3>, dim3(blocks_for(N / 4, 8192)), dim3(256), 0, stream, J, J6, L, N);
-  else
-    hipLaunchKernelGGL(k_msc_bonds<2>, dim3(blocks_for(N / 4, 8192)), dim3(256), 0, stream, J, J6, L, N);
-  return hipGetLastError();
-}
-
-hipError_t launch_msc_phase(uint32_t* S, const uint32_t* J6, const MscArgs& a, uint32_t d, hipStream_t stream) {
+hipError_t launch_msc_phase(uint32_t* S, const uint32_t* J, const MscArgs& a, uint32_t d, hipStream_t stream) {
   const unsigned blocks = blocks_for(a.N / 8, 1u << 20);
   if (d == 3)
-    hipLaunchKernelGGL(k_msc_phase<3>, dim3(blocks), dim3(256), 0, stream, S, J6, a);
+    hipLaunchKernelGGL(k_msc_phase<3>, dim3(blocks), dim3(256), 0, stream, S, J, a);
   else
-    hipLaunchKernelGGL(k_msc_phase<2>, dim3(blocks), dim3(256), 0, stream, S, J6, a);
+    hipLaunchKernelGGL(k_msc_phase<2>, dim3(blocks), dim3(256), 0, stream, S, J, a);
   return hipGetLastError();
 }
 

@@ -25,3 +25,25 @@ def test_parts_equal_streaming(L, rows, planes):
         np.testing.assert_array_equal(a.spins(system), b.spins(system))
     a.close()
     b.close()
+
+
+# odd group counts and the smallest lattice; both sides of the size above which planes are streamed
+@pytest.mark.parametrize("L,d", [(8, 2), (40, 2), (104, 2), (8, 3), (40, 3)])
+def test_phase_kernel_matches_oracle(oracle_mod, L, d):
+    cs, seed = workloads.seed(0x68), workloads.seed(0x69)
+    m, ch = spin.Msc(L, d, cs, 4, seed, 3), oracle_mod.MscChain(L, d, cs, 4, seed, 3)
+    print("phase", L, d, flush=True)
+    assert m.kernel == 0
+    for beta in (0.7, float("inf")):
+        for x, y in zip(m.sweep_record(2, beta, 1), ch.sweep(2, beta, every=1)):
+            np.testing.assert_array_equal(x, y)
+    for system in (0, 31):
+        np.testing.assert_array_equal(m.spins(system), ch.spins[system])
+    m.close()
+
+
+def test_streaming_beyond_the_cache():
+    for L, d, kernel in ((2048, 2, 0), (4096, 2, 1), (200, 3, 0), (256, 3, 2)):
+        m = spin.Msc(L, d, 1, 0, 1)
+        assert m.kernel == kernel
+        m.close()

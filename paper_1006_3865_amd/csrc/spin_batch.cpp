@@ -255,7 +255,7 @@ static void free_member(spin_batch* b, Member& mb) {
   if (mb.big) spin_free(mb.big);
   if (mb.spins) b->slab.put(mb.spins, mb.N);
   if (mb.jn) {
-    const size_t jbytes = (size_t)mb.d * mb.N / 2;
+    const size_t jbytes = (size_t)mb.N / 2;
     if (mb.jn_shared) {
       auto it = b->shared.find(mb.key);
       if (it != b->shared.end() && --it->second.refs == 0) {
@@ -411,16 +411,15 @@ static int init_member(spin_batch* b, int slot, const spin_desc& s, bool upload)
   hipError_t e = launch_init_spins(lat, b->stream);
   if (e != hipSuccess) return hfail(e, "hot start");
   if (s.model == SPIN_EA_PMJ) {
-    const uint64_t nbytes = (uint64_t)s.d * mb.N;
     if (!s.couplings) {
       mb.key = std::make_tuple(s.coupling_seed, s.realisation, s.L, s.d);
       auto it = b->shared.find(mb.key);
       if (it == b->shared.end()) {
-        uint32_t* jn = (uint32_t*)b->slab.get(nbytes / 2);
+        uint32_t* jn = (uint32_t*)b->slab.get(mb.N / 2);
         if (!jn) return bfail(SPIN_ENOMEM, "coupling allocation failed");
         e = launch_couplings_nibble(jn, mb.N, (uint32_t)s.d, s.coupling_seed, s.realisation, b->stream);
         if (e != hipSuccess) {
-          b->slab.put(jn, nbytes / 2);
+          b->slab.put(jn, mb.N / 2);
           return hfail(e, "coupling generation");
         }
         it = b->shared.emplace(mb.key, Shared{jn, 0}).first;
@@ -429,12 +428,13 @@ static int init_member(spin_batch* b, int slot, const spin_desc& s, bool upload)
       mb.jn = it->second.jn;
       mb.jn_shared = true;
     } else {
-      mb.jn = (uint32_t*)b->slab.get(nbytes / 2);
+      mb.jn = (uint32_t*)b->slab.get(mb.N / 2);
       if (!mb.jn) return bfail(SPIN_ENOMEM, "coupling allocation failed");
+      const uint64_t nbytes = (uint64_t)s.d * mb.N;
       int8_t* tmp;
       if (!dmalloc(&tmp, nbytes)) return bfail(SPIN_ENOMEM, "coupling staging allocation failed");
       e = hipMemcpyAsync(tmp, s.couplings, nbytes, hipMemcpyHostToDevice, b->stream);
-      if (e == hipSuccess) e = launch_pack_nibbles(tmp, mb.jn, nbytes, b->stream);
+      if (e == hipSuccess) e = launch_pack_nibbles(tmp, mb.jn, mb.N, (uint32_t)s.d, b->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
       device_free(tmp);
       if (e != hipSuccess) return hfail(e, "coupling upload");

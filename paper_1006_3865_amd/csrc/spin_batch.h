@@ -72,8 +72,9 @@ hipError_t launch_batch_single(BatchSingle* blk, const BatchLattice& lat, const 
 hipError_t launch_batch(uint32_t d, bool ea, uint32_t nt, BatchLattice* lats, const BatchCall* calls,
                         const uint32_t* order, uint32_t ntasks, uint32_t* counter, size_t lds_bytes,
                         uint32_t grid, hipStream_t stream);
+// Coupling words (spin_nibble.h), N / 8: generated, or packed from d * N int8 couplings [dir][site].
 hipError_t launch_couplings_nibble(uint32_t* Jn, uint64_t N, uint32_t d, uint64_t cseed,
                                    uint32_t realisation, hipStream_t stream);
-hipError_t launch_pack_nibbles(const int8_t* src, uint32_t* dst, uint64_t nbytes, hipStream_t stream);
+hipError_t launch_pack_nibbles(const int8_t* src, uint32_t* dst, uint64_t N, uint32_t d, hipStream_t stream);
 
 }  // namespace spin

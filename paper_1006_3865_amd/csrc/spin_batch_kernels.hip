@@ -51,29 +51,32 @@ __device__ __forceinline__ void philox_lane_unfolded(uint32_t c0, const PhiloxUn
 
 // ---------------------------------------------------------------- couplings
 
-// Generate couplings (Philox rule of spin.h) directly in nibble form:
-// word w of direction dir holds J[dir][8w .. 8w+7].
+// Generate couplings (Philox rule of spin.h) directly as coupling words.
 __global__ void k_couplings_nibble(uint32_t* __restrict__ Jn, uint32_t nwords, uint32_t d,
                                    RoundKeys K, uint32_t realisation) {
-  for (uint32_t dir = 0; dir < d; ++dir)
-    for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < nwords; w += gridDim.x * blockDim.x) {
-      uint32_t v = 0;
+  for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < nwords; w += gridDim.x * blockDim.x) {
+    uint32_t v = 0;
+    for (uint32_t dir = 0; dir < d; ++dir)
 #pragma unroll
       for (uint32_t h = 0; h < 2; ++h) {
         uint32_t r[4];
         philox(2 * w + h, dir, realisation, 3u, K, r);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v |= ((r[j] >> 31) ? 0xFu : 0x1u) << (4 * (4 * h + j));
+        for (int j = 0; j < 4; ++j) v |= (r[j] >> 31) << (4 * (4 * h + j) + 1 + dir);
       }
-      Jn[(size_t)dir * nwords + w] = v;
-    }
+    Jn[w] = v;
+  }
 }
 
-// Pack int8 couplings [dir][site] into nibble words.
-__global__ void k_pack_nibbles(const int8_t* __restrict__ src, uint32_t* __restrict__ dst, uint32_t nwords) {
+// Pack int8 couplings [dir][site] (N sites, a multiple of 8) into coupling words.
+__global__ void k_pack_nibbles(const int8_t* __restrict__ src, uint32_t* __restrict__ dst, uint32_t nwords, uint32_t d) {
   for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < nwords; w += gridDim.x * blockDim.x) {
-    const uint2 b = reinterpret_cast<const uint2*>(src)[w];
-    dst[w] = pack_nibbles(b.x, b.y);
+    uint32_t v = 0;
+    for (uint32_t dir = 0; dir < d; ++dir) {
+      const uint2 b = reinterpret_cast<const uint2*>(src)[(size_t)dir * nwords + w];
+      v |= coupling_bits(b.x, b.y, (int)dir);
+    }
+    dst[w] = v;
   }
 }
 
@@ -86,10 +89,10 @@ hipError_t launch_couplings_nibble(uint32_t* Jn, uint64_t N, uint32_t d, uint64_
   return hipGetLastError();
 }
 
-hipError_t launch_pack_nibbles(const int8_t* src, uint32_t* dst, uint64_t nbytes, hipStream_t stream) {
-  const uint32_t nwords = (uint32_t)(nbytes / 8);
+hipError_t launch_pack_nibbles(const int8_t* src, uint32_t* dst, uint64_t N, uint32_t d, hipStream_t stream) {
+  const uint32_t nwords = (uint32_t)(N / 8);
   const uint32_t blocks = (nwords + 255) / 256 < 4096 ? (nwords + 255) / 256 : 4096;
-  hipLaunchKernelGGL(k_pack_nibbles, dim3(blocks ? blocks : 1), dim3(256), 0, stream, src, dst, nwords);
+  hipLaunchKernelGGL(k_pack_nibbles, dim3(blocks ? blocks : 1), dim3(256), 0, stream, src, dst, nwords, d);
   return hipGetLastError();
 }
 
@@ -105,9 +108,6 @@ template <int D, bool EA, int NT>
 __device__ void batch_record(const BatchLattice& B, const BatchCall& Cl, const uint32_t* sp, int64_t* red,
                              uint32_t rec) {
   const uint32_t L = B.L, LG = L / 8, R = (D == 3) ? L * L : L, NW = R * LG, PS = L * LG;
-  const uint32_t* Jx = B.Jn;
-  const uint32_t* Jy = EA ? B.Jn + NW : nullptr;
-  const uint32_t* Jz = EA ? B.Jn + 2 * NW : nullptr;
   int64_t unsat = 0, neg = 0;
   for (uint32_t w = threadIdx.x; w < NW; w += NT) {
     const uint32_t c = sp[w];
@@ -116,11 +116,12 @@ __device__ void batch_record(const BatchLattice& B, const BatchCall& Cl, const u
     const uint32_t rwd = sp[(x + 1 < LG) ? w + 1 : w - (LG - 1)];
     const uint32_t Rx = __builtin_amdgcn_alignbit(rwd, c, 4);
     const uint32_t yp = sp[(y + 1 < L) ? w + LG : w - (L - 1) * LG];
-    unsat += __popc(xor3(c, Rx, EA ? Jx[w] : 0u) & 0x88888888u);
-    unsat += __popc(xor3(c, yp, EA ? Jy[w] : 0u) & 0x88888888u);
+    const uint32_t j = EA ? B.Jn[w] : 0u;
+    unsat += __popc(xor3(c, Rx, j) & 0x22222222u);
+    unsat += __popc(xor3(c, yp, j) & 0x44444444u);
     if (D == 3) {
       const uint32_t zp = sp[(z + 1 < L) ? w + PS : w - (L - 1) * PS];
-      unsat += __popc(xor3(c, zp, EA ? Jz[w] : 0u) & 0x88888888u);
+      unsat += __popc(xor3(c, zp, j) & 0x88888888u);
     }
   }
   const int64_t su = block_sum<NT>(unsat, red);
@@ -199,7 +200,7 @@ __device__ __forceinline__ void batch_colour(uint32_t* sp, const uint32_t* bound
     const uint32_t wym = w + (YFIX ? ymo : (y ? 0u - LG : g.ym_wrap));
     const uint32_t wyp = w + (YFIX ? ypo : ((y + 1 < L) ? LG : 0u - g.ym_wrap));
     uint32_t nb[2 * D - 2];
-    uint32_t jn[2 * D];
+    uint32_t jn[D + 1];
     nb[0] = sp[wym];
     nb[1] = sp[wyp];
     uint32_t wzm = 0;
@@ -213,16 +214,10 @@ __device__ __forceinline__ void batch_colour(uint32_t* sp, const uint32_t* bound
       nb[3] = sp[wzp];
     }
     if (EA) {
-      const uint32_t jx = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * w, 0, 0);
-      const uint32_t jxl = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
-      jn[0] = __builtin_amdgcn_alignbit(jx, jxl, 28);  // bond (x-1, x)
-      jn[1] = jx;                                      // bond (x, x+1)
-      jn[2] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wym, 4u * NW, 0);
-      jn[3] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * w, 4u * NW, 0);
-      if (D == 3) {
-        jn[4] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wzm, 8u * NW, 0);
-        jn[5] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * w, 8u * NW, 0);
-      }
+      jn[0] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
+      jn[1] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * w, 0, 0);
+      jn[2] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wym, 0, 0);
+      if (D == 3) jn[D] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wzm, 0, 0);
     }
     const uint32_t S = nib_unsat<D, EA>(c, lw, rw, nb, jn);
     uint32_t rnd[4];
@@ -279,7 +274,7 @@ __device__ __forceinline__ void batch_colour2(uint32_t* sp, const uint32_t* boun
       nbp[2] = *reinterpret_cast<const uint2*>(sp + wzm);
       nbp[3] = *reinterpret_cast<const uint2*>(sp + wzp);
     }
-    uint32_t nb0[2 * D - 2], nb1[2 * D - 2], jn0[2 * D], jn1[2 * D];
+    uint32_t nb0[2 * D - 2], nb1[2 * D - 2], jn0[D + 1], jn1[D + 1];
 #pragma unroll
     for (int k = 0; k < 2 * D - 2; ++k) {
       nb0[k] = nbp[k].x;
@@ -287,25 +282,17 @@ __device__ __forceinline__ void batch_colour2(uint32_t* sp, const uint32_t* boun
     }
     if (EA) {
       typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-      const u2v jx = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * w, 0, 0);
-      const uint32_t jxl = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
-      const u2v jy = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * w, 4u * NW, 0);
-      const u2v jym = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wym, 4u * NW, 0);
-      jn0[0] = __builtin_amdgcn_alignbit(jx.x, jxl, 28);   // bond (x-1, x)
-      jn0[1] = jx.x;                                       // bond (x, x+1)
-      jn1[0] = __builtin_amdgcn_alignbit(jx.y, jx.x, 28);
-      jn1[1] = jx.y;
+      const u2v j = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * w, 0, 0);
+      const u2v jym = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wym, 0, 0);
+      jn0[0] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
+      jn0[1] = jn1[0] = j.x;
+      jn1[1] = j.y;
       jn0[2] = jym.x;
-      jn0[3] = jy.x;
       jn1[2] = jym.y;
-      jn1[3] = jy.y;
       if (D == 3) {
-        const u2v jz = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * w, 8u * NW, 0);
-        const u2v jzm = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wzm, 8u * NW, 0);
-        jn0[4] = jzm.x;
-        jn0[5] = jz.x;
-        jn1[4] = jzm.y;
-        jn1[5] = jz.y;
+        const u2v jzm = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wzm, 0, 0);
+        jn0[D] = jzm.x;
+        jn1[D] = jzm.y;
       }
     }
     const uint32_t S0 = nib_unsat<D, EA>(c.x, lw, c.y, nb0, jn0);
@@ -372,9 +359,9 @@ __device__ __forceinline__ void batch_sweeps(const BatchLattice& B, const BatchC
   }
   const bool active2 = pair && tid < g2.RI * (g.LG / 2);
   const bool yfix2 = g2.dy == 0;
-  // couplings by buffer loads: one descriptor over the d arrays of NW words, byte offsets per lane
+  // couplings by buffer loads: one descriptor over the NW words, byte offsets per lane
   const __amdgpu_buffer_rsrc_t rj =
-      __builtin_amdgcn_make_buffer_rsrc((void*)B.Jn, 0, (int)(4u * D * g.NW), 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc((void*)B.Jn, 0, (int)(4u * g.NW), 0x00020000);
   const uint32_t nev = NEVER ? Cl.never4 : 0u;
   uint32_t rec = 0;
   for (uint32_t i = 0; i < Cl.n; ++i) {

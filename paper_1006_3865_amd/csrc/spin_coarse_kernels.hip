@@ -145,7 +145,6 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
   const uint32_t L = a.L, GPR = L / 8;
   const uint32_t first = xcd_tile() * S::TPW;  // neighbouring tiles share the lines of their rows: one L2
   gu32* Jn = as_global(Jraw);
-  const uint32_t NW = (D == 3) ? L * L * GPR : L * GPR;  // words of one direction of couplings
   // this thread's unit: group cw of row ry, plane rz of tile `slot` (a tile past the last one repeats
   // that: loaded, updated, not stored)
   const uint32_t slot = S::TPW > 1 ? tid / S::U : 0u, u = tid - slot * S::U;
@@ -157,13 +156,10 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
   const uint32_t at = base + slot * S::TB + (D == 3 ? (rz + 1u) * PS : 0u) + (ry + 1u) * RS + 4u * (cw + 1u);
   const bool odd = ((ry + rz) & 1u) != 0;  // colour-0 sites of the row are its odd x (tile edges are even)
   uint2 sp[S::NL + 1];
-  uint32_t jw[S::NL + 1][EA ? D : 1];
+  uint32_t jw[S::NL + 1];
   auto load = [&](uint32_t n, uint32_t g) {
     sp[n] = reinterpret_cast<const uint2*>(spins)[g];
-    if (EA) {
-#pragma unroll
-      for (int dir = 0; dir < D; ++dir) jw[n][dir] = Jn[dir * NW + g];
-    }
+    if (EA) jw[n] = Jn[g];
   };
   if (S::OWN) load(S::NL, w);
 #pragma unroll
@@ -193,13 +189,8 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
     lds_store32(o, po ? h.y : h.x);
     lds_store32(o + S::PB, po ? h.x : h.y);
     if (EA) {
-      // nibble j of a word is site j's coupling (0x1 or 0xF): its even and its odd nibbles are the two planes' bytes
-      uint32_t je = jw[n][0] & kCoarseNeg, jo = (jw[n][0] >> 4) & kCoarseNeg;
-#pragma unroll
-      for (int dir = 1; dir < D; ++dir) {
-        je |= (jw[n][EA ? dir : 0] & kCoarseNeg) << dir;
-        jo |= ((jw[n][EA ? dir : 0] >> 4) & kCoarseNeg) << dir;
-      }
+      // nibble j of a word has site j's couplings: its even and its odd nibbles are the two planes' bytes
+      const uint32_t je = jw[n] & (7u * kCoarseNeg), jo = (jw[n] >> 4) & (7u * kCoarseNeg);
       lds_store32(o + 2u * S::PB, po ? jo : je);
       lds_store32(o + 3u * S::PB, po ? je : jo);
     }

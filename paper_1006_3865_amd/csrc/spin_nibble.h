@@ -4,9 +4,13 @@
 //
 // Site 8w+j is nibble j of word w: +1 = 0x1, -1 = 0xF (the low nibble of the
 // int8 value), so bits 1..3 of a nibble carry the sign.  (a ^ b) & 0x2 per
-// nibble marks an unsatisfied bond (with a coupling nibble, +1 = 0x1 and
-// -1 = 0xF, in the XOR for the +-J glass), the sum over the 2d neighbours is
-// 2u per nibble (u <= 6), and a flip XORs the nibble with 0xE.
+// nibble marks an unsatisfied bond (with the coupling's sign in the XOR for the
+// +-J glass), the sum over the 2d neighbours is 2u per nibble (u <= 6), and
+// a flip XORs the nibble with 0xE.
+//
+// Couplings of 8 sites are one word as well, a nibble per site whose bits 1, 2
+// and 3 are set where the bond to the next site in x, y and z is -1: a third
+// of the bytes of a word per direction.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -40,18 +44,25 @@ __device__ __forceinline__ void unpack_nibbles(uint32_t w, uint32_t& lo, uint32_
   hi = nibbles_to_bytes(w >> 16);
 }
 
-// Unsatisfied-bond count (2u per nibble) of word c with neighbour words.
+// The coupling bits of direction dir (0, 1, 2) from its 8 int8 couplings (0x01 / 0xFF).
+__device__ __forceinline__ uint32_t coupling_bits(uint32_t lo, uint32_t hi, int dir) {
+  return (pack_nibbles(lo, hi) & 0x22222222u) << dir;
+}
+
+// Unsatisfied-bond count (2u per nibble) of word c with neighbour words; j (EA): the coupling words of
+// the word on the left, of c, and of the words at y-1 and (3D) z-1.
 template <int D, bool EA>
 __device__ __forceinline__ uint32_t nib_unsat(uint32_t c, uint32_t lw, uint32_t rw, const uint32_t (&nb)[2 * D - 2],
-                                              const uint32_t (&jn)[2 * D]) {
+                                              const uint32_t (&j)[D + 1]) {
   constexpr uint32_t m = 0x22222222u;
   const uint32_t Lx = __builtin_amdgcn_alignbit(c, lw, 28);  // site x-1 of each nibble
   const uint32_t Rx = __builtin_amdgcn_alignbit(rw, c, 4);   // site x+1
   uint32_t S;
   if (EA) {
-    S = (xor3(c, Lx, jn[0]) & m) + (xor3(c, Rx, jn[1]) & m);
-#pragma unroll
-    for (int k = 0; k < 2 * D - 2; ++k) S += xor3(c, nb[k], jn[2 + k]) & m;
+    S = (xor3(c, Lx, __builtin_amdgcn_alignbit(j[1], j[0], 28)) & m) + (xor3(c, Rx, j[1]) & m);
+    // y on bit 2, where two bonds still fit the nibble
+    S += ((xor3(c, nb[0], j[2]) & (m << 1)) + (xor3(c, nb[1], j[1]) & (m << 1))) >> 1;
+    if (D == 3) S += (xor3(c, nb[2 * D - 4], j[D] >> 2) & m) + (xor3(c, nb[2 * D - 3], j[1] >> 2) & m);
   } else {
     S = ((c ^ Lx) & m) + ((c ^ Rx) & m);
 #pragma unroll

@@ -547,10 +547,9 @@ static int check_beta(double beta) {
 static int ensure_jn(spin_lattice* h, const CallScratch* fx = nullptr) {
   if (h->model != SPIN_EA_PMJ || h->jn) return SPIN_OK;
   if (fx) return fail(SPIN_ESTATE, "the packed couplings of this lattice are not allocated yet");
-  const uint64_t nbytes = (uint64_t)h->d * h->N;
-  h->jn = (uint32_t*)h->mem.get(nbytes / 2);
+  h->jn = (uint32_t*)h->mem.get(h->N / 2);
   if (!h->jn) return fail(SPIN_ENOMEM, "allocation of the packed couplings failed");
-  hipError_t e = launch_pack_nibbles(h->J, h->jn, nbytes, h->stream);
+  hipError_t e = launch_pack_nibbles(h->J, h->jn, h->N, (uint32_t)h->d, h->stream);
   if (e != hipSuccess) return hip_fail(e, "coupling packing launch");
   return SPIN_OK;
 }

@@ -107,27 +107,16 @@ __device__ __forceinline__ void sg_store(uint32_t* slot, const StreamArgs& a, ui
   }
 }
 
-// Couplings of the 2d bonds of word w (raw words: x at w and its left
-// neighbour word, y at w and the row below, z at w and the plane below).
+// Coupling words (spin_nibble.h) of word w: of the word left of it, its own, and those of the row below
+// and (3D) the plane below.
 template <int D>
-__device__ __forceinline__ void sg_jload(gu32* Jn, uint32_t NW, uint32_t w, uint32_t g, uint32_t y, uint32_t z,
-                                         const StreamArgs& a, uint32_t (&j)[2 * D]) {
+__device__ __forceinline__ void sg_jload(gu32* Jn, uint32_t w, uint32_t g, uint32_t y, uint32_t z,
+                                         const StreamArgs& a, uint32_t (&j)[D + 1]) {
   const uint32_t GPR = a.GPR, L = a.L;
-  const uint32_t wl = g ? w - 1u : w + GPR - 1u;
-  j[0] = ldg_word(Jn, wl);
+  j[0] = ldg_word(Jn, g ? w - 1u : w + GPR - 1u);
   j[1] = ldg_word(Jn, w);
-  if (D == 3) {
-    const uint32_t wym = y ? w - GPR : w + (L - 1u) * GPR;
-    const uint32_t wzm = z ? w - L * GPR : w + (L - 1u) * L * GPR;
-    j[2] = ldg_word(Jn, NW + wym);
-    j[3] = ldg_word(Jn, NW + w);
-    j[4] = ldg_word(Jn, 2 * NW + wzm);
-    j[5] = ldg_word(Jn, 2 * NW + w);
-  } else {
-    const uint32_t wym = z ? w - GPR : w + (L - 1u) * GPR;
-    j[2] = ldg_word(Jn, NW + wym);
-    j[3] = ldg_word(Jn, NW + w);
-  }
+  j[2] = ldg_word(Jn, (D == 3 ? y : z) ? w - GPR : w + (L - 1u) * GPR);
+  if (D == 3) j[D] = ldg_word(Jn, z ? w - L * GPR : w + (L - 1u) * L * GPR);
 }
 
 // Update the colour-C nibbles of word g of slice row r (slots pm, pc, pp hold
@@ -137,7 +126,7 @@ template <int D, bool EA, bool NEVER, uint32_t C>
 __device__ __forceinline__ uint32_t sg_unit(const uint32_t* pm, const uint32_t* pc, const uint32_t* pp, uint32_t r,
                                             uint32_t g, uint32_t y, uint32_t z, uint32_t w, const StreamArgs& a,
                                             const PhiloxUniform& U, const uint32_t* bound, uint32_t RW,
-                                            const uint32_t (&jr)[2 * D]) {
+                                            const uint32_t (&jr)[D + 1]) {
   const uint32_t o = r * RW + 1 + g;
   const uint32_t c = pc[o];
   const uint32_t lw = pc[o - 1], rw = pc[o + 1];
@@ -151,18 +140,7 @@ __device__ __forceinline__ uint32_t sg_unit(const uint32_t* pm, const uint32_t* 
     nb[0] = pm[o];
     nb[1] = pp[o];
   }
-  uint32_t jn[2 * D];
-  if (EA) {
-    jn[0] = __builtin_amdgcn_alignbit(jr[1], jr[0], 28);  // bond (x-1, x) of each site
-    jn[1] = jr[1];
-    jn[2] = jr[2];
-    jn[3] = jr[3];
-    if (D == 3) {
-      jn[4] = jr[4];
-      jn[5] = jr[5];
-    }
-  }
-  const uint32_t S = nib_unsat<D, EA>(c, lw, rw, nb, jn);
+  const uint32_t S = nib_unsat<D, EA>(c, lw, rw, nb, jr);
   uint32_t rnd[4];
   philox_lane(w, U, a.keys, rnd);
   const uint32_t p = (C + y + z) & 1u;
@@ -176,7 +154,7 @@ __device__ __forceinline__ uint32_t sg_unit(const uint32_t* pm, const uint32_t* 
 template <int D, bool EA, bool NEVER, int NT, uint32_t C>
 __device__ __forceinline__ void sg_units(const uint32_t* pm, uint32_t* pc, const uint32_t* pp, uint32_t n, uint32_t y0,
                                          uint32_t z, const StreamArgs& a, const PhiloxUniform& U,
-                                         const uint32_t* bound, uint32_t RW, gu32* Jn, uint32_t NW,
+                                         const uint32_t* bound, uint32_t RW, gu32* Jn,
                                          int8_t* __restrict__ dst) {
   const uint32_t GPR = a.GPR, L = a.L;
   constexpr uint32_t RB0 = (D == 3) ? (C == 0 ? 1u : 2u) : 0u;  // first slice row
@@ -188,8 +166,8 @@ __device__ __forceinline__ void sg_units(const uint32_t* pm, uint32_t* pc, const
     return C == 0 ? wrap_sub2(y0 + rr, L) : y0 + rr - 2u;
   };
   auto word = [&](uint32_t y, uint32_t gg) -> uint32_t { return (D == 3) ? (z * L + y) * GPR + gg : z * GPR + gg; };
-  uint32_t jc[2 * D] = {}, jx[2 * D] = {};
-  if (EA && threadIdx.x < n) sg_jload<D>(Jn, NW, word(ycoord(r + RB0), g), g, ycoord(r + RB0), z, a, jc);
+  uint32_t jc[D + 1] = {}, jx[D + 1] = {};
+  if (EA && threadIdx.x < n) sg_jload<D>(Jn, word(ycoord(r + RB0), g), g, ycoord(r + RB0), z, a, jc);
   for (uint32_t u = threadIdx.x; u < n; u += NT) {
     const uint32_t rr = r + RB0;
     const uint32_t y = ycoord(rr);
@@ -199,7 +177,7 @@ __device__ __forceinline__ void sg_units(const uint32_t* pm, uint32_t* pc, const
       gn -= GPR;
       rn += 1;
     }
-    if (EA && u + NT < n) sg_jload<D>(Jn, NW, word(ycoord(rn + RB0), gn), gn, ycoord(rn + RB0), z, a, jx);
+    if (EA && u + NT < n) sg_jload<D>(Jn, word(ycoord(rn + RB0), gn), gn, ycoord(rn + RB0), z, a, jx);
     const uint32_t v = sg_unit<D, EA, NEVER, C>(pm, pc, pp, rr, g, y, z, w, a, U, bound, RW, jc);
     if (C == 0) {
       uint32_t* row = pc + rr * RW;
@@ -213,7 +191,7 @@ __device__ __forceinline__ void sg_units(const uint32_t* pm, uint32_t* pc, const
     }
     if (EA) {
 #pragma unroll
-      for (int k = 0; k < 2 * D; ++k) jc[k] = jx[k];
+      for (int k = 0; k < D + 1; ++k) jc[k] = jx[k];
     }
     r = rn;
     g = gn;
@@ -234,30 +212,22 @@ __device__ __forceinline__ uint2 ldg_pair(gu32* base, uint32_t i) {  // words i,
   return make_uint2(v.x, v.y);
 }
 
-// Couplings of the pair at words w, w+1: x at the pair and the word left of
-// it, y at the pair and the row below, z at the pair and the plane below.
+// The same of the pair at words w, w+1: the word left of it, then pairs.
 template <int D>
-__device__ __forceinline__ void sg_jload2(gu32* Jn, uint32_t NW, uint32_t w, uint32_t g, uint32_t y, uint32_t z,
-                                          const StreamArgs& a, uint32_t (&j)[4 * D + 1]) {
+__device__ __forceinline__ void sg_jload2(gu32* Jn, uint32_t w, uint32_t g, uint32_t y, uint32_t z,
+                                          const StreamArgs& a, uint32_t (&j)[2 * D + 1]) {
   const uint32_t GPR = a.GPR, L = a.L;
-  const uint32_t wl = g ? w - 1u : w + GPR - 1u;
-  j[0] = ldg_word(Jn, wl);
-  const uint2 jx = ldg_pair(Jn, w);
-  j[1] = jx.x;
-  j[2] = jx.y;
-  const uint32_t wym = (D == 3) ? (y ? w - GPR : w + (L - 1u) * GPR) : (z ? w - GPR : w + (L - 1u) * GPR);
-  const uint2 jym = ldg_pair(Jn, NW + wym), jy = ldg_pair(Jn, NW + w);
-  j[3] = jym.x;
-  j[4] = jym.y;
-  j[5] = jy.x;
-  j[6] = jy.y;
+  j[0] = ldg_word(Jn, g ? w - 1u : w + GPR - 1u);
+  const uint2 own = ldg_pair(Jn, w);
+  j[1] = own.x;
+  j[2] = own.y;
+  const uint2 ym = ldg_pair(Jn, (D == 3 ? y : z) ? w - GPR : w + (L - 1u) * GPR);
+  j[3] = ym.x;
+  j[4] = ym.y;
   if (D == 3) {
-    const uint32_t wzm = z ? w - L * GPR : w + (L - 1u) * L * GPR;
-    const uint2 jzm = ldg_pair(Jn, 2 * NW + wzm), jz = ldg_pair(Jn, 2 * NW + w);
-    j[7] = jzm.x;
-    j[8] = jzm.y;
-    j[9] = jz.x;
-    j[10] = jz.y;
+    const uint2 zm = ldg_pair(Jn, z ? w - L * GPR : w + (L - 1u) * L * GPR);
+    j[2 * D - 1] = zm.x;
+    j[2 * D] = zm.y;
   }
 }
 
@@ -267,7 +237,7 @@ template <int D, bool EA, bool NEVER, uint32_t C>
 __device__ __forceinline__ uint2 sg_unit2(const uint32_t* pm, const uint32_t* pc, const uint32_t* pp, uint32_t r,
                                           uint32_t g, uint32_t y, uint32_t z, uint32_t w, const StreamArgs& a,
                                           const PhiloxUniform& U, const uint32_t* bound, uint32_t RW,
-                                          const uint32_t (&jr)[4 * D + 1]) {
+                                          const uint32_t (&jr)[2 * D + 1]) {
   const uint32_t o = r * RW + 2 + g;
   const uint2 c = *reinterpret_cast<const uint2*>(pc + o);
   const uint32_t lw = pc[o - 1], rw = pc[o + 2];
@@ -281,26 +251,20 @@ __device__ __forceinline__ uint2 sg_unit2(const uint32_t* pm, const uint32_t* pc
     nbp[0] = *reinterpret_cast<const uint2*>(pm + o);
     nbp[1] = *reinterpret_cast<const uint2*>(pp + o);
   }
-  uint32_t nb0[2 * D - 2], nb1[2 * D - 2], jn0[2 * D], jn1[2 * D];
+  uint32_t nb0[2 * D - 2], nb1[2 * D - 2], jn0[D + 1], jn1[D + 1];
 #pragma unroll
   for (int k = 0; k < 2 * D - 2; ++k) {
     nb0[k] = nbp[k].x;
     nb1[k] = nbp[k].y;
   }
   if (EA) {
-    jn0[0] = __builtin_amdgcn_alignbit(jr[1], jr[0], 28);  // bond (x-1, x) of each site
-    jn0[1] = jr[1];
-    jn1[0] = __builtin_amdgcn_alignbit(jr[2], jr[1], 28);
+    jn0[0] = jr[0];
+    jn0[1] = jn1[0] = jr[1];
     jn1[1] = jr[2];
-    jn0[2] = jr[3];
-    jn1[2] = jr[4];
-    jn0[3] = jr[5];
-    jn1[3] = jr[6];
-    if (D == 3) {
-      jn0[4] = jr[7];
-      jn1[4] = jr[8];
-      jn0[5] = jr[9];
-      jn1[5] = jr[10];
+#pragma unroll
+    for (int k = 2; k <= D; ++k) {
+      jn0[k] = jr[2 * k - 1];
+      jn1[k] = jr[2 * k];
     }
   }
   const uint32_t S0 = nib_unsat<D, EA>(c.x, lw, c.y, nb0, jn0);
@@ -318,7 +282,7 @@ __device__ __forceinline__ uint2 sg_unit2(const uint32_t* pm, const uint32_t* pc
 template <int D, bool EA, bool NEVER, int NT, uint32_t C>
 __device__ __forceinline__ void sg_units2(const uint32_t* pm, uint32_t* pc, const uint32_t* pp, uint32_t n,
                                           uint32_t y0, uint32_t z, const StreamArgs& a, const PhiloxUniform& U,
-                                          const uint32_t* bound, uint32_t RW, gu32* Jn, uint32_t NW,
+                                          const uint32_t* bound, uint32_t RW, gu32* Jn,
                                           int8_t* __restrict__ dst) {
   const uint32_t GPR = a.GPR, L = a.L, PG = GPR / 2;
   constexpr uint32_t RB0 = (D == 3) ? (C == 0 ? 1u : 2u) : 0u;  // first slice row
@@ -329,8 +293,8 @@ __device__ __forceinline__ void sg_units2(const uint32_t* pm, uint32_t* pc, cons
     return C == 0 ? wrap_sub2(y0 + rr, L) : y0 + rr - 2u;
   };
   auto word = [&](uint32_t y, uint32_t gg) -> uint32_t { return (D == 3) ? (z * L + y) * GPR + gg : z * GPR + gg; };
-  uint32_t jc[4 * D + 1] = {}, jx[4 * D + 1] = {};
-  if (EA && threadIdx.x < n) sg_jload2<D>(Jn, NW, word(ycoord(r + RB0), 2 * q), 2 * q, ycoord(r + RB0), z, a, jc);
+  uint32_t jc[2 * D + 1] = {}, jx[2 * D + 1] = {};
+  if (EA && threadIdx.x < n) sg_jload2<D>(Jn, word(ycoord(r + RB0), 2 * q), 2 * q, ycoord(r + RB0), z, a, jc);
   for (uint32_t u = threadIdx.x; u < n; u += NT) {
     const uint32_t rr = r + RB0, g = 2 * q;
     const uint32_t y = ycoord(rr);
@@ -340,7 +304,7 @@ __device__ __forceinline__ void sg_units2(const uint32_t* pm, uint32_t* pc, cons
       qn -= PG;
       rn += 1;
     }
-    if (EA && u + NT < n) sg_jload2<D>(Jn, NW, word(ycoord(rn + RB0), 2 * qn), 2 * qn, ycoord(rn + RB0), z, a, jx);
+    if (EA && u + NT < n) sg_jload2<D>(Jn, word(ycoord(rn + RB0), 2 * qn), 2 * qn, ycoord(rn + RB0), z, a, jx);
     const uint2 v = sg_unit2<D, EA, NEVER, C>(pm, pc, pp, rr, g, y, z, w, a, U, bound, RW, jc);
     if (C == 0) {
       uint32_t* row = pc + rr * RW;
@@ -355,7 +319,7 @@ __device__ __forceinline__ void sg_units2(const uint32_t* pm, uint32_t* pc, cons
     }
     if (EA) {
 #pragma unroll
-      for (int k = 0; k < 4 * D + 1; ++k) jc[k] = jx[k];
+      for (int k = 0; k < 2 * D + 1; ++k) jc[k] = jx[k];
     }
     r = rn;
     q = qn;
@@ -374,7 +338,6 @@ __global__ __launch_bounds__(NT) void k_streamg(const int8_t* __restrict__ src, 
   const uint32_t TY = (D == 3) ? a.TY : 1u;
   const uint32_t RP = (D == 3) ? TY + 4 : 1u;
   const uint32_t SB = RP * RW;
-  const uint32_t NW = (D == 3) ? L * L * GPR : L * GPR;
   const uint32_t y0 = (D == 3) ? blockIdx.x * TY : 0u;
   const uint32_t z0 = blockIdx.y * a.H;
   const uint32_t H = (L - z0 < a.H) ? L - z0 : a.H;
@@ -404,17 +367,17 @@ __global__ __launch_bounds__(NT) void k_streamg(const int8_t* __restrict__ src, 
     if (PAIR) {
       if (i <= H + 1)
         sg_units2<D, EA, NEVER, NT, 0>(ring + s_m1 * SB, ring + sa * SB, ring + s_p1 * SB, U0n, y0,
-                                       wrap_sub2(z0 + i + 1, L), a, U0, bound, RW, Jn, NW, dst);
+                                       wrap_sub2(z0 + i + 1, L), a, U0, bound, RW, Jn, dst);
       if (i >= 3)
         sg_units2<D, EA, NEVER, NT, 1>(ring + s_m3 * SB, ring + s_m2 * SB, ring + s_m1 * SB, U1n, y0, z0 + i - 3u,
-                                       a, U1, bound, RW, Jn, NW, dst);
+                                       a, U1, bound, RW, Jn, dst);
     } else {
       if (i <= H + 1)
         sg_units<D, EA, NEVER, NT, 0>(ring + s_m1 * SB, ring + sa * SB, ring + s_p1 * SB, U0n, y0,
-                                      wrap_sub2(z0 + i + 1, L), a, U0, bound, RW, Jn, NW, dst);
+                                      wrap_sub2(z0 + i + 1, L), a, U0, bound, RW, Jn, dst);
       if (i >= 3)
         sg_units<D, EA, NEVER, NT, 1>(ring + s_m3 * SB, ring + s_m2 * SB, ring + s_m1 * SB, U1n, y0, z0 + i - 3u, a,
-                                      U1, bound, RW, Jn, NW, dst);
+                                      U1, bound, RW, Jn, dst);
     }
     if (i <= H) sg_store<NT, OFF>(ring + s_p2 * SB, a, tot, RW, nxt);
     __syncthreads();

@@ -177,10 +177,10 @@ bool plan_for(int d, int model, int L, Plan* out) {
   return true;
 }
 
-// Workgroups of nt threads with `lds` bytes of dynamic LDS that one CU holds.
+// Workgroups of nt threads with `lds` bytes of LDS for lattices that one CU holds.
 uint32_t max_per_cu(uint32_t nt, size_t lds) {
   const uint32_t by_threads = 2048u / nt;
-  const uint32_t by_lds = (uint32_t)((160 * 1024 - 256) / std::max<size_t>(lds, 1));
+  const uint32_t by_lds = (uint32_t)(160 * 1024 / (lds + kBatchCtl));
   return std::max<uint32_t>(1, std::min(by_threads, by_lds));
 }
 

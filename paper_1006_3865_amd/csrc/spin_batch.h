@@ -11,7 +11,9 @@
 namespace spin {
 
 // Largest dynamic LDS block of the batch kernel (spins packed 2 per byte).
-constexpr size_t kBatchMaxLds = 150 * 1024;  // plus 208 bytes of static LDS
+constexpr size_t kBatchMaxLds = 150 * 1024;  // plus kBatchCtl bytes
+// Behind the lattice in LDS: the pair table of accept bounds, then sums, then the task index.
+constexpr uint32_t kBatchRed = 400, kBatchTask = 528, kBatchCtl = 544;
 
 // Device-resident state of one lattice of a batch.
 struct BatchLattice {

@@ -16,6 +16,7 @@
 
 #include "spin_batch.h"
 #include "spin_device.h"
+#include "spin_lds.h"
 
 namespace spin {
 
@@ -173,135 +174,116 @@ __device__ __forceinline__ BatchCall uniform_call(const BatchCall& C) {
   return u;
 }
 
-// Per-thread geometry of a task: thread -> (word column xg, first row); rows
-// advance by RI = NT / LG per iteration.
+// Per-thread geometry of a task: thread -> (column xg of words or pairs of words, first row); rows
+// advance by RI per iteration.  Places and distances are in bytes, of the LDS words and of the coupling
+// words alike, so that one sum per neighbour addresses both.
 struct BatchGeo {
-  uint32_t L, LG, R, NW, PS, RI, xg, r_first, dy, dz, wl, wr, ym_wrap, zm_wrap;
+  uint32_t L, LG, R, NB, PB, RI, xg, r_first, dy, dz, wl, wr, ym_wrap;
 };
 
-// One colour phase over the thread's rows.  YFIX: RI is a multiple of L, so
-// every row the thread visits has the same y: its y-neighbour offsets are
-// fixed, and the parity of the active sites steps by dz per row.
-template <int D, bool EA, bool NEVER, bool YFIX>
-__device__ __forceinline__ void batch_colour(uint32_t* sp, const uint32_t* bound, __amdgpu_buffer_rsrc_t rj,
-                                             const BatchGeo& g, const PhiloxUniform& U, const RoundKeys& K,
-                                             uint32_t colour, uint32_t nev) {
-  const uint32_t L = g.L, LG = g.LG, PS = g.PS, NW = g.NW;
-  uint32_t y = g.r_first % L, z = g.r_first / L;
-  const uint32_t ymo = y ? 0u - LG : g.ym_wrap;               // used when YFIX
-  const uint32_t ypo = (y + 1 < L) ? LG : 0u - g.ym_wrap;
-  uint32_t p = (colour + y + z) & 1u;
-  const uint32_t pstep = g.dz & 1u;
-  const uint32_t wstep = g.RI * LG;
-  uint32_t w = g.r_first * LG + g.xg;
-  for (uint32_t row = g.r_first; row < g.R; row += g.RI, w += wstep) {
-    const uint32_t c = sp[w];
-    const uint32_t lw = sp[w + g.wl], rw = sp[w + g.wr];
-    const uint32_t wym = w + (YFIX ? ymo : (y ? 0u - LG : g.ym_wrap));
-    const uint32_t wyp = w + (YFIX ? ypo : ((y + 1 < L) ? LG : 0u - g.ym_wrap));
-    uint32_t nb[2 * D - 2];
-    uint32_t jn[D + 1];
-    nb[0] = sp[wym];
-    nb[1] = sp[wyp];
-    uint32_t wzm = 0;
-    if (D == 3) {
-      // planes z-1 and z+1, periodic: w -/+ PS wrapped into [0, NW) by an unsigned minimum (the
-      // out-of-range candidate has wrapped past 2^32 or is at least NW), no per-lane select
-      const uint32_t m = w - PS, q = w + PS;
-      wzm = __builtin_elementwise_min(m, m + NW);
-      const uint32_t wzp = __builtin_elementwise_min(q, q - NW);
-      nb[2] = sp[wzm];
-      nb[3] = sp[wzp];
-    }
-    if (EA) {
-      jn[0] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
-      jn[1] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * w, 0, 0);
-      jn[2] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wym, 0, 0);
-      if (D == 3) jn[D] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * wzm, 0, 0);
-    }
-    const uint32_t S = nib_unsat<D, EA>(c, lw, rw, nb, jn);
-    uint32_t rnd[4];
-    philox_lane_unfolded(w, U, K, rnd);
-    sp[w] = c ^ nib_flips<NEVER>(S, p, rnd, bound, nev);
-    if (YFIX) {
-      z += g.dz;
-      p ^= pstep;
-    } else {
-      y += g.dy;
-      z += g.dz;
-      if (y >= L) {
-        y -= L;
-        z += 1;
-      }
-      p = (colour + y + z) & 1u;
-    }
+// Flip mask (nib_flips) with the bounds of two sites from one 8-byte entry of the pair table at LDS address
+// table: v_dot4 turns two bytes 2u into its offset 8 (u0 + (2D + 1) u1).
+template <int D, bool NEVER>
+__device__ __forceinline__ uint32_t batch_flips(uint32_t S, uint32_t p, const uint32_t r[4], uint32_t table,
+                                                uint32_t nev) {
+  constexpr uint32_t W = 4u + 256u * 4u * (2u * D + 1u);
+  const uint32_t T = (S >> (4u * p)) & 0x0F0F0F0Fu;  // byte i: 2u of active nibble i
+  const uint2 b01 = lds_load64(__builtin_amdgcn_udot4(T, W, table, false));
+  const uint2 b23 = lds_load64(__builtin_amdgcn_udot4(T, W << 16, table, false));
+  bool a0 = r[0] <= b01.x, a1 = r[1] <= b01.y, a2 = r[2] <= b23.x, a3 = r[3] <= b23.y;
+  if (NEVER) {
+    a0 = a0 && (T & 0xFFu) >= nev;
+    a1 = a1 && __builtin_amdgcn_perm(0u, T, 0x0C0C0C01u) >= nev;
+    a2 = a2 && __builtin_amdgcn_ubfe(T, 16u, 8u) >= nev;
+    a3 = a3 && (T >> 24) >= nev;
   }
+  return (xor3(a0 ? 0xEu : 0u, a1 ? 0xE00u : 0u, a2 ? 0xE0000u : 0u) ^ (a3 ? 0xE000000u : 0u)) << (4u * p);
 }
 
-// The same phase with two adjacent words per thread (rows of an even number
-// of words): the pair is one 8-byte LDS access per neighbour row and one
-// 8-byte coupling load per direction and side, so a word costs 3 coupling
-// loads instead of 6 and 4.5 LDS reads instead of 7 (the coupling loads
-// through the vector memory path, not the ALU, set this kernel's pace).  The
-// x neighbours and the x bond between the two words come from the pair
-// itself.  g describes the pair columns: xg the pair, wl / wr the offsets of
-// the words left of the first and right of the second word.
-template <int D, bool EA, bool NEVER, bool YFIX>
-__device__ __forceinline__ void batch_colour2(uint32_t* sp, const uint32_t* bound, __amdgpu_buffer_rsrc_t rj,
-                                              const BatchGeo& g, const PhiloxUniform& U, const RoundKeys& K,
-                                              uint32_t colour, uint32_t nev) {
-  const uint32_t L = g.L, LG = g.LG, PS = g.PS, NW = g.NW;
+// One colour phase over the thread's rows, a word (PAIR: two adjacent words, rows of an even number of
+// words) at a time.  YFIX: RI is a multiple of L, so every row the thread visits has the same y: its
+// y-neighbour offsets are fixed, and the parity of the active sites steps by dz per row.
+//
+// Bound by VALU issue (92 % of the cycles of a busy compute unit): a pair is 172 operations for 8 attempts, 84 of
+// them the two draws, 181 with word indices and four single bounds a word.  Lattices L = 16 .. 64, 410 of
+// each, 50 sweeps: 6.52 -> 6.19 ms.
+// A pair is one 8-byte LDS access and one 8-byte coupling load per neighbour row; the x neighbours and the x
+// bond between its words come from itself.  g describes the columns: wl / wr the distances to the words
+// left of the first and right of the last word.
+template <int D, bool EA, bool NEVER, bool YFIX, bool PAIR>
+__device__ __forceinline__ void batch_colour(uint32_t base, uint32_t table, __amdgpu_buffer_rsrc_t rj, const BatchGeo& g,
+                                             const PhiloxUniform& U, const RoundKeys& K, uint32_t colour, uint32_t nev) {
+  typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+  const uint32_t L = g.L, RB = 4u * g.LG;
   uint32_t y = g.r_first % L, z = g.r_first / L;
-  const uint32_t ymo = y ? 0u - LG : g.ym_wrap;               // used when YFIX
-  const uint32_t ypo = (y + 1 < L) ? LG : 0u - g.ym_wrap;
+  const uint32_t ymo = y ? 0u - RB : g.ym_wrap;               // used when YFIX
+  const uint32_t ypo = (y + 1 < L) ? RB : 0u - g.ym_wrap;
   uint32_t p = (colour + y + z) & 1u;
   const uint32_t pstep = g.dz & 1u;
-  const uint32_t wstep = g.RI * LG;
-  uint32_t w = g.r_first * LG + 2u * g.xg;
+  const uint32_t wstep = g.RI * RB;
+  uint32_t w = g.r_first * RB + (PAIR ? 8u : 4u) * g.xg;
+  auto get = [&](uint32_t at) {
+    return PAIR ? lds_load64(base + at) : make_uint2(lds_load32(base + at), 0u);
+  };
+  auto bonds = [&](uint32_t at) {
+    if (PAIR) {
+      const u2v v = __builtin_amdgcn_raw_buffer_load_b64(rj, at, 0, 0);
+      return make_uint2(v.x, v.y);
+    }
+    return make_uint2(__builtin_amdgcn_raw_buffer_load_b32(rj, at, 0, 0), 0u);
+  };
   for (uint32_t row = g.r_first; row < g.R; row += g.RI, w += wstep) {
-    const uint2 c = *reinterpret_cast<const uint2*>(sp + w);
-    const uint32_t lw = sp[w + g.wl], rw = sp[w + g.wr];
-    const uint32_t wym = w + (YFIX ? ymo : (y ? 0u - LG : g.ym_wrap));
-    const uint32_t wyp = w + (YFIX ? ypo : ((y + 1 < L) ? LG : 0u - g.ym_wrap));
-    uint2 nbp[2 * D - 2];
-    nbp[0] = *reinterpret_cast<const uint2*>(sp + wym);
-    nbp[1] = *reinterpret_cast<const uint2*>(sp + wyp);
+    // keeps the compiler from giving each neighbour's address a register of its own to step (26
+    // additions a row where these sums are 9)
+    asm("" : "+v"(w));
+    const uint2 c = get(w);
+    const uint32_t wl = w + g.wl;
+    const uint32_t lw = lds_load32(base + wl), rw = lds_load32(base + w + g.wr);
+    const uint32_t wym = w + (YFIX ? ymo : (y ? 0u - RB : g.ym_wrap));
+    const uint32_t wyp = w + (YFIX ? ypo : ((y + 1 < L) ? RB : 0u - g.ym_wrap));
+    uint2 nb[2 * D - 2];
+    nb[0] = get(wym);
+    nb[1] = get(wyp);
     uint32_t wzm = 0;
     if (D == 3) {
-      const uint32_t m = w - PS, q = w + PS;
-      wzm = __builtin_elementwise_min(m, m + NW);
-      const uint32_t wzp = __builtin_elementwise_min(q, q - NW);
-      nbp[2] = *reinterpret_cast<const uint2*>(sp + wzm);
-      nbp[3] = *reinterpret_cast<const uint2*>(sp + wzp);
+      // planes z-1 and z+1, periodic: w -/+ PB wrapped into [0, NB) by an unsigned minimum (the
+      // out-of-range candidate has wrapped past 2^32 or is at least NB), no per-lane select
+      const uint32_t m = w - g.PB, q = w + g.PB;
+      wzm = __builtin_elementwise_min(m, m + g.NB);
+      const uint32_t wzp = __builtin_elementwise_min(q, q - g.NB);
+      nb[2 * D - 4] = get(wzm);
+      nb[2 * D - 3] = get(wzp);
     }
-    uint32_t nb0[2 * D - 2], nb1[2 * D - 2], jn0[D + 1], jn1[D + 1];
+    uint32_t nb0[2 * D - 2], nb1[2 * D - 2], j0[D + 1], j1[D + 1];
 #pragma unroll
     for (int k = 0; k < 2 * D - 2; ++k) {
-      nb0[k] = nbp[k].x;
-      nb1[k] = nbp[k].y;
+      nb0[k] = nb[k].x;
+      nb1[k] = nb[k].y;
     }
     if (EA) {
-      typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-      const u2v j = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * w, 0, 0);
-      const u2v jym = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wym, 0, 0);
-      jn0[0] = __builtin_amdgcn_raw_buffer_load_b32(rj, 4u * (w + g.wl), 0, 0);
-      jn0[1] = jn1[0] = j.x;
-      jn1[1] = j.y;
-      jn0[2] = jym.x;
-      jn1[2] = jym.y;
+      j0[0] = __builtin_amdgcn_raw_buffer_load_b32(rj, wl, 0, 0);
+      const uint2 j = bonds(w), jym = bonds(wym);
+      j0[1] = j1[0] = j.x;
+      j1[1] = j.y;
+      j0[2] = jym.x;
+      j1[2] = jym.y;
       if (D == 3) {
-        const u2v jzm = __builtin_amdgcn_raw_buffer_load_b64(rj, 4u * wzm, 0, 0);
-        jn0[D] = jzm.x;
-        jn1[D] = jzm.y;
+        const uint2 jzm = bonds(wzm);
+        j0[D] = jzm.x;
+        j1[D] = jzm.y;
       }
     }
-    const uint32_t S0 = nib_unsat<D, EA>(c.x, lw, c.y, nb0, jn0);
-    const uint32_t S1 = nib_unsat<D, EA>(c.y, c.x, rw, nb1, jn1);
     uint32_t r0[4], r1[4];
-    philox_lane_unfolded(w, U, K, r0);
-    philox_lane_unfolded(w + 1u, U, K, r1);
-    *reinterpret_cast<uint2*>(sp + w) =
-        make_uint2(c.x ^ nib_flips<NEVER>(S0, p, r0, bound, nev), c.y ^ nib_flips<NEVER>(S1, p, r1, bound, nev));
+    const uint32_t S0 = nib_unsat<D, EA>(c.x, lw, PAIR ? c.y : rw, nb0, j0);
+    philox_lane_unfolded(w >> 2, U, K, r0);
+    if (PAIR) {
+      const uint32_t S1 = nib_unsat<D, EA>(c.y, c.x, rw, nb1, j1);
+      philox_lane_unfolded((w >> 2) + 1u, U, K, r1);
+      lds_store64(base + w, make_uint2(c.x ^ batch_flips<D, NEVER>(S0, p, r0, table, nev),
+                                       c.y ^ batch_flips<D, NEVER>(S1, p, r1, table, nev)));
+    } else {
+      lds_store32(base + w, c.x ^ batch_flips<D, NEVER>(S0, p, r0, table, nev));
+    }
     if (YFIX) {
       z += g.dz;
       p ^= pstep;
@@ -321,13 +303,14 @@ __device__ __forceinline__ void batch_colour2(uint32_t* sp, const uint32_t* boun
 // classes with T == 0.
 template <int D, bool EA, int NT, bool NEVER>
 __device__ __forceinline__ void batch_sweeps(const BatchLattice& B, const BatchCall& Cl, uint32_t* sp,
-                                             const uint32_t* bound, int64_t* red) {
+                                             const uint32_t* pair_table, int64_t* red) {
+  const uint32_t base = lds_addr(sp), table = lds_addr(pair_table);
   BatchGeo g;
   g.L = B.L;
   g.LG = g.L / 8;                                  // words per row
   g.R = (D == 3) ? g.L * g.L : g.L;                // rows
-  g.NW = g.R * g.LG;                               // words
-  g.PS = g.L * g.LG;                               // words per plane (3D)
+  g.NB = 4u * g.R * g.LG;
+  g.PB = 4u * g.L * g.LG;                          // a plane (3D)
   const uint32_t tid = threadIdx.x;
   g.RI = NT / g.LG;                                // rows per iteration (>= 1: L <= 8192)
   // rows of a fixed y per thread (a multiple of L rows per iteration) when that keeps at least 4/5
@@ -338,12 +321,11 @@ __device__ __forceinline__ void batch_sweeps(const BatchLattice& B, const BatchC
   g.r_first = tid / g.LG;
   g.dz = g.RI / g.L;                               // row step in (y, z)
   g.dy = g.RI % g.L;
-  g.wl = g.xg ? 0u - 1u : g.LG - 1u;               // offset to the word on the left
-  g.wr = (g.xg + 1 < g.LG) ? 1u : 0u - (g.LG - 1u);
-  g.ym_wrap = (g.L - 1) * g.LG;
-  g.zm_wrap = (g.L - 1) * g.PS;
+  g.wl = g.xg ? 0u - 4u : 4u * (g.LG - 1u);        // to the word on the left
+  g.wr = (g.xg + 1 < g.LG) ? 4u : 0u - 4u * (g.LG - 1u);
+  g.ym_wrap = 4u * (g.L - 1) * g.LG;
   const bool yfix = g.dy == 0;
-  // rows of an even number of words: pairs of words per thread (batch_colour2)
+  // rows of an even number of words: pairs of words per thread
   const bool pair = (g.LG & 1u) == 0;
   BatchGeo g2 = g;
   if (pair) {
@@ -354,15 +336,15 @@ __device__ __forceinline__ void batch_sweeps(const BatchLattice& B, const BatchC
     g2.r_first = tid / PG;
     g2.dz = g2.RI / g.L;
     g2.dy = g2.RI % g.L;
-    g2.wl = g2.xg ? 0u - 1u : g.LG - 1u;            // word left of the pair's first word
-    g2.wr = (g2.xg + 1 < PG) ? 2u : 2u - g.LG;      // word right of its second word
+    g2.wl = g2.xg ? 0u - 4u : 4u * (g.LG - 1u);     // word left of the pair's first word
+    g2.wr = (g2.xg + 1 < PG) ? 8u : 8u - 4u * g.LG; // word right of its second word
   }
   const bool active2 = pair && tid < g2.RI * (g.LG / 2);
   const bool yfix2 = g2.dy == 0;
-  // couplings by buffer loads: one descriptor over the NW words, byte offsets per lane
+  // couplings by buffer loads: one descriptor over the words, byte offsets per lane
   const __amdgpu_buffer_rsrc_t rj =
-      __builtin_amdgcn_make_buffer_rsrc((void*)B.Jn, 0, (int)(4u * g.NW), 0x00020000);
-  const uint32_t nev = NEVER ? Cl.never4 : 0u;
+      __builtin_amdgcn_make_buffer_rsrc((void*)B.Jn, 0, (int)g.NB, 0x00020000);
+  const uint32_t nev = NEVER ? Cl.never4 / 2u : 0u;
   uint32_t rec = 0;
   for (uint32_t i = 0; i < Cl.n; ++i) {
     const uint32_t t = B.t + i;
@@ -372,15 +354,15 @@ __device__ __forceinline__ void batch_sweeps(const BatchLattice& B, const BatchC
       if (pair) {
         if (active2) {
           if (yfix2)
-            batch_colour2<D, EA, NEVER, true>(sp, bound, rj, g2, U, B.keys, colour, nev);
+            batch_colour<D, EA, NEVER, true, true>(base, table, rj, g2, U, B.keys, colour, nev);
           else
-            batch_colour2<D, EA, NEVER, false>(sp, bound, rj, g2, U, B.keys, colour, nev);
+            batch_colour<D, EA, NEVER, false, true>(base, table, rj, g2, U, B.keys, colour, nev);
         }
       } else if (active) {
         if (yfix)
-          batch_colour<D, EA, NEVER, true>(sp, bound, rj, g, U, B.keys, colour, nev);
+          batch_colour<D, EA, NEVER, true, false>(base, table, rj, g, U, B.keys, colour, nev);
         else
-          batch_colour<D, EA, NEVER, false>(sp, bound, rj, g, U, B.keys, colour, nev);
+          batch_colour<D, EA, NEVER, false, false>(base, table, rj, g, U, B.keys, colour, nev);
       }
       __syncthreads();
     }
@@ -407,7 +389,18 @@ __device__ void batch_task(const BatchLattice& Bg, const BatchCall& Cg, uint32_t
     const uint2 b = reinterpret_cast<const uint2*>(B.spins)[w];
     sp[w] = pack_nibbles(b.x, b.y);
   }
-  if (tid < 8) bound[tid] = Cl.bound[tid];
+  // accept bounds of two sites by their u
+  constexpr uint32_t Z1 = 2u * D + 1u;
+  if (tid < Z1 * Z1) {
+    uint32_t b0 = 0, b1 = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < Z1; ++u) {  // (no indexed access to the uniform registers)
+      b0 = tid % Z1 == u ? Cl.bound[u] : b0;
+      b1 = tid / Z1 == u ? Cl.bound[u] : b1;
+    }
+    bound[2u * tid] = b0;
+    bound[2u * tid + 1u] = b1;
+  }
   __syncthreads();
   if (Cl.never4)
     batch_sweeps<D, EA, NT, true>(B, Cl, sp, bound, red);
@@ -421,14 +414,20 @@ __device__ void batch_task(const BatchLattice& Bg, const BatchCall& Cg, uint32_t
   }
 }
 
+static_assert(kBatchRed >= 7 * 7 * 8 && kBatchTask >= kBatchRed + 16 * 8 && kBatchCtl >= kBatchTask + 4, "");
+
 template <int D, bool EA, int NT>
 __global__ __launch_bounds__(NT) void k_batch(BatchLattice* lats, const BatchCall* calls,
-                                              const uint32_t* order, uint32_t ntasks, uint32_t* next) {
-  __shared__ uint32_t bound[8];   // static LDS first: lookups use a constant base
-  __shared__ int64_t red[16];
-  __shared__ uint32_t task;
+                                              const uint32_t* order, uint32_t ntasks, uint32_t* next,
+                                              uint32_t ctl) {
+  // all LDS in one block, the lattice at its start: a word's LDS address is its byte offset, which also
+  // addresses its couplings; behind it (at ctl) the pair table, sums and the task index
   extern __shared__ __align__(16) uint32_t lds[];
   uint32_t* sp = lds;
+  char* const end = reinterpret_cast<char*>(lds) + ctl;
+  uint32_t* bound = reinterpret_cast<uint32_t*>(end);
+  int64_t* red = reinterpret_cast<int64_t*>(end + kBatchRed);
+  uint32_t& task = *reinterpret_cast<uint32_t*>(end + kBatchTask);
   // Termination: the queue fetch, both barriers, the readfirstlane of the
   // task index and the exit test sit at this one loop level, and no branch
   // at this level depends on per-lane data: the fetch and the counter store
@@ -469,7 +468,8 @@ static hipError_t set_batch_attrs() {
   const void* ks[4] = {(const void*)k_batch<2, false, NT>, (const void*)k_batch<2, true, NT>,
                        (const void*)k_batch<3, false, NT>, (const void*)k_batch<3, true, NT>};
   for (const void* k : ks) {
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchMaxLds);
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(kBatchMaxLds + kBatchCtl));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -478,10 +478,10 @@ static hipError_t set_batch_attrs() {
 template <int NT>
 static void go_batch(uint32_t d, bool ea, dim3 grid, size_t lds, hipStream_t stream, BatchLattice* lats,
                      const BatchCall* calls, const uint32_t* order, uint32_t ntasks, uint32_t* counter) {
-  if (d == 2 && !ea) hipLaunchKernelGGL((k_batch<2, false, NT>), grid, dim3(NT), lds, stream, lats, calls, order, ntasks, counter);
-  if (d == 2 && ea) hipLaunchKernelGGL((k_batch<2, true, NT>), grid, dim3(NT), lds, stream, lats, calls, order, ntasks, counter);
-  if (d == 3 && !ea) hipLaunchKernelGGL((k_batch<3, false, NT>), grid, dim3(NT), lds, stream, lats, calls, order, ntasks, counter);
-  if (d == 3 && ea) hipLaunchKernelGGL((k_batch<3, true, NT>), grid, dim3(NT), lds, stream, lats, calls, order, ntasks, counter);
+  if (d == 2 && !ea) hipLaunchKernelGGL((k_batch<2, false, NT>), grid, dim3(NT), lds + kBatchCtl, stream, lats, calls, order, ntasks, counter, (uint32_t)lds);
+  if (d == 2 && ea) hipLaunchKernelGGL((k_batch<2, true, NT>), grid, dim3(NT), lds + kBatchCtl, stream, lats, calls, order, ntasks, counter, (uint32_t)lds);
+  if (d == 3 && !ea) hipLaunchKernelGGL((k_batch<3, false, NT>), grid, dim3(NT), lds + kBatchCtl, stream, lats, calls, order, ntasks, counter, (uint32_t)lds);
+  if (d == 3 && ea) hipLaunchKernelGGL((k_batch<3, true, NT>), grid, dim3(NT), lds + kBatchCtl, stream, lats, calls, order, ntasks, counter, (uint32_t)lds);
 }
 
 hipError_t launch_batch(uint32_t d, bool ea, uint32_t nt, BatchLattice* lats, const BatchCall* calls,

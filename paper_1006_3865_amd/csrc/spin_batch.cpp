@@ -209,6 +209,7 @@ struct spin_batch {
   static constexpr int kAux = 4;
   hipStream_t aux[kAux] = {};
   hipEvent_t fork = nullptr;
+  hipEvent_t ready = nullptr;         // a call's tables are on the device: its classes may start
   hipEvent_t joined[kAux] = {};
   int next_aux = 0;
   int num_cu = 256;
@@ -285,6 +286,7 @@ static void batch_destroy(spin_batch* b) {
   if (b->h_order) (void)hipHostFree(b->h_order);
   if (b->uploaded) (void)hipEventDestroy(b->uploaded);
   if (b->fork) (void)hipEventDestroy(b->fork);
+  if (b->ready) (void)hipEventDestroy(b->ready);
   for (int k = 0; k < spin_batch::kAux; ++k) {
     if (b->joined[k]) (void)hipEventDestroy(b->joined[k]);
     if (b->aux[k]) {
@@ -629,9 +631,39 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
     b->last_calls.assign(b->h_calls, b->h_calls + S);
     b->last_order.assign(b->h_order, b->h_order + norder);
   }
+  // The classes side by side, the one with most work on the pool's stream, where it starts first, the
+  // others on the pool's further streams: they run in the places that its workgroups leave on the
+  // compute units and fill its end, when ever fewer tasks are left.  +-J lattices L = 16 .. 64, 410 of
+  // each, 50 sweeps: 7.01 ms one after another, 6.19 side by side.
+  std::vector<size_t> by_work(classes.size());
+  std::vector<uint64_t> work(classes.size(), 0);
   for (size_t k = 0; k < classes.size(); ++k) {
+    by_work[k] = k;
+    for (uint32_t i : classes[k].members) work[k] += b->m[i].N * (uint64_t)b->h_calls[i].n;
+  }
+  std::stable_sort(by_work.begin(), by_work.end(), [&](size_t x, size_t y) { return work[x] > work[y]; });
+  if (classes.size() > 1) {
+    e = hipEventRecord(b->ready, b->stream);
+    if (e != hipSuccess) {
+      join_aux(b, used);
+      return hfail(e, "batch fork");
+    }
+  }
+  for (size_t j = 0; j < classes.size(); ++j) {
+    const size_t k = by_work[j];
     const Class& cl = classes[k];
     const uint32_t ntasks = ranges[k].second;
+    hipStream_t on = b->stream;
+    if (j > 0) {
+      const int a = (int)((j - 1) % spin_batch::kAux);
+      on = b->aux[a];
+      e = hipStreamWaitEvent(on, b->ready, 0);
+      if (e != hipSuccess) {
+        join_aux(b, used);
+        return hfail(e, "batch fork wait");
+      }
+      used[a] = true;
+    }
     // workgroups per CU: the override, else the plan when every member has one (never more than
     // the class's LDS allows), else as many as threads and LDS allow
     uint32_t per_cu = max_per_cu(cl.nt, cl.lds);
@@ -639,13 +671,13 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
     if (b->wgs_override > 0) per_cu = (uint32_t)b->wgs_override;
     const uint32_t grid = std::min<uint32_t>(ntasks, per_cu * (uint32_t)b->num_cu);
     e = launch_batch(cl.d, cl.ea, cl.nt, b->d_lats, b->d_calls, b->d_order + ranges[k].first, ntasks,
-                     b->d_counters + k, cl.lds, grid, b->stream);
+                     b->d_counters + k, cl.lds, grid, on);
     if (e != hipSuccess) {
       join_aux(b, used);
       return hfail(e, "batch launch");
     }
   }
-  // join: later work on the pool's stream waits for the larger members
+  // join: later work on the pool's stream waits for all of it
   if (int rc = join_aux(b, used)) return rc;
   if (cap) {
     b->t_stale = true;  // every replay advances the device counters
@@ -676,7 +708,8 @@ spin_batch* spin_batch_create(int count, const spin_desc* descs, void* stream) {
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&b->num_cu, hipDeviceAttributeMultiprocessorCount, dev);
   bool ok = hipEventCreateWithFlags(&b->uploaded, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
+            hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&b->ready, hipEventDisableTiming) == hipSuccess;
   for (int k = 0; ok && k < spin_batch::kAux; ++k)
     ok = hipStreamCreateWithFlags(&b->aux[k], hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&b->joined[k], hipEventDisableTiming) == hipSuccess;

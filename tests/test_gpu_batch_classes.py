@@ -9,6 +9,15 @@ from paper_1006_3865_amd import spin, workloads
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    spin.load()
+    return torch
+
+
 def test_more_classes_than_streams():
     sizes = [(d, m, L) for d, edges in ((2, (8, 40, 64, 256, 400)), (3, (8, 16, 24, 48, 64))) for m in (0, 1) for L in edges]
     descs = [dict(model=m, L=L, d=d, seed=workloads.seed(0x900 + i), replica=i,

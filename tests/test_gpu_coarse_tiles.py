@@ -11,6 +11,15 @@ from paper_1006_3865_amd import spin, workloads
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    spin.load()
+    return torch
+
+
 @pytest.mark.parametrize("model,d,L,T,k", [
     (0, 2, 48, 8, 4), (1, 2, 48, 8, 5), (0, 2, 80, 8, 9), (1, 2, 96, 16, 4), (0, 2, 32, 16, 9), (1, 2, 64, 32, 5),
     (0, 2, 128, 64, 9), (0, 3, 16, 8, 5), (1, 3, 48, 8, 4), (1, 3, 32, 16, 5),

@@ -9,6 +9,15 @@ from paper_1006_3865_amd import spin, workloads
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    spin.load()
+    return torch
+
+
 # (L, rows, planes): 256 has at most 2 parts, 128 at most 4; fewer where the strips do not divide L / parts
 @pytest.mark.parametrize("L,rows,planes", [(256, 8, 2), (256, 4, 256), (128, 4, 2), (128, 8, 64), (128, 4, 4),
                                            (128, 8, 32)])

@@ -20,36 +20,6 @@
 
 namespace spin {
 
-// Philox4x32-10 as philox_lane computes it, with round 3 left in the loop of
-// the later rounds: c3 after round 2 is recovered from the folded word
-// (x4 = c3 ^ k1[2]) on the scalar unit.  Same words; this kernel waits on
-// its texture path rather than on VALU issue, and measured this form 3 %
-// faster than the folded one, whose changed schedule costs it more than the
-// operation it saves.
-__device__ __forceinline__ void philox_lane_unfolded(uint32_t c0, const PhiloxUniform& U, const RoundKeys& K,
-                                                     uint32_t r[4]) {
-  const uint64_t p0 = (uint64_t)kPhiloxM0 * c0;
-  const uint32_t a2 = (uint32_t)(p0 >> 32) ^ U.x1;
-  const uint32_t a3 = (uint32_t)p0;
-  const uint64_t p1 = (uint64_t)kPhiloxM1 * a2;
-  uint32_t d0 = (uint32_t)(p1 >> 32) ^ U.x2;
-  uint32_t d1 = (uint32_t)p1;
-  uint32_t d2 = a3 ^ U.x3;
-  uint32_t d3 = U.x4 ^ K.k1[2];
-#pragma unroll
-  for (int i = 2; i < 10; ++i) {
-    const uint64_t q0 = (uint64_t)kPhiloxM0 * d0;
-    const uint64_t q1 = (uint64_t)kPhiloxM1 * d2;
-    const uint32_t n0 = xor3((uint32_t)(q1 >> 32), d1, K.k0[i]);
-    const uint32_t n2 = xor3((uint32_t)(q0 >> 32), d3, K.k1[i]);
-    d1 = (uint32_t)q1;
-    d3 = (uint32_t)q0;
-    d0 = n0;
-    d2 = n2;
-  }
-  r[0] = d0; r[1] = d1; r[2] = d2; r[3] = d3;
-}
-
 // ---------------------------------------------------------------- couplings
 
 // Generate couplings (Philox rule of spin.h) directly as coupling words.
@@ -206,7 +176,8 @@ __device__ __forceinline__ uint32_t batch_flips(uint32_t S, uint32_t p, const ui
 //
 // Bound by VALU issue (92 % of the cycles of a busy compute unit): a pair is 172 operations for 8 attempts, 84 of
 // them the two draws, 181 with word indices and four single bounds a word.  Lattices L = 16 .. 64, 410 of
-// each, 50 sweeps: 6.52 -> 6.19 ms.
+// each, 50 sweeps: 6.52 -> 6.19 ms, and 6.16 with round 3 of the draws folded as elsewhere (slower while this
+// kernel waited for its coupling loads).
 // A pair is one 8-byte LDS access and one 8-byte coupling load per neighbour row; the x neighbours and the x
 // bond between its words come from itself.  g describes the columns: wl / wr the distances to the words
 // left of the first and right of the last word.
@@ -275,10 +246,10 @@ __device__ __forceinline__ void batch_colour(uint32_t base, uint32_t table, __am
     }
     uint32_t r0[4], r1[4];
     const uint32_t S0 = nib_unsat<D, EA>(c.x, lw, PAIR ? c.y : rw, nb0, j0);
-    philox_lane_unfolded(w >> 2, U, K, r0);
+    philox_lane(w >> 2, U, K, r0);
     if (PAIR) {
       const uint32_t S1 = nib_unsat<D, EA>(c.y, c.x, rw, nb1, j1);
-      philox_lane_unfolded((w >> 2) + 1u, U, K, r1);
+      philox_lane((w >> 2) + 1u, U, K, r1);
       lds_store64(base + w, make_uint2(c.x ^ batch_flips<D, NEVER>(S0, p, r0, table, nev),
                                        c.y ^ batch_flips<D, NEVER>(S1, p, r1, table, nev)));
     } else {

@@ -497,9 +497,10 @@ uint64_t spin_msc_sweeps_done(const spin_msc* h);
  * rows 4 or 8 (default 8), planes even and dividing L (default 32), threads
  * 0 or 64 * (rows + 2), width 0 or L; streaming == 0 launches one kernel per
  * colour.
- * At creation the library picks a streaming shape measured to be fast for
- * L and d where one fits, else the per-colour kernel.  SPIN_EINVAL if the
- * streaming shape does not fit L. */
+ * At creation the library picks the register-column kernel where it fits, else
+ * the per-colour kernel while spins and couplings stay in the GPU's cache, and
+ * a streaming shape beyond that where one fits.  SPIN_EINVAL if the streaming
+ * shape does not fit L. */
 int spin_msc_set_kernel(spin_msc* h, int streaming, int rows, int planes, int threads, int width);
 
 /* The kernel the next sweep uses: 0 (one launch per colour), 1 (streamed

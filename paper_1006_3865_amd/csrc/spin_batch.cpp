@@ -2,9 +2,10 @@
 // a pool of lattices (disorder realisations x temperatures, or the jobs of a
 // serving loop) advanced together.  Members whose spins fit one workgroup's
 // LDS are swept by one persistent launch per class of (dimension, model,
-// workgroup size); larger members are advanced by the single-lattice kernels
-// on the same stream in the same call.  Members can be added and removed
-// between calls; their slots are reused.
+// workgroup size), the classes side by side on the pool's stream and its
+// further ones; larger members are advanced by the single-lattice kernels on
+// those in the same call.  Members can be added and removed between calls;
+// their slots are reused.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -122,7 +123,7 @@ struct Member {
   uint64_t t = 0;                // sweep counter of a resident member (host mirror)
   bool resident = false;         // swept by the persistent batch kernel
   int8_t* spins = nullptr;       // resident: slab block of N bytes
-  uint32_t* jn = nullptr;        // resident EA: nibble couplings, d*N/2 bytes
+  uint32_t* jn = nullptr;        // resident EA: coupling words, N/2 bytes
   bool jn_shared = false;        // jn belongs to the shared map under `key`
   CouplingKey key;
   spin_lattice* big = nullptr;   // not resident: a single-lattice handle
@@ -769,7 +770,8 @@ int spin_batch_is_member(const spin_batch* b, int i) { return slot_ok(b, i) ? 1 
 uint64_t spin_batch_footprint(const spin_batch* b, int i) {
   if (!slot_ok(b, i)) return 0;
   const Member& mb = b->m[i];
-  // spins, ping-pong copy, and for the glass the int8 couplings and their nibble-packed copy
+  // spins, ping-pong copy, and for the glass the int8 couplings and their packed copy, the latter at d N / 2
+  // bytes: callers' budgets are made with this figure, and the N / 2 it takes stay within it
   if (mb.big) return mb.N * 2 + (mb.model == SPIN_EA_PMJ ? (uint64_t)mb.d * mb.N + (uint64_t)mb.d * mb.N / 2 : 0);
   return mb.N + (mb.model == SPIN_EA_PMJ ? (uint64_t)mb.d * mb.N / 2 : 0);
 }

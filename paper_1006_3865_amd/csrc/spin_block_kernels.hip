@@ -702,6 +702,13 @@ BlockPlan block_plan(const Lat& lat, uint32_t k, double* us) {
         if ((ty > tz ? ty - tz : tz - ty) <= 8u) consider(BlockPlan{k, 0, ty, tz, 1024});
   } else if (is_rag(lat)) {
     for (uint32_t ty : {1u, 2u, 4u, 6u, 8u, 16u}) consider(BlockPlan{k, 0, ty, 1, 1024});
+  } else if (lat.N >= 1u << 24) {
+    // several rounds of workgroups a compute unit, where the estimate takes shapes whose registers
+    // (89 a lane with up to four units kept there) halve what a compute unit holds: the listed form
+    // (31 registers) with this tile was the fastest of the shapes below at L = 4608 .. 15360 for k <= 3 and
+    // within 4 % of it for k <= 5.  us a sweep, the estimate's choice and now: L = 5120 k = 1 35.6 -> 24.9, L =
+    // 6144 k = 1 49.5 -> 30.8, k = 2 35.5 -> 25.2, k = 4 27.7 -> 23.0
+    consider(BlockPlan{k, 32, 64, 1, 512});
   } else {
     for (uint32_t tx : {4u, 8u, 16u, 32u})
       for (uint32_t ty : {4u, 8u, 16u, 32u, 64u})

@@ -652,6 +652,30 @@ static int run_lcg(spin_lattice* h, int n, const Accept& acc, int every, int64_t
   return SPIN_OK;
 }
 
+// Whether launches of up to k sweeps of k_block are faster for n sweeps with nrec records than the
+// launches of the family that single sweeps name.  Where they are not (us a sweep, the family
+// against k_block):
+//   3D +-J in the streaming kernel: from L = 352 its slabs of 16 rows (L % 16 == 0) are faster (84
+//     against 95, L = 512 179 against 285), from L = 392 those of 8 rows (111 against 133); but it
+//     counts a record in a pass of its own (L = 512 117 a record against 17, with rows of 8 L = 504 692 against 17),
+//     so k_block runs calls that record every sweep, with 8 rows every sixth;
+//   2D Ising in the tiled form of the row kernel, one sweep a launch and no record: from L = 2560 with
+//     512-site tiles (L = 3584 14.9 against 18.8, 5120 22.9 against 24.9, 10240 67 against 75), below
+//     L = 1536 and from 3072 with 128-site ones (L = 384 3.3 against 4.0, 3200 12.1 against 15.2), below L =
+//     768 with 16-site ones (L = 432 3.7 against 4.2).
+static bool block_wins(const spin_lattice* h, int kernel, const Tile& tile, uint32_t k, uint32_t n, uint32_t nrec) {
+  if (kernel == SPIN_KERNEL_STREAM && h->d == 3 && h->model == SPIN_EA_PMJ) {
+    const bool rows16 = h->L % 16 == 0;
+    return h->L < (rows16 ? 352 : 392) || (uint64_t)nrec * (rows16 ? 1u : 6u) >= n;
+  }
+  if (kernel == SPIN_KERNEL_FUSED && h->d == 2 && k == 1 && nrec == 0) {
+    if (tile.x == 512) return h->L < 2560;
+    if (tile.x == 128) return h->L >= 1536 && h->L < 3072;
+    if (tile.x == 16) return h->L >= 768;
+  }
+  return true;
+}
+
 // How n sweeps are cut into k_block launches: the number of launches (0: not at all) and the plan of
 // the longest; launch i runs n / launches sweeps, the first n % launches of them one more, all on
 // one tile shape.  The number has the parity that leaves the current buffer where the family's own
@@ -685,7 +709,7 @@ static uint32_t block_launches(spin_lattice* h, int n, int kernel, BlockPlan* pl
 // be faster.  *ran = false (and nothing enqueued) where neither runs: the caller goes on with the
 // family's own kernels.
 static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64_t* dE, int64_t* dM, int kernel,
-                     const CallScratch* fx, bool* ran) {
+                     const Tile& tile, const CallScratch* fx, bool* ran) {
   *ran = false;
   if (!block_lattice_ok(lat_of(h), acc)) return SPIN_OK;
   BlockPlan plan;
@@ -702,8 +726,8 @@ static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64
     h->t += (uint64_t)n;
     return SPIN_OK;
   }
-  if (m == 0) return SPIN_OK;
   const uint32_t nrec = every > 0 ? (uint32_t)(n / every) : 0;
+  if (m == 0 || !block_wins(h, kernel, tile, plan.k, (uint32_t)n, nrec)) return SPIN_OK;
   const uint32_t tiles = block_tiles(lat_of(h), plan);
   if (fx && (!h->buf[1] || (size_t)nrec * tiles * 2 > fx->part_slots)) return SPIN_OK;
   if (!h->buf[1]) {
@@ -755,7 +779,7 @@ static int run_sweeps(spin_lattice* h, int n, double beta, int every, int64_t* d
   const int kernel = resolve(h, &tile, &block);
   if (block) {
     bool ran = false;
-    if (int rc = run_block(h, n, acc, every, dE, dM, kernel, fx, &ran)) return rc;
+    if (int rc = run_block(h, n, acc, every, dE, dM, kernel, tile, fx, &ran)) return rc;
     if (ran) return SPIN_OK;
   }
   hipError_t e = hipSuccess;

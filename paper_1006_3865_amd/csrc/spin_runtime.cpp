@@ -500,16 +500,19 @@ static void make_plans(spin_lattice* h) {
   h->plans_made = true;
 }
 
-// Make room for nrec records of `parts` slots each.
-static int reserve_parts(spin_lattice* h, uint32_t nrec, uint32_t parts) {
+// Make room for nrec records of `parts` slots each: false where the memory is not to be had.
+static bool grow_parts(spin_lattice* h, uint32_t nrec, uint32_t parts) {
   const size_t need = (size_t)nrec * parts * 2;
-  if (need <= h->part_slots) return SPIN_OK;
+  if (need <= h->part_slots) return true;
   (void)hipStreamSynchronize(h->stream);
   h->mem.put(h->part);
   h->part = (int64_t*)h->mem.get(need * sizeof(int64_t));
   h->part_slots = h->part ? need : 0;
-  if (!h->part) return fail(SPIN_ENOMEM, "record buffer allocation failed");
-  return SPIN_OK;
+  return h->part != nullptr;
+}
+
+static int reserve_parts(spin_lattice* h, uint32_t nrec, uint32_t parts) {
+  return grow_parts(h, nrec, parts) ? SPIN_OK : fail(SPIN_ENOMEM, "record buffer allocation failed");
 }
 
 // Partial-count slots for nrec records of `parts` slots each: the caller's fixed
@@ -729,13 +732,11 @@ static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64
   const uint32_t nrec = every > 0 ? (uint32_t)(n / every) : 0;
   if (m == 0 || !block_wins(h, kernel, tile, plan.k, (uint32_t)n, nrec)) return SPIN_OK;
   const uint32_t tiles = block_tiles(lat_of(h), plan);
-  if (fx && (!h->buf[1] || (size_t)nrec * tiles * 2 > fx->part_slots)) return SPIN_OK;
-  if (!h->buf[1]) {
-    h->buf[1] = (int8_t*)h->mem.get(spin_bytes(h));
-    if (!h->buf[1]) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
-  }
-  int64_t* part = nullptr;
-  if (int rc = take_parts(h, fx, nrec, tiles, &part)) return rc;
+  // memory that the call has not got (the second buffer is taken at creation where there is room for
+  // it; in-place families run without): the family's own kernels
+  if (!h->buf[1]) return SPIN_OK;
+  if (fx ? (size_t)nrec * tiles * 2 > fx->part_slots : nrec > 0 && !grow_parts(h, nrec, tiles)) return SPIN_OK;
+  int64_t* const part = nrec == 0 ? nullptr : fx ? fx->part : h->part;
   *ran = true;
   uint32_t done = 0, rec = 0;
   for (uint32_t i = 0; i < m; ++i) {
@@ -859,7 +860,8 @@ int spin::sweep_record_fixed(spin_lattice* h, int n, double beta, int every, int
 
 // Allocate what the handle's next sweep needs (the second spin buffer of the
 // ping-pong kernels, the packed couplings), so that sweeping later allocates
-// nothing.
+// nothing.  A family that works in place is not refused for want of a second buffer: its calls then
+// run without k_block.
 static int prepare_buffers(spin_lattice* h) {
   if (h->rng != SPIN_RNG_PHILOX) return SPIN_OK;
   if (h->schedule == SPIN_SCHEDULE_COARSE) return ensure_jn(h);
@@ -869,9 +871,10 @@ static int prepare_buffers(spin_lattice* h) {
   if (block && block_offered(h)) make_plans(h);
   if ((kernel == SPIN_KERNEL_RESIDENT && single_threads(h, tile)) || kernel == SPIN_KERNEL_STREAM)
     if (int rc = ensure_jn(h)) return rc;
-  if ((kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM || (block && block_offered(h))) && !h->buf[1]) {
+  const bool pingpong = kernel == SPIN_KERNEL_FUSED || kernel == SPIN_KERNEL_STREAM;
+  if ((pingpong || (block && block_offered(h))) && !h->buf[1]) {
     h->buf[1] = (int8_t*)h->mem.get(spin_bytes(h));
-    if (!h->buf[1]) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
+    if (!h->buf[1] && pingpong) return fail(SPIN_ENOMEM, "allocation of the second spin buffer failed");
   }
   return SPIN_OK;
 }

@@ -1075,12 +1075,25 @@ int spin_sweep_record_device(spin_lattice* h, int n, double beta, int every, int
   return run_sweeps(h, n, beta, every, E, M);
 }
 
+// Whether work enqueued on the stream is being captured into a graph.
+static bool capturing(hipStream_t stream) {
+  if (!stream) return false;  // the null stream is never captured here
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 int spin_sweep_record(spin_lattice* h, int n, double beta, int every, int64_t* E, int64_t* M) {
   if (!h) return fail(SPIN_EINVAL, "NULL handle");
   if (every < 1) return fail(SPIN_EINVAL, "every must be >= 1");
   if (n < 0) return fail(SPIN_EINVAL, "n must be >= 0");
   const int nrec = n / every;
   if (nrec > 0 && (!E || !M)) return fail(SPIN_EINVAL, "NULL record arrays");
+  if (capturing(h->stream))
+    return fail(SPIN_ESTATE, "records for host arrays cannot be captured (spin_sweep_record_device can)");
   if ((size_t)nrec > h->rec_cap) {
     (void)hipStreamSynchronize(h->stream);
     h->mem.put(h->rec);

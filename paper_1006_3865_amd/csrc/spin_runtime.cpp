@@ -1086,6 +1086,8 @@ static bool capturing(hipStream_t stream) {
   return st != hipStreamCaptureStatusNone;
 }
 
+static const size_t kRecKept = 65536;  // records whose device arrays a handle keeps
+
 int spin_sweep_record(spin_lattice* h, int n, double beta, int every, int64_t* E, int64_t* M) {
   if (!h) return fail(SPIN_EINVAL, "NULL handle");
   if (every < 1) return fail(SPIN_EINVAL, "every must be >= 1");
@@ -1102,24 +1104,32 @@ int spin_sweep_record(spin_lattice* h, int n, double beta, int every, int64_t* E
     if (!h->rec) return fail(SPIN_ENOMEM, "record buffer allocation failed");
     h->rec_cap = (size_t)nrec;
   }
-  if (int rc = run_sweeps(h, n, beta, every, h->rec, h->rec + nrec)) return rc;
-  hipError_t e = hipSuccess;
-  if (nrec > 0) {
-    // both arrays in one copy
-    std::vector<int64_t> both((size_t)nrec * 2);
-    e = hipMemcpyAsync(both.data(), h->rec, 2 * sizeof(int64_t) * (size_t)nrec, hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  int rc = run_sweeps(h, n, beta, every, h->rec, h->rec + nrec);
+  if (rc == SPIN_OK) {
+    // short calls: both arrays in one copy, as each waits for its own way to the host
+    int64_t both[2 * 512];
+    const bool one = nrec <= 512;
+    const size_t bytes = sizeof(int64_t) * (size_t)nrec;
+    hipError_t e = hipSuccess;
+    if (nrec > 0) e = hipMemcpyAsync(one ? both : E, h->rec, one ? 2 * bytes : bytes, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess && !one) e = hipMemcpyAsync(M, h->rec + nrec, bytes, hipMemcpyDeviceToHost, h->stream);
+    const hipError_t done = hipStreamSynchronize(h->stream);  // also after a failure: no copy may outlive its target
+    if (e == hipSuccess) e = done;
     if (e != hipSuccess) {
-      (void)hipStreamSynchronize(h->stream);  // the copy may not outlive its target
-      return hip_fail(e, "record copy");
+      rc = hip_fail(e, "record copy");
+    } else if (one && nrec > 0) {
+      std::memcpy(E, both, bytes);
+      std::memcpy(M, both + nrec, bytes);
     }
-    std::memcpy(E, both.data(), sizeof(int64_t) * (size_t)nrec);
-    std::memcpy(M, both.data() + nrec, sizeof(int64_t) * (size_t)nrec);
-  } else {
-    e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return hip_fail(e, "synchronize");
   }
-  return SPIN_OK;
+  // what is kept for the next call is bounded (1 MiB); more goes back, as the memory of every call did
+  if (h->rec_cap > kRecKept) {
+    (void)hipStreamSynchronize(h->stream);
+    h->mem.put(h->rec);
+    h->rec = nullptr;
+    h->rec_cap = 0;
+  }
+  return rc;
 }
 
 int spin_measure(spin_lattice* h, int64_t* E, int64_t* M) {

@@ -46,3 +46,30 @@ def test_capture_is_refused_and_changes_nothing(torch, oracle_mod, L):
     np.testing.assert_array_equal(Ea, Eo)
     np.testing.assert_array_equal(Ma, Mo)
     lat.close()
+
+
+@pytest.mark.parametrize("n", [512, 513, 2000])
+def test_long_calls(torch, n):
+    """Up to 512 records come in one copy, more in one for each array."""
+    seed = workloads.seed(0x631)
+    a, b = spin.Lattice(0, 16, 2, seed), spin.Lattice(0, 16, 2, seed)
+    Ea, Ma = a.sweep_record(n, 0.4, 1)
+    parts = [b.sweep_record(k, 0.4, 1) for k in [100] * (n // 100) + ([n % 100] if n % 100 else [])]
+    np.testing.assert_array_equal(Ea, np.concatenate([p[0] for p in parts]))
+    np.testing.assert_array_equal(Ma, np.concatenate([p[1] for p in parts]))
+    np.testing.assert_array_equal(a.spins(), b.spins())
+    a.close()
+    b.close()
+
+
+def test_kept_memory_is_bounded(torch):
+    base = spin.live_allocations()
+    lat = spin.Lattice(0, 16, 2, workloads.seed(0x632))
+    none = spin.live_allocations()
+    lat.sweep_record(1000, 0.4, 1)
+    assert spin.live_allocations() == none + 1
+    lat.sweep_record(70000, 0.4, 1)  # 1.1 MB: not kept
+    assert spin.live_allocations() == none
+    lat.sweep_record(10, 0.4, 1)
+    lat.close()
+    assert spin.live_allocations() == base

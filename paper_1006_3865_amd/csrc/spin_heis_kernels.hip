@@ -123,38 +123,70 @@ __device__ __forceinline__ bool heis_decide(const float4& cur, const float4& tri
   return (dE <= 0.0f) | heis_accept(u, -(beta * dE));
 }
 
-// One colour in place, a thread per site of the colour: threads over (row, site), 32-bit
-// coordinates walked without divisions (the 64-bit divisions by L that stood here were most
-// of the kernel: 2D L = 1024 16 us a colour).
+// Order of a colour's workgroups.  XCD x (workgroups are dealt to the eight in turn) takes runs of `chunk`
+// consecutive ones, `groups` such runs, so that neighbouring rows and planes come from one L2; the rest
+// follow as numbered.  Colour 1 goes through them from the last to the first: it begins where colour 0 ended, with what the
+// memory-side cache still holds.
+struct HeisOrder {
+  uint32_t groups, chunk;
+};
+__device__ __forceinline__ uint32_t heis_order(const HeisOrder& o, bool reverse) {
+  const uint32_t b = blockIdx.x, span = 8u * o.chunk;
+  if (b >= o.groups * span) return b;
+  uint32_t g = o.groups > 1u ? b / span : 0u, i = (b - g * span) >> 3;
+  if (reverse) {
+    g = o.groups - 1u - g;
+    i = o.chunk - 1u - i;
+  }
+  return g * span + (b & 7u) * o.chunk + i;
+}
+
+// One colour in place, a thread per site of the colour: a workgroup of xw sites (segment `seg`, of nseg, of a
+// row's) by rpt rows.  Coordinates come without a division a lane (the 64-bit divisions by L that stood here
+// at first were most of the kernel: 2D L = 1024 16 us a colour), and all loads are under way
+// before the draws (the site's own vector, left to the compiler, was asked for after the neighbours had come).
 template <int D>
-__global__ __launch_bounds__(256) void k_heis_phase(float4* __restrict__ S, HeisArgs a, uint32_t nrows, uint32_t nseg) {
-  // a workgroup: segment `seg` (256 sites of the colour) of one row, or several whole rows where they
-  // are shorter
-  const uint32_t L = a.L, half = L / 2, xw = half < 256u ? half : 256u, rpt = 256u / xw;
-  const uint32_t b = xcd_tile(), rb = b / nseg, seg = b - rb * nseg;
-  const uint32_t rl = threadIdx.x / xw, j = threadIdx.x - rl * xw + 256u * seg;
-  const uint32_t row = rb * rpt + rl;
-  if (rl >= rpt || row >= nrows || j >= half) return;
+__global__ __launch_bounds__(512) void k_heis_phase(float4* __restrict__ S, HeisArgs a, HeisOrder o, uint32_t nrows,
+                                                    uint32_t nseg, uint32_t xw, uint32_t rpt) {
+  const uint32_t L = a.L, half = L / 2, b = heis_order(o, a.colour != 0);
+  uint32_t rb = b, seg = 0;
+  if (nseg > 1) {
+    rb = b / nseg;
+    seg = b - rb * nseg;
+  }
+  const uint32_t row0 = rb * rpt, row = row0 + threadIdx.y, j = threadIdx.x + xw * seg;
+  if (row >= nrows || j >= half) return;
+  uint32_t z = D == 3 ? row0 / L : 0u, y = row0 - z * L + threadIdx.y;  // the workgroup's first row, then this one
+  if (D == 3)
+    while (y >= L) {
+      y -= L;
+      ++z;
+    }
   const uint64_t plane = (uint64_t)L * L;
   const PhiloxUniform U = philox_uniform(a.t, a.replica, 10u + a.colour, a.keys);
-  const uint32_t z = D == 3 ? row / L : 0u, y = row - z * L;
+  keys_resident(a.keys);
   const uint64_t base = (uint64_t)row * L;
-  const float4* const R = S + base;
-  const float4* const ym = y ? R - L : R + (plane - L);
-  const float4* const yp = y + 1 < L ? R + L : R - (plane - L);
   const uint32_t x = 2 * j + ((a.colour + y + z) & 1u);
-  float4 h = R[x ? x - 1 : L - 1];
-  heis_add(h, R[x + 1 < L ? x + 1 : 0]);
-  heis_add(h, ym[x]);
-  heis_add(h, yp[x]);
+  float4* const P = S + base + x;
+  float4 n[2 * D];
+  n[0] = x ? P[-1] : P[L - 1];
+  n[1] = x + 1 < L ? P[1] : P[1 - (int64_t)L];
+  n[2] = y ? P[-(int64_t)L] : P[plane - L];
+  n[3] = y + 1 < L ? P[L] : P[(int64_t)L - (int64_t)plane];
   if (D == 3) {
-    heis_add(h, z ? R[x - plane] : R[x + plane * (L - 1u)]);
-    heis_add(h, z + 1 < L ? R[x + plane] : R[x - plane * (L - 1u)]);
+    n[2 * D - 2] = z ? P[-(int64_t)plane] : P[plane * (L - 1u)];
+    n[2 * D - 1] = z + 1 < L ? P[plane] : P[-(int64_t)(plane * (L - 1u))];
   }
+  const float4 cur = *P;
+  __builtin_amdgcn_sched_barrier(0);
   uint32_t w[4];
   philox_lane((uint32_t)(base + x), U, a.keys, w);
   const float4 trial = heis_direction(w[0], w[1]);
-  if (heis_decide(R[x], trial, h, heis_uniform(w[2]), a.beta)) S[base + x] = trial;
+  __builtin_amdgcn_sched_barrier(0);
+  float4 h = n[0];
+#pragma unroll
+  for (int k = 1; k < 2 * D; ++k) heis_add(h, n[k]);
+  if (heis_decide(cur, trial, h, heis_uniform(w[2]), a.beta)) *P = trial;
 }
 
 // ---------------------------------------------------------------------------
@@ -321,14 +353,25 @@ hipError_t launch_heis_init(float4* S, uint64_t N, uint64_t seed, uint32_t repli
   return hipGetLastError();
 }
 
+// Rows are cut into equal segments of at most 512 sites of the colour, and as many whole ones as 512 threads hold go
+// into a workgroup (with 256 threads and one row each the lanes of 128 < L / 2 < 256 were up to half idle).  Each
+// XCD takes an eighth of the lattice; beyond the 256 MB memory-side cache all eight go through it together, four
+// planes each at a time, and the planes that are read again stay cached.  us a sweep 3D, the flat order of one thread a
+// site and the kernel before this rule, then now: L = 256 218, 149, 141; 258 389, 244, 194; 300 407, 462, 355;
+// 320 489, 556, 463; 400 1072, 1120, 1066; 520 3571, 4040, 2489.
 hipError_t launch_heis_phase(float4* S, uint32_t d, const HeisArgs& a, hipStream_t stream) {
-  const uint32_t half = a.L / 2u, rpt = half < 256u ? 256u / half : 1u, nseg = (half + 255u) / 256u;
-  const uint32_t nrows = (uint32_t)(a.N / a.L);
-  const unsigned blocks = (nrows + rpt - 1u) / rpt * nseg;
+  constexpr uint32_t NT = 512;
+  const uint32_t half = a.L / 2u, nseg = (half + NT - 1u) / NT, xw = (half + nseg - 1u) / nseg, rpt = NT / xw;
+  const uint32_t nrows = (uint32_t)(a.N / a.L), blocks = (nrows + rpt - 1u) / rpt * nseg;
+  HeisOrder o{1u, blocks / 8u};
+  if (d == 3 && a.N * sizeof(float4) > (uint64_t)300 << 20) {
+    o.chunk = 4u * a.L / rpt * nseg;
+    o.groups = blocks / (8u * o.chunk);
+  }
   if (d == 3)
-    hipLaunchKernelGGL(k_heis_phase<3>, dim3(blocks), dim3(256), 0, stream, S, a, nrows, nseg);
+    hipLaunchKernelGGL(k_heis_phase<3>, dim3(blocks), dim3(xw, rpt), 0, stream, S, a, o, nrows, nseg, xw, rpt);
   else
-    hipLaunchKernelGGL(k_heis_phase<2>, dim3(blocks), dim3(256), 0, stream, S, a, nrows, nseg);
+    hipLaunchKernelGGL(k_heis_phase<2>, dim3(blocks), dim3(xw, rpt), 0, stream, S, a, o, nrows, nseg, xw, rpt);
   return hipGetLastError();
 }
 

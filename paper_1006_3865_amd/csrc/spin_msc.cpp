@@ -197,12 +197,13 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
     h->H = 16;
     if (msc_stream_supported((uint32_t)L, 2, 1, h->H, 256, h->XW)) h->NT = 256;
   }
-  // While spins and couplings stay in the 256 MB memory-side cache the phase kernel, which has every load in
-  // flight at once, beats the planes' march (a barrier and a round of loads a step): us a sweep 2D L =
-  // 64 7.3 against 33.5, 1024 9.1 against 32.6, 2048 25 against 45; 3D L = 64 8.1 against 18.9, 160 32
-  // against 55, 200 55 against 101, 256 100 against 118.  Beyond, reading the couplings twice a
-  // sweep costs more: 2D L = 3072 54 against 48, 4096 87 against 68; 3D L = 320 337 against 250.
-  if (N * 4 * (uint64_t)(d + 1) <= (uint64_t)(d == 3 ? 288 : 100) << 20) h->NT = 0;
+  // While spins and couplings stay in the 256 MB memory-side cache (2D, where the march reads its
+  // couplings once: a third of it) the phase kernel, which has every load in flight at once, beats the
+  // planes' march (a barrier and a round of loads a step): us a sweep 2D L = 64 7.3 against 33.5, 1024 9.1
+  // against 32.6, 2048 25 against 44, 2624 40.1 against 41.1; 3D L = 64 8.1 against 18.9, 160 31 against 54, 248 94 against
+  // 174.  Beyond, reading the couplings twice a sweep costs more: 2D L = 2752 43.0 against 41.8, 2944 48.1 against
+  // 42.2, 4096 84 against 65; 3D L = 264 171 against 160, 320 329 against 248.
+  if (N * 4 * (uint64_t)(d + 1) <= (uint64_t)(d == 3 ? 256 : 80) << 20) h->NT = 0;
   h->part = nullptr;
   h->rec = nullptr;
   h->rec_cap = 0;

@@ -22,7 +22,7 @@
 // (-1), in two planes by colour: plane c holds the four colour-c sites of a group as one dword, so the
 // active sites and the row and plane neighbours of a phase are dwords as they stand.  For the +-J
 // glass two more planes hold the couplings (bit 1 the bond to x+1, bit 2 to y+1, bit 3 to z+1 of
-// each site), staged once per launch and reused by all k hits.  Hit h of sweep t draws from Philox
+// each site), read once per launch into registers and reused by all k hits.  Hit h of sweep t draws from Philox
 // counter (s>>3, t*k + h, replica, colour), as the oracle's coarse mode does.
 // us a launch of 4 hits, before (nibble words, bounds looked up in each phase) and now, 2D Ising L = 1024: T = 8
 // 11.1 -> 4.7, 16 5.6 -> 4.3, 32 5.8 -> 4.8, 64 6.9 -> 5.2; L = 4096, T = 8 120 -> 26, T = 32, where issue
@@ -208,27 +208,46 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
     }
   }
   __syncthreads();
-  // colour c of a hit with thresholds t
-  auto phase = [&](uint32_t c, uint32_t t) {
+  // The couplings of the unit's bonds by colour, one bit (0x02) a site: to I, to N, to the rows y+1 and y-1, the planes
+  // z+1 and z-1.  They are the same in all hits: read once (five reads a phase and their masks
+  // otherwise: 3D +-J L = 256, T = 16, 100 hits 2035 us for two sweeps, 1631 so).
+  uint32_t js[2][EA ? 2 * D : 1];
+  if (EA) {
+#pragma unroll
+    for (uint32_t c = 0; c < 2; ++c) {
+      const uint32_t jm = at + (2u + c) * S::PB, jo = at + (3u - c) * S::PB;
+      const bool P = odd == (c != 0);
+      const uint32_t own = lds_load32(jm), oth = lds_load32(jo), left = lds_load32(jo - 4u), jym = lds_load32(jo - RS);
+      const uint32_t lj = __builtin_amdgcn_perm(oth, left, 0x06050403u);  // x bonds of the sites to the left
+      js[c][0] = (P ? own : oth) & kCoarseNeg;
+      js[c][EA ? 1 : 0] = (P ? lj : own) & kCoarseNeg;
+      js[c][EA ? 2 : 0] = (own >> 1) & kCoarseNeg;
+      js[c][EA ? 3 : 0] = (jym >> 1) & kCoarseNeg;
+      if (D == 3) {
+        js[c][EA ? 2 * D - 2 : 0] = (own >> 2) & kCoarseNeg;
+        js[c][EA ? 2 * D - 1 : 0] = (lds_load32(jo - PS) >> 2) & kCoarseNeg;
+      }
+    }
+  }
+  // t plus twice the unsatisfied bonds, a byte a site, of the colour-c sites A
+  auto unsat2 = [&](uint32_t c, uint32_t t, uint32_t& A) {
     const uint32_t am = at + (c ? S::PB : 0u), ao = at + (c ? 0u : S::PB);
     const bool P = odd == (c != 0);  // active sites: even x (row parity and colour the same)
-    const uint32_t A = lds_load32(am), I = lds_load32(ao), W = lds_load32(P ? ao - 4u : ao + 4u);
+    A = lds_load32(am);
+    const uint32_t I = lds_load32(ao), W = lds_load32(P ? ao - 4u : ao + 4u);
     const uint32_t ym = lds_load32(ao - RS), yp = lds_load32(ao + RS);
     const uint32_t zm = D == 3 ? lds_load32(ao - PS) : 0u, zp = D == 3 ? lds_load32(ao + PS) : 0u;
     // the row neighbours on the other side: the other plane moved by a byte
     const uint32_t N = __builtin_amdgcn_perm(I, W, P ? 0x06050403u : 0x00070605u);
     uint32_t X = t;
     if (EA) {
-      const uint32_t jm = am + 2u * S::PB, jo = ao + 2u * S::PB;
-      const uint32_t own = lds_load32(jm), oth = lds_load32(jo), left = lds_load32(jo - 4u), jym = lds_load32(jo - RS);
-      const uint32_t lj = __builtin_amdgcn_perm(oth, left, 0x06050403u);  // x bonds of the sites to the left
-      X += ((I ^ (P ? own : oth)) & kCoarseNeg) ^ A;
-      X += ((N ^ (P ? lj : own)) & kCoarseNeg) ^ A;
-      X += ((yp ^ (own >> 1)) & kCoarseNeg) ^ A;
-      X += ((ym ^ (jym >> 1)) & kCoarseNeg) ^ A;
+      X += xor3(I, js[c][0], A);
+      X += xor3(N, js[c][EA ? 1 : 0], A);
+      X += xor3(yp, js[c][EA ? 2 : 0], A);
+      X += xor3(ym, js[c][EA ? 3 : 0], A);
       if (D == 3) {
-        X += ((zp ^ (own >> 2)) & kCoarseNeg) ^ A;
-        X += ((zm ^ (lds_load32(jo - PS) >> 2)) & kCoarseNeg) ^ A;
+        X += xor3(zp, js[c][EA ? 2 * D - 2 : 0], A);
+        X += xor3(zm, js[c][EA ? 2 * D - 1 : 0], A);
       }
     } else {
       X += I ^ A;
@@ -240,7 +259,13 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
         X += zp ^ A;
       }
     }
-    lds_store32(am, A ^ ((X >> 6) & kCoarseNeg));
+    return X;
+  };
+  // colour c of a hit with thresholds t
+  auto phase = [&](uint32_t c, uint32_t t) {
+    uint32_t A;
+    const uint32_t X = unsat2(c, t, A);
+    lds_store32(at + (c ? S::PB : 0u), A ^ ((X >> 6) & kCoarseNeg));
     __syncthreads();
   };
   for (uint32_t h = 0;;) {

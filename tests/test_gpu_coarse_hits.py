@@ -1,0 +1,53 @@
+"""Many hits per tile load: hits beyond the four whose draws are made under the loads (3D: bounds looked up) against the
+oracle, with and without classes of T = 0 and with a class of T = 1 beside them, and their cost."""
+import math
+import time
+
+import numpy as np
+import pytest
+
+from paper_1006_3865_amd import spin, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    spin.load()
+
+
+@pytest.mark.parametrize("model,d,L,T,k", [(0, 3, 16, 8, 4), (0, 3, 32, 8, 6), (1, 3, 16, 8, 13), (0, 3, 32, 16, 11), (1, 3, 32, 16, 6),
+                                           (1, 3, 48, 8, 8), (1, 2, 32, 8, 11), (1, 2, 64, 16, 6), (1, 2, 64, 32, 9), (1, 2, 128, 64, 7)])
+def test_matches_oracle(oracle_mod, model, d, L, T, k):
+    seed, cs = workloads.seed(0x660 + L + k), workloads.seed(0x13) if model else None
+    lat = spin.Lattice(model, L, d, seed, coupling_seed=cs, replica=1)
+    lat.set_schedule(spin.SPIN_SCHEDULE_COARSE, T, k)
+    ch = oracle_mod.Chain(L, d, seed, 1, J=oracle_mod.couplings(L, d, cs, 0) if model else None)
+    for beta in (0.3, 1.9, 2.73, 0.7, 5.45, 3.0, 0.0, math.inf, 0.2):
+        print("coarse hits", model, d, L, T, k, beta, flush=True)
+        for got, want in zip(lat.sweep_record(1, beta, 1), ch.coarse_sweep(1, beta, T, k, every=1)):
+            np.testing.assert_array_equal(got, want)
+        np.testing.assert_array_equal(lat.spins(), ch.spins)
+    lat.close()
+
+
+def us(model, T, hits):
+    lat = spin.Lattice(model, 256, 3, workloads.seed(0x661), coupling_seed=workloads.seed(0x13) if model else None)
+    lat.set_schedule(spin.SPIN_SCHEDULE_COARSE, T, hits)
+    best = math.inf
+    for _ in range(5):
+        lat.synchronize()
+        t0 = time.perf_counter()
+        lat.sweep(4, 0.4)
+        lat.synchronize()
+        best = min(best, time.perf_counter() - t0)
+    lat.close()
+    return best / 4 * 1e6
+
+
+def test_couplings_cost_no_more_with_every_hit():
+    """3D L = 256, 100 hits a tile load: about as long with couplings as without (read in every phase: 1.24 times)."""
+    assert us(1, 16, 100) <= 1.1 * us(0, 16, 100)

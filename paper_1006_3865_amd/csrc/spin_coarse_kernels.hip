@@ -24,6 +24,8 @@
 // glass two more planes hold the couplings (bit 1 the bond to x+1, bit 2 to y+1, bit 3 to z+1 of
 // each site), read once per launch into registers and reused by all k hits.  Hit h of sweep t draws from Philox
 // counter (s>>3, t*k + h, replica, colour), as the oracle's coarse mode does.
+// Hits after the fourth look their bounds up in 3D, where the three thresholds of a draw cost more than a lookup: 3D L =
+// 384, T = 8, 64 hits two sweeps 3007 us with nibble words, 3250 with thresholds, 2440 so (+-J 3280, 3775, 2600).
 // us a launch of 4 hits, before (nibble words, bounds looked up in each phase) and now, 2D Ising L = 1024: T = 8
 // 11.1 -> 4.7, 16 5.6 -> 4.3, 32 5.8 -> 4.8, 64 6.9 -> 5.2; L = 4096, T = 8 120 -> 26, T = 32, where issue
 // bounds it, 21.2 -> 20.1; 3D L = 256, T = 16 25.8 -> 24.4.
@@ -49,6 +51,7 @@ struct CoarseArgs {
   uint32_t k;        // hits per tile load
   uint32_t replica;
   uint32_t q;        // tile parity of this launch
+  uint32_t look;     // 3D: hits after the first kCoarseAhead look their bounds up
 };
 
 constexpr uint32_t kCoarseNeg = 0x02020202u;
@@ -107,6 +110,10 @@ struct CoarseShape {
   static constexpr uint32_t NG = (D == 3 ? T + 2 : 1) * RR * RW;  // groups of a tile's region
   static constexpr uint32_t PB = 4 * NG;                      // bytes of a colour plane
   static constexpr uint32_t TB = PB * (EA ? 4 : 2);           // bytes of a tile
+  // Accept bounds of two sites by their u (phase_look), 3D: drawn under the loads, thresholds are off the chain; later they
+  // are 27 operations a unit where a lookup is 12.
+  static constexpr bool LOOK = D == 3;
+  static constexpr uint32_t PAIRS = LOOK ? 7 * 7 * 8 : 0;
   // Groups read, NL a thread.  2D: its own and those left and right of the tile's rows; 3D, where a tile's
   // row is one or two groups, whole rows with both (a wavefront's loads of the sides alone touch as many
   // lines again: +-J L = 256, T = 8, k = 1 47.8 us a launch so, 34.7 by rows).  Both: the rows
@@ -140,8 +147,8 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
                                                                               CoarseArgs a) {
   using S = CoarseShape<D, T, EA, NEVER>;
   constexpr uint32_t RS = 4 * S::RW, PS = RS * S::RR;  // LDS bytes of a row, of a z plane
-  __shared__ __align__(16) char lds[S::TPW * S::TB];
-  const uint32_t base = lds_addr(lds), tid = threadIdx.x;
+  __shared__ __align__(16) char lds[S::TPW * S::TB + S::PAIRS];
+  const uint32_t base = lds_addr(lds), tid = threadIdx.x, pairs = base + S::TPW * S::TB;
   const uint32_t L = a.L, GPR = L / 8;
   const uint32_t first = xcd_tile() * S::TPW;  // neighbouring tiles share the lines of their rows: one L2
   gu32* Jn = as_global(Jraw);
@@ -155,6 +162,7 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
   const uint32_t w = ((z0 + rz) * L + y0 + ry) * GPR + x0w + cw;
   const uint32_t at = base + slot * S::TB + (D == 3 ? (rz + 1u) * PS : 0u) + (ry + 1u) * RS + 4u * (cw + 1u);
   const bool odd = ((ry + rz) & 1u) != 0;  // colour-0 sites of the row are its odd x (tile edges are even)
+  if (S::LOOK && tid < 49u) lds_store64(pairs + 8u * tid, make_uint2(a.bound[tid % 7u], a.bound[tid / 7u]));
   uint2 sp[S::NL + 1];
   uint32_t jw[S::NL + 1];
   auto load = [&](uint32_t n, uint32_t g) {
@@ -268,6 +276,22 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
     lds_store32(at + (c ? S::PB : 0u), A ^ ((X >> 6) & kCoarseNeg));
     __syncthreads();
   };
+  // colour c of hit `hit` with its draws' bounds looked up, those of two sites at a time
+  auto phase_look = [&](uint32_t c, uint32_t hit) {
+    constexpr uint32_t kW = 4u + 256u * 4u * (2u * (uint32_t)D + 1u);  // byte 2u of two sites -> 8 (u0 + (2D + 1) u1)
+    uint32_t A, r[4];
+    philox_lane(w, philox_uniform(hit, a.replica, c, a.keys), a.keys, r);
+    // T = 0 classes hold bound 0 and (a.look) no class has T = 1: the draw 0, the only one those would accept, may count as 1
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = NEVER ? __builtin_elementwise_max(r[i], 1u) : r[i];
+    const uint32_t X = unsat2(c, 0u, A);
+    const uint2 b01 = lds_load64(__builtin_amdgcn_udot4(X, kW, pairs, false));
+    const uint2 b23 = lds_load64(__builtin_amdgcn_udot4(X, kW << 16, pairs, false));
+    const uint32_t F = xor3(r[0] <= b01.x ? 0x02u : 0u, r[1] <= b01.y ? 0x0200u : 0u, r[2] <= b23.x ? 0x020000u : 0u) ^
+                       (r[3] <= b23.y ? 0x02000000u : 0u);
+    lds_store32(at + (c ? S::PB : 0u), A ^ F);
+    __syncthreads();
+  };
   for (uint32_t h = 0;;) {
 #pragma unroll
     for (uint32_t j = 0; j < kCoarseAhead; ++j)
@@ -277,6 +301,13 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
       }
     h += kCoarseAhead;
     if (h >= a.k) break;
+    if (S::LOOK && a.look) {
+      for (; h < a.k; ++h) {
+        phase_look(0u, a.t * a.k + h);
+        phase_look(1u, a.t * a.k + h);
+      }
+      break;
+    }
 #pragma unroll
     for (uint32_t j = 0; j < kCoarseAhead; ++j)
       if (h + j < a.k) {
@@ -330,6 +361,10 @@ hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, u
   a.replica = lat.replica;
   a.q = q;
   const bool never = acc.never_level > 0;
+  a.look = 1;  // but for a class with T = 1 next to one with T = 0: their bounds coincide
+  if (never)
+    for (uint32_t u = 0; u <= 2u * lat.d; ++u)
+      if (acc.T[u] == 1) a.look = 0;
   if (lat.d == 2) {
     if (T == 8) return go_coarse<2, 8>(lat, Jn, a, never, stream);
     if (T == 16) return go_coarse<2, 16>(lat, Jn, a, never, stream);

@@ -51,3 +51,10 @@ def us(model, T, hits):
 def test_couplings_cost_no_more_with_every_hit():
     """3D L = 256, 100 hits a tile load: about as long with couplings as without (read in every phase: 1.24 times)."""
     assert us(1, 16, 100) <= 1.1 * us(0, 16, 100)
+
+
+def test_later_hits_cost():
+    """3D L = 256, T = 8, where issue bounds a launch: a hit beyond the fourth (bounds looked up) costs 0.74 of a
+    second to fourth one (thresholds; with thresholds for all 0.96)."""
+    t1, t4, t100 = (us(0, 8, k) for k in (1, 4, 100))
+    assert (t100 - t4) / 96 <= 0.85 * (t4 - t1) / 3, (t1, t4, t100)

@@ -632,18 +632,34 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
     b->last_calls.assign(b->h_calls, b->h_calls + S);
     b->last_order.assign(b->h_order, b->h_order + norder);
   }
-  // The classes side by side, the one with most work on the pool's stream, where it starts first, the
-  // others on the pool's further streams: they run in the places that its workgroups leave on the
+  // The classes side by side, the longest on the pool's stream, where it starts first, the others on further
+  // streams, if there are any that no larger member of this call is on: they run in the places that its workgroups leave on the
   // compute units and fill its end, when ever fewer tasks are left.  +-J lattices L = 16 .. 64, 410 of
-  // each, 50 sweeps: 7.01 ms one after another, 6.19 side by side.
-  std::vector<size_t> by_work(classes.size());
-  std::vector<uint64_t> work(classes.size(), 0);
+  // each, 50 sweeps: 7.01 ms one after another, 6.19 side by side; behind one 3D L = 128 member 850 us a call, beside it
+  // 750.  Crossing to other streams and back takes 15 to 45 us, so classes that are estimated shorter than that
+  // follow one another (4 lattices each of 16^3 and 64^2, 2 sweeps: 51 us side by side, 27 so).
+  std::vector<size_t> by_time(classes.size());
+  std::vector<double> est(classes.size(), 0.0);  // us: one lattice in a workgroup 3 attempts a ns, the chip 1600
+  double rest = 0.0;
   for (size_t k = 0; k < classes.size(); ++k) {
-    by_work[k] = k;
-    for (uint32_t i : classes[k].members) work[k] += b->m[i].N * (uint64_t)b->h_calls[i].n;
+    uint64_t sum = 0, longest = 0;
+    for (uint32_t i : classes[k].members) {
+      const uint64_t w = b->m[i].N * (uint64_t)b->h_calls[i].n;
+      sum += w;
+      longest = std::max(longest, w);
+    }
+    est[k] = std::max((double)longest / 3e3, (double)sum / 1.6e6);
+    by_time[k] = k;
+    rest += est[k];
   }
-  std::stable_sort(by_work.begin(), by_work.end(), [&](size_t x, size_t y) { return work[x] > work[y]; });
-  if (classes.size() > 1) {
+  std::stable_sort(by_time.begin(), by_time.end(), [&](size_t x, size_t y) { return est[x] > est[y]; });
+  if (!classes.empty()) rest -= est[by_time[0]];
+  const bool side = rest >= 40.0;
+  std::vector<int> streams;  // of the further classes, in turn
+  for (int a = 0; side && a < spin_batch::kAux; ++a)
+    if (!used[a]) streams.push_back(a);
+  for (int a = 0; side && streams.empty() && a < spin_batch::kAux; ++a) streams.push_back(a);
+  if (side) {
     e = hipEventRecord(b->ready, b->stream);
     if (e != hipSuccess) {
       join_aux(b, used);
@@ -651,12 +667,12 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
     }
   }
   for (size_t j = 0; j < classes.size(); ++j) {
-    const size_t k = by_work[j];
+    const size_t k = by_time[j];
     const Class& cl = classes[k];
     const uint32_t ntasks = ranges[k].second;
     hipStream_t on = b->stream;
-    if (j > 0) {
-      const int a = (int)((j - 1) % spin_batch::kAux);
+    if (j > 0 && side) {
+      const int a = streams[(j - 1) % streams.size()];
       on = b->aux[a];
       e = hipStreamWaitEvent(on, b->ready, 0);
       if (e != hipSuccess) {

@@ -16,6 +16,7 @@
 
 #include "spin_batch.h"
 #include "spin_device.h"
+#include "spin_launch.h"
 #include "spin_lds.h"
 
 namespace spin {
@@ -436,14 +437,10 @@ size_t batch_lds_bytes(uint32_t L, uint32_t d) {
 
 template <int NT>
 static hipError_t set_batch_attrs() {
-  const void* ks[4] = {(const void*)k_batch<2, false, NT>, (const void*)k_batch<2, true, NT>,
-                       (const void*)k_batch<3, false, NT>, (const void*)k_batch<3, true, NT>};
-  for (const void* k : ks) {
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)(kBatchMaxLds + kBatchCtl));
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  static OncePerDevice once;
+  return allow_lds(once, {(const void*)k_batch<2, false, NT>, (const void*)k_batch<2, true, NT>,
+                          (const void*)k_batch<3, false, NT>, (const void*)k_batch<3, true, NT>},
+                   (int)(kBatchMaxLds + kBatchCtl));
 }
 
 template <int NT>
@@ -458,23 +455,19 @@ static void go_batch(uint32_t d, bool ea, dim3 grid, size_t lds, hipStream_t str
 hipError_t launch_batch(uint32_t d, bool ea, uint32_t nt, BatchLattice* lats, const BatchCall* calls,
                         const uint32_t* order, uint32_t ntasks, uint32_t* counter, size_t lds_bytes,
                         uint32_t grid, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = set_batch_attrs<256>();
-    if (e == hipSuccess) e = set_batch_attrs<512>();
-    if (e == hipSuccess) e = set_batch_attrs<576>();
-    if (e == hipSuccess) e = set_batch_attrs<1024>();
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  hipError_t e = nt == 256    ? set_batch_attrs<256>()
+                 : nt == 512  ? set_batch_attrs<512>()
+                 : nt == 576  ? set_batch_attrs<576>()
+                 : nt == 1024 ? set_batch_attrs<1024>()
+                              : hipErrorInvalidValue;
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, counter, 1u);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (nt == 256) go_batch<256>(d, ea, dim3(grid), lds_bytes, stream, lats, calls, order, ntasks, counter);
   else if (nt == 512) go_batch<512>(d, ea, dim3(grid), lds_bytes, stream, lats, calls, order, ntasks, counter);
   else if (nt == 576) go_batch<576>(d, ea, dim3(grid), lds_bytes, stream, lats, calls, order, ntasks, counter);
-  else if (nt == 1024) go_batch<1024>(d, ea, dim3(grid), lds_bytes, stream, lats, calls, order, ntasks, counter);
-  else return hipErrorInvalidValue;
+  else go_batch<1024>(d, ea, dim3(grid), lds_bytes, stream, lats, calls, order, ntasks, counter);
   return hipGetLastError();
 }
 

@@ -47,6 +47,7 @@
 
 #include "spin_block.h"
 #include "spin_device.h"
+#include "spin_launch.h"
 #include "spin_lds.h"
 #include "spin_tile.h"
 
@@ -728,13 +729,9 @@ static uint32_t block_passes(const Lat& lat, const BlockPlan& p, const BlockArgs
 template <int D, bool EA, bool NEVER, bool RAG, int M>
 static hipError_t go_block(const int8_t* src, int8_t* dst, const int8_t* J, const BlockArgs& a, uint32_t tiles,
                            uint32_t threads, size_t lds, int64_t* part, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_block<D, EA, NEVER, RAG, M>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_block<D, EA, NEVER, RAG, M>}, 160 * 1024);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_block<D, EA, NEVER, RAG, M>), dim3(tiles), dim3(threads), lds, stream, src, dst, J, a, part);
   return hipGetLastError();
 }
@@ -801,13 +798,9 @@ double whole_us(const Lat& lat, const Accept& acc, uint32_t n) {
 template <int D, bool EA, bool NEVER, bool RAG, int M>
 static hipError_t go_whole_m(int8_t* spins, const int8_t* J, const BlockArgs& a, uint32_t threads, size_t lds, uint32_t n,
                              uint32_t every, int64_t* E, int64_t* Mg, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_whole<D, EA, NEVER, RAG, M>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_whole<D, EA, NEVER, RAG, M>}, 160 * 1024);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_whole<D, EA, NEVER, RAG, M>), dim3(1), dim3(threads), lds, stream, spins, J, a, n, every, E, Mg);
   return hipGetLastError();
 }

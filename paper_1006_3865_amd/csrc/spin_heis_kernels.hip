@@ -22,6 +22,7 @@
 
 #include "spin_device.h"
 #include "spin_heis.h"
+#include "spin_launch.h"
 #include "spin_lds.h"
 #include "spin_tile.h"
 
@@ -399,12 +400,9 @@ bool heis_block_ok(uint32_t L, uint32_t d, uint64_t N, const HeisPlan& p) {
 template <int D>
 static hipError_t go_heis_block(const float4* src, float4* dst, const HeisBlockArgs& a, uint32_t tiles, uint32_t threads,
                                 size_t lds, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_heis_block<D>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_heis_block<D>}, 160 * 1024);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_heis_block<D>, dim3(tiles), dim3(threads), lds, stream, src, dst, a);
   return hipGetLastError();
 }

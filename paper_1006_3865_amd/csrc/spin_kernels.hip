@@ -17,6 +17,7 @@
 
 #include "spin_device.h"
 #include "spin_internal.h"
+#include "spin_launch.h"
 #include "spin_phase.h"
 
 namespace spin {
@@ -377,13 +378,9 @@ size_t resident_lds_bytes(const Lat& lat) { return (size_t)lat.N; }
 hipError_t launch_resident(const Lat& lat, uint32_t t0, int n, const Accept& acc, int every,
                            int64_t* E, int64_t* M, int threads, hipStream_t stream) {
   const size_t bytes = resident_lds_bytes(lat);
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_resident,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_resident}, 150 * 1024);
+  if (e != hipSuccess) return e;
   if (threads <= 0) threads = 512;
   hipLaunchKernelGGL(k_resident, dim3(1), dim3(threads), bytes, stream, lat, t0, n, acc, every, E,
                      M);

@@ -20,6 +20,7 @@
 
 #include "spin_device.h"
 #include "spin_internal.h"
+#include "spin_launch.h"
 #include "spin_msc.h"
 #include "spin_tile.h"
 
@@ -485,13 +486,9 @@ bool msc_stream_supported(uint32_t L, uint32_t d, uint32_t TY, uint32_t H, uint3
 template <int D, int NT>
 static hipError_t go_msc_stream(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a,
                                 uint32_t TY, uint32_t H, uint32_t XW, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_msc_stream<D, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)kMscMaxLds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_msc_stream<D, NT>}, (int)kMscMaxLds);
+  if (e != hipSuccess) return e;
   const uint32_t nseg = a.L / XW;
   const dim3 grid((D == 3 ? (a.L / TY) * nseg : nseg) * ((a.L + H - 1) / H));
   hipLaunchKernelGGL((k_msc_stream<D, NT>), grid, dim3(NT), msc_stream_lds(a.L, D, TY, XW), stream, src, dst, J, a,
@@ -913,13 +910,9 @@ bool msc_col_supported(uint32_t L, uint32_t d, uint32_t TY, uint32_t H) {
 template <uint32_t L, int TY, bool REV>
 static hipError_t go_msc_dir(const uint32_t* src, uint32_t* dst, const uint32_t* J, const MscArgs& a, uint32_t H,
                              hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_msc_col<L, TY, REV>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)msc_col_lds(TY));
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_msc_col<L, TY, REV>}, (int)msc_col_lds(TY));
+  if (e != hipSuccess) return e;
   // strips side by side in a wavefront: as many as the row leaves lanes for, each L / parts planes
   // after the last, where that is a whole number of strips
   uint32_t parts = 512u / L;

@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include "spin_internal.h"
+#include "spin_launch.h"
 #include "spin_nibble.h"
 
 namespace spin {
@@ -411,16 +412,9 @@ size_t streamg_lds_bytes(const Lat& lat, const Tile& tile) {
 template <int D, bool EA, int NT, bool PAIR>
 static hipError_t go_streamg_p(dim3 grid, size_t lds, bool never, const int8_t* src, int8_t* dst, const uint32_t* Jn,
                                const StreamArgs& a, hipStream_t stream) {
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_streamg<D, EA, true, NT, PAIR>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_streamg<D, EA, false, NT, PAIR>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = allow_lds(once, {(const void*)k_streamg<D, EA, true, NT, PAIR>, (const void*)k_streamg<D, EA, false, NT, PAIR>}, 150 * 1024);
+  if (e != hipSuccess) return e;
   if (never)
     hipLaunchKernelGGL((k_streamg<D, EA, true, NT, PAIR>), grid, dim3(NT), lds, stream, src, dst, Jn, a);
   else

@@ -326,22 +326,23 @@ static uint32_t single_threads(const spin_lattice* h, const Tile& tile) {
 struct Tuned {
   int kernel;
   Tile tile;
-  bool block;  // several sweeps per launch (k_block) where a call has them
+  int block;  // several sweeps per launch (k_block) where a call has them: 1, 0, or kUntold
 };
+static const int kUntold = -1;  // not in the record: as for the automatic choice
 static std::mutex g_tune_mu;
 static std::map<std::tuple<int, int, int>, Tuned> g_tuned;
 
 static bool g_tuned_loaded = false;
 
 // Records "lattice <arch> model L d kernel x y z threads [block]": the persisted choices of
-// spin_autotune (no block field: 0).
+// spin_autotune.  Records from before k_block have no block field: it was no candidate then.
 static void load_tuned_locked() {
   if (g_tuned_loaded) return;
   g_tuned_loaded = true;
   for (const auto& v : tune_cache_read("lattice"))
     if (v.size() >= 8)
       g_tuned[std::make_tuple((int)v[0], (int)v[1], (int)v[2])] =
-          Tuned{(int)v[3], Tile{(int)v[4], (int)v[5], (int)v[6], (int)v[7]}, v.size() > 8 && v[8] != 0};
+          Tuned{(int)v[3], Tile{(int)v[4], (int)v[5], (int)v[6], (int)v[7]}, v.size() > 8 ? (int)(v[8] != 0) : kUntold};
 }
 
 static bool tuned_choice(const spin_lattice* h, Tuned* out) {
@@ -462,7 +463,12 @@ static int resolve(const spin_lattice* h, Tile* tile, bool* block = nullptr) {
   Tuned tc;
   if (tuned_choice(h, &tc) && family_ok(h, tc.kernel, tc.tile)) {
     *tile = tc.tile;
-    *block = tc.block;
+    if (tc.block == kUntold) {
+      Tile named;
+      auto_family(h, &named, block);
+    } else {
+      *block = tc.block != 0;
+    }
     return tc.kernel;
   }
   return auto_family(h, tile, block);
@@ -894,29 +900,29 @@ int spin::record_device(spin_lattice* h, int64_t* E, int64_t* M) {
 static std::vector<Tuned> tune_candidates(const spin_lattice* h) {
   std::vector<Tuned> c;
   const int L = h->L;
-  for (int th : {256, 512, 1024}) c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, th}, false});
-  c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, 512 + 64}, false});  // the per-site resident kernel
+  for (int th : {256, 512, 1024}) c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, th}, 0});
+  c.push_back({SPIN_KERNEL_RESIDENT, Tile{0, 0, 0, 512 + 64}, 0});  // the per-site resident kernel
   if (h->d == 2) {
     for (int th : {256, 512, 1024})
-      for (int H : {8, 16, 32}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, H, 0, th}, false});
+      for (int H : {8, 16, 32}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, H, 0, th}, 0});
     const int f2[7][3] = {{256, 32, 256}, {512, 32, 512}, {128, 16, 256}, {16, 8, 64},
                           {512, 16, 256}, {512, 32, 256}, {512, 64, 256}};
-    for (auto& f : f2) c.push_back({SPIN_KERNEL_FUSED, Tile{f[0], f[1], 0, f[2]}, false});
+    for (auto& f : f2) c.push_back({SPIN_KERNEL_FUSED, Tile{f[0], f[1], 0, f[2]}, 0});
     const int t2[5][3] = {{256, 32, 256}, {128, 16, 256}, {512, 32, 512}, {64, 8, 64}, {16, 8, 64}};
-    for (auto& f : t2) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], 0, f[2]}, false});
+    for (auto& f : t2) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], 0, f[2]}, 0});
     for (int th : {256, 512})
-      for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, 1, H, th}, false});
+      for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, 1, H, th}, 0});
   } else {
     const int f3[5][2] = {{8, 640}, {8, 320}, {16, 576}, {16, 384}, {32, 704}};
     for (auto& f : f3)
-      for (int H : {8, 16, 32, 64}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, f[0], H, f[1]}, false});
+      for (int H : {8, 16, 32, 64}) c.push_back({SPIN_KERNEL_FUSED, Tile{L, f[0], H, f[1]}, 0});
     const int t3[4][4] = {{64, 8, 8, 256}, {32, 8, 4, 128}, {128, 8, 4, 256}, {16, 4, 4, 64}};
-    for (auto& f : t3) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], f[2], f[3]}, false});
+    for (auto& f : t3) c.push_back({SPIN_KERNEL_TILED, Tile{f[0], f[1], f[2], f[3]}, 0});
     for (int th : {256, 512})
       for (int TY : {4, 8, 16, 32})
-        for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, TY, H, th}, false});
+        for (int H : {4, 8, 16, 32}) c.push_back({SPIN_KERNEL_STREAM, Tile{L, TY, H, th}, 0});
   }
-  c.push_back({SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, false});
+  c.push_back({SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, 0});
   // k_block, under the family that the automatic choice names for single sweeps
   spin_lattice plain = *h;
   plain.kernel = SPIN_KERNEL_AUTO;
@@ -924,7 +930,7 @@ static std::vector<Tuned> tune_candidates(const spin_lattice* h) {
   Tile t;
   bool block;
   const int k = auto_family(&plain, &t, &block);
-  if (block && block_offered(h)) c.push_back({k, t, true});
+  if (block && block_offered(h)) c.push_back({k, t, 1});
   return c;
 }
 
@@ -1251,11 +1257,11 @@ int spin_autotune(spin_lattice* h, double beta, int sweeps) {
     return hip_fail(hipGetLastError(), "autotune event");
   }
   float best_ms = 1e30f;
-  Tuned best{SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, false};
+  Tuned best{SPIN_KERNEL_GENERIC, Tile{0, 0, 0, 256}, 0};
   for (const Tuned& cand : tune_candidates(h)) {
     s->kernel = cand.kernel;
     s->tile = cand.tile;
-    s->block = cand.block;
+    s->block = cand.block == 1;
     if (!family_ok(s, cand.kernel, default_tile(s, cand.kernel))) continue;
     if (run_sweeps(s, 1, beta, 0, nullptr, nullptr) != SPIN_OK) continue;
     if (hipEventRecord(e0, s->stream) != hipSuccess) continue;
@@ -1280,10 +1286,10 @@ int spin_autotune(spin_lattice* h, double beta, int sweeps) {
     g_tuned[std::make_tuple(h->model, h->L, h->d)] = best;
   }
   tune_cache_append("lattice", {h->model, h->L, h->d, best.kernel, best.tile.x, best.tile.y, best.tile.z,
-                                best.tile.threads, best.block ? 1 : 0});
+                                best.tile.threads, best.block});
   h->kernel = best.kernel;
   h->tile = best.tile;
-  h->block = best.block;
+  h->block = best.block == 1;
   if (int rc = prepare_buffers(h)) return rc;
   return best.kernel;
 }

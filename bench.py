@@ -97,11 +97,11 @@ KERNEL_SOURCES = {
     "k_stream3d": ("spin_stream3d.hip", "spin_phase.h", "spin_device.h", "spin_packed.h"),
     "k_stream3r": ("spin_stream3d.hip", "spin_phase.h", "spin_device.h", "spin_packed.h"),
     "k_streamg": ("spin_stream_kernels.hip", "spin_nibble.h", "spin_device.h"),
-    "k_batch": ("spin_batch_kernels.hip", "spin_nibble.h", "spin_device.h"),
-    "k_msc_stream": ("spin_msc_kernels.hip", "spin_msc.h", "spin_device.h"),
-    "k_msc_col": ("spin_msc_kernels.hip", "spin_msc.h", "spin_device.h"),
-    "k_coarse": ("spin_coarse_kernels.hip", "spin_nibble.h", "spin_device.h"),
-    "k_heis_phase": ("spin_heis_kernels.hip", "spin_heis.h", "spin_device.h"),
+    "k_batch": ("spin_batch_kernels.hip", "spin_nibble.h", "spin_device.h", "spin_lds.h"),
+    "k_msc_stream": ("spin_msc_kernels.hip", "spin_msc.h", "spin_device.h", "spin_tile.h"),
+    "k_msc_col": ("spin_msc_kernels.hip", "spin_msc.h", "spin_device.h", "spin_tile.h"),
+    "k_coarse": ("spin_coarse_kernels.hip", "spin_nibble.h", "spin_device.h", "spin_packed.h", "spin_lds.h", "spin_tile.h"),
+    "k_heis_block": ("spin_heis_kernels.hip", "spin_heis.h", "spin_device.h", "spin_lds.h", "spin_tile.h"),
 }
 
 
@@ -440,9 +440,10 @@ def bench_rng_quality(torch, spin, workloads, L=64, sweeps=200_000, therm=10_000
 
 
 def bench_heisenberg(torch, spin, workloads, shapes=((4096, 2), (256, 3)), beta=0.7):
-    """Continuous spins (classical Heisenberg, float): attempts/ns over back-to-back sweeps (one launch
-    per colour), HIP events on the handle's stream, with the HBM rate of the algorithmic traffic (each
-    site's float4 read and written once and read once more as a neighbour per sweep: 48 B per attempt)."""
+    """Continuous spins (classical Heisenberg, float): attempts/ns over back-to-back sweeps, HIP events on
+    the handle's stream, with the HBM rate of the algorithmic traffic.  2D: launches of four sweeps of a
+    tile, in which each site's float4 is read and written once: 8 B per attempt.  3D above L = 64: one launch per colour, in
+    which it is read and written once and read once more as a neighbour: 48 B per attempt."""
     stream = torch.cuda.Stream()
     out = {}
     for (L, d) in shapes:
@@ -458,12 +459,13 @@ def bench_heisenberg(torch, spin, workloads, shapes=((4096, 2), (256, 3)), beta=
         ms = a.elapsed_time(b)
         h.close()
         rate = N * n / (ms * 1e6)
-        rec = {"attempts_per_ns": round(rate, 1), "ms_per_sweep": round(ms / n, 4), "sweeps": n,
-               "alg_hbm_GBps": round(48 * rate, 1), "alg_hbm_frac": round(48 * rate / HBM_PEAK_GBS, 4)}
-        traffic = profiled_traffic("k_heis_phase", L) if d == 2 else None
-        if traffic is not None:  # counted HBM bytes per colour launch
-            rec["traffic_bytes_per_sweep"] = 2 * traffic
-            rec["traffic_GBps"] = round(2 * traffic / (ms / n * 1e6), 1)
+        per = 8.0 if d == 2 else 48.0
+        rec = {"attempts_per_ns": round(rate, 1), "ms_per_sweep": round(ms / n, 4), "sweeps": n, "alg_bytes_per_attempt": per,
+               "alg_hbm_GBps": round(per * rate, 1), "alg_hbm_frac": round(per * rate / HBM_PEAK_GBS, 4)}
+        traffic = profiled_traffic("k_heis_block", L) if d == 2 else None
+        if traffic is not None:  # counted HBM bytes per launch of four sweeps
+            rec["traffic_bytes_per_sweep"] = traffic / 4
+            rec["traffic_GBps"] = round(traffic / 4 / (ms / n * 1e6), 1)
         out["d%d_L%d" % (d, L)] = rec
     return {"workload": "classical Heisenberg, float, beta %g" % beta, "rates": out}
 
@@ -713,7 +715,8 @@ def bench_c1(torch, spin, workloads):
         res[tag] = {"kernel": spin.KERNEL_NAMES[lat.kernel], "us_per_sweep": round(ms * 1e3 / n, 3),
                     "attempts_per_ns": round(n * L * L / (ms * 1e6), 3)}
         lat.close()
-    res["note"] = "latency-bound: the lattice lives in one CU's LDS for the whole call"
+    res["note"] = ("latency-bound: the lattice lives in one CU's LDS for the whole call (k_whole, for the family that AUTO "
+                   "names)")
     return res
 
 

@@ -60,9 +60,11 @@ enum spin_status {
 
 /* Kernel families; the chain (and so every bit of output) is the same. */
 enum spin_kernel {
-  SPIN_KERNEL_AUTO = 0,     /* library picks; calls of several sweeps on lattices without a
-                               register-column kernel run k sweeps of a tile per launch (ping-pong
-                               buffers; spin_get_kernel still names what single sweeps run) */
+  SPIN_KERNEL_AUTO = 0,     /* library picks a family by the lattice; a call, also of one sweep, runs
+                               several sweeps of a tile per launch instead (a second buffer, where there
+                               is memory for one), or all sweeps of a small lattice in one launch, in place,
+                               where that is faster.  The current buffer after the call is the one the
+                               family's own launches would leave */
   SPIN_KERNEL_GENERIC = 1,  /* per-site, global memory, any even L */
   SPIN_KERNEL_RESIDENT = 2, /* whole lattice in one workgroup's LDS, all sweeps in one launch */
   SPIN_KERNEL_TILED = 3,    /* LDS tile + halo per colour phase, needs L % 8 == 0 */
@@ -232,7 +234,9 @@ int spin_set_rng(spin_lattice* h, int rng);
  * L^d / 8) into a host array.  Synchronous.  SPIN_ESTATE under Philox. */
 int spin_get_rng_state(const spin_lattice* h, uint64_t* out, size_t n);
 
-/* Kernel family that spin_sweep will use next (spin_kernel value). */
+/* Kernel family set, tuned or picked for the lattice (spin_kernel value).  What an
+ * AUTO call runs in its place has no name here: this family runs where that cannot or is
+ * not faster. */
 int spin_get_kernel(const spin_lattice* h);
 
 /* Tile shape that spin_sweep will use next (as spin_set_kernel takes it;
@@ -334,10 +338,10 @@ int  spin_batch_remove(spin_batch* b, int i);
 int  spin_batch_is_member(const spin_batch* b, int i);
 
 /* Device bytes that slot i's lattice may hold: spins (twice L^d for a
- * lattice beyond the LDS-sized kind: the streaming kernels' second buffer)
+ * lattice beyond the LDS-sized kind: the second buffer)
  * plus its couplings (d*L^d/2 packed for the LDS-sized kind, 3*d*L^d/2 --
- * int8 and packed -- otherwise), counted in full even when shared with
- * other members; 0 for a free slot.  An upper bound for admission control. */
+ * int8 and packed -- otherwise; the packed ones take L^d/2 of theirs), counted in full even
+ * when shared with other members; 0 for a free slot.  An upper bound for admission control. */
 uint64_t spin_batch_footprint(const spin_batch* b, int i);
 
 /* Advance slot i by n[i] >= 0 sweeps at beta[i] (host arrays of
@@ -416,7 +420,9 @@ int spin_batch_synchronize(spin_batch* b);
  * -87 < y < 0 as 2^k e^r with k = floor(y log2 e + 1/2), r = y - k ln 2
  * (ln 2 in two parts) and e^r by its Taylor polynomial to r^7; y <= -87
  * rejects.  Every result is therefore a definite float.  Spins live on the
- * device as float4 (x, y, z, 0).  A sweep is L^d attempts. */
+ * device as float4 (x, y, z, 0), 16 L^d bytes, in 2D and in 3D up to L = 64 twice where there is
+ * memory for it (several sweeps of a tile per launch; else, and above, one launch per
+ * colour in place).  A sweep is L^d attempts. */
 typedef struct spin_heis spin_heis;
 
 /* NULL on error (spin_last_error). */

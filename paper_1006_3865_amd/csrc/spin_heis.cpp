@@ -64,9 +64,9 @@ static int reserve(spin_heis* h, size_t nrec) {
 
 // The launch shape by lattice size.  2D: the smallest tile of the list that needs no more tiles than
 // the chip has compute units (each then holds one), and up to 6 sweeps a launch (4 with the largest
-// tile, whose halo costs more); measured us a sweep against one launch per colour: L = 64 1.8 / 5.4,
-// 256 2.3 / 5.6, 512 3.2 / 6.8, 1024 7.0 / 13.7, 4096 96 / 155.  3D: two sweeps a launch up to L = 64
-// (L = 32 3.9 / 6.0, 64 6.8 / 7.4); above that the recomputed halo of a 3D tile costs more than the
+// tile, whose halo costs more); measured us a sweep (calls of 20) against one launch per colour: L = 64 1.9 / 6.0,
+// 256 2.2 / 6.5, 512 3.2 / 6.6, 1024 7.0 / 13.1, 4096 90 / 150.  3D: two sweeps a launch up to L = 64
+// (L = 32 3.7 / 6.0, 64 6.5 / 6.8); above that the recomputed halo of a 3D tile costs more than the
 // launch and the traffic it saves (L = 100 18.0 / 13.0, 256 208 / 141).
 static HeisPlan heis_plan(uint32_t L, uint32_t d) {
   HeisPlan p{0, 0, 0, 1, 0};

@@ -49,9 +49,10 @@ __device__ __forceinline__ void heis_cos_sin(float x, float& c, float& sn) {
 }
 
 // sqrt(v), correctly rounded, for v = 0 or 2^-23 <= v <= 1: the hardware's root is within one unit in
-// the last place, so the nearest of it and its two neighbours is told by the signs of the
-// residuals v - s' s and v - s'' s (no scaling or special case is needed in this range; at v = 0 both
-// tests fail and the root stays 0).
+// the last place, and s is the nearest float iff s s' < v <= s s'' for its neighbours s' < s < s'' (Tuckerman's
+// test: P. Markstein, IBM J. Res. Dev. 34 (1990) 111), told here by the signs of the exactly rounded residuals
+// v - s' s and v - s'' s.  The AMDGPU back end of LLVM expands a correctly rounded root by the same test, with a
+// scaling and special cases that this range does not need; at v = 0 both tests fail and the root stays 0.
 __device__ __forceinline__ float heis_sqrt(float v) {
   const float s = __builtin_amdgcn_sqrtf(v);
   const float dn = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(512) void k_heis_phase(float4* __restrict__ S, Heis
 // same float operations, so all agree bit for bit.  In x all columns are
 // computed in every phase; what is wrong at the region's ends moves inwards
 // one site a phase and never reaches the tile.  What bounds it is the issue of
-// about 150 vector operations an attempt (Philox 37, direction 45, decision 35).
+// about 165 vector operations an attempt.
 struct HeisBlockArgs {
   RoundKeys keys;
   float beta;

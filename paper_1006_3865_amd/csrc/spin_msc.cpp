@@ -34,8 +34,8 @@ struct spin_msc {
   uint32_t* S;       // [N] current spins
   uint32_t* S2;      // [N] second buffer of the streaming kernel (allocated on first use)
   uint32_t TY, H, NT, XW;  // streaming shape; NT == 0: the per-colour phase kernel
-  bool col;          // the register-column kernel (3D L = 512; shape TY, H)
-  uint32_t* J;       // [d][N] (measurement)
+  bool col;          // the register-column kernel (3D L = 128, 256, 512; shape TY, H)
+  uint32_t* J;       // [d][N] coupling words
   int64_t* part;     // measurement partial counts
   int64_t* rec;      // records staging (2 * 32 * rec_cap)
   size_t rec_cap;
@@ -147,8 +147,8 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
   h->S = nullptr;
   h->S2 = nullptr;
   h->J = nullptr;
-  // streaming shape, from measured rates (used where neither rule below takes another kernel): 3D whole rows in slabs of 16 rows (from L = 256 up, where
-  // the ring fits LDS), else 8, else 4, and strips of planes sized so that the grid holds about one
+  // streaming shape, from measured rates (used where neither rule below takes another kernel): 3D whole rows in
+  // slabs of 16 rows (from L = 256 up, where the ring fits LDS), else 8, else 4, and strips of planes sized so that the grid holds about one
   // workgroup per compute unit (at least 4 planes); 512 threads from L = 256 up, else 256.  2D rows
   // cut into segments of at most 2048 sites, strips of 16 rows, 256 threads.  Else the phase kernel.
   int cus = 256, dev = 0;

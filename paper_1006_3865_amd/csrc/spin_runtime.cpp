@@ -726,7 +726,7 @@ static int run_block(spin_lattice* h, int n, const Accept& acc, int every, int64
   const uint32_t m = block_offered(h) ? block_launches(h, n, kernel, &plan, &us) : 0;
   const double w_us = whole_us(lat_of(h), acc, (uint32_t)n);
   // without a k_block plan (a single sweep in place) the resident family is slower at any size that
-  // fits one workgroup, the two launches of the others take about 8 us
+  // fits one workgroup; the two launches of the others (tuned: AUTO names the resident family here) take about 8 us
   if (w_us >= 0 && (m ? w_us <= us : kernel == SPIN_KERNEL_RESIDENT || w_us < 8.0)) {
     hipError_t e = launch_whole(lat_of(h), (uint32_t)h->t, (uint32_t)n, acc, every > 0 && n >= every ? (uint32_t)every : 0u,
                                 dE, dM, h->stream);

@@ -1,5 +1,5 @@
 """AUTO's choice between one launch per sweep and several sweeps of a tile per launch: a call is not slower
-than the same call on the family that AUTO names (times of the same box and moment, the better of
+than the same call on the family that AUTO names (times taken in turn, the best of
 several), and the bits do not depend on which of the two a call takes."""
 import sys
 import time

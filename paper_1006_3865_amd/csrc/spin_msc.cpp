@@ -200,10 +200,10 @@ spin_msc* spin_msc_create(int L, int d, uint64_t coupling_seed, uint32_t realisa
   // While spins and couplings stay in the 256 MB memory-side cache (2D, where the march reads its
   // couplings once: a third of it) the phase kernel, which has every load in flight at once, beats the
   // planes' march (a barrier and a round of loads a step): us a sweep 2D L = 64 7.3 against 33.5, 1024 9.1
-  // against 32.6, 2048 25 against 44, 2624 40.1 against 41.1; 3D L = 64 8.1 against 18.9, 160 31 against 54, 248 94 against
-  // 174.  Beyond, reading the couplings twice a sweep costs more: 2D L = 2752 43.0 against 41.8, 2944 48.1 against
-  // 42.2, 4096 84 against 65; 3D L = 264 171 against 160, 320 329 against 248.
-  if (N * 4 * (uint64_t)(d + 1) <= (uint64_t)(d == 3 ? 256 : 80) << 20) h->NT = 0;
+  // against 32.6, 2048 25 against 42, 2560 39.5 against 39.5; 3D L = 64 8.1 against 18.9, 160 31 against 54, 248 94
+  // against 127.  Beyond, reading the couplings twice a sweep costs more: 2D L = 2624 41.5 against 39.8, 2752 44.5
+  // against 40.4, 4096 84 against 64; 3D L = 264 172 against 156, 320 329 against 244.
+  if (N * 4 * (uint64_t)(d + 1) <= (uint64_t)(d == 3 ? 256 : 76) << 20) h->NT = 0;
   h->part = nullptr;
   h->rec = nullptr;
   h->rec_cap = 0;

@@ -99,15 +99,20 @@ __device__ __forceinline__ void load8(const uint32_t* p, uint32_t (&v)[8]) {
 // u1 u0) is at least u*(r).  The thresholds grow with u, so r reaches them in
 // order and each one reached replaces the mask by the next narrower one: a
 // compare and a select each (counting u* first and comparing it cost three more
-// operations a threshold).  A threshold of 2^32 is reached by no r (its high word
-// is the same for the whole launch, so that test is a scalar one).
-template <int D>
+// operations a threshold).  A threshold of 2^32 is reached by no r.
+// SPLIT: that is asked once, of the high word, and the low words are compared.  The phase kernel takes it
+// (2D L = 2048 24.8 us a sweep, 26.9 with 64-bit compares); in the marching ones the scalar masks that it
+// keeps do not fit the registers next to the rest (2D L = 2944 43.6 us, 40.5 with 64-bit compares; 3D L = 400 457 and 447).
+template <int D, bool SPLIT>
 __device__ __forceinline__ uint32_t msc_flips(uint32_t u0, uint32_t u1, uint32_t u2, uint32_t r,
                                               const uint64_t (&thr)[3]) {
+  auto reached = [&](int k) {
+    return SPLIT ? (r >= (uint32_t)thr[k]) & ((uint32_t)(thr[k] >> 32) == 0u) : r >= thr[k];
+  };
   uint32_t m = 0xFFFFFFFFu;
-  m = (r >= (uint32_t)thr[0]) & ((uint32_t)(thr[0] >> 32) == 0u) ? (u0 | u1 | u2) : m;
-  m = (r >= (uint32_t)thr[1]) & ((uint32_t)(thr[1] >> 32) == 0u) ? (u1 | u2) : m;
-  if (D == 3) m = (r >= (uint32_t)thr[2]) & ((uint32_t)(thr[2] >> 32) == 0u) ? (u2 | (u1 & u0)) : m;
+  m = reached(0) ? (u0 | u1 | u2) : m;
+  m = reached(1) ? (u1 | u2) : m;
+  if (D == 3) m = reached(2) ? (u2 | (u1 & u0)) : m;
   return m;
 }
 
@@ -142,12 +147,12 @@ __device__ __forceinline__ void msc_update8(uint32_t (&c)[8], uint32_t lw, uint3
       const uint32_t s1 = xor3(b0, b1, b2), c1 = maj3(b0, b1, b2);
       u0 = s1 ^ b3;
       const uint32_t t = s1 & b3;
-      // u1 | u2 in one word, as only their or is asked for (in two, the compiler kept both: 2D L = 3072 45.0 us a
-      // sweep, 43.3 so)
+      // u1 | u2 in one word, as only their or is asked for (in two, the compiler keeps both: 32 vector operations
+      // more a plane step)
       u1 = c1 | t;
       u2 = 0u;
     }
-    c[j] = s ^ msc_flips<D>(u0, u1, u2, r[i], a.thr);
+    c[j] = s ^ msc_flips<D, false>(u0, u1, u2, r[i], a.thr);
   }
 }
 
@@ -201,7 +206,7 @@ __device__ __forceinline__ u32x4 msc_update4(u32x4 A, u32x4 o, u32x4 N, u32x4 ym
       u1 = c1 | t;  // u1 | u2, as in msc_update8
       u2 = 0u;
     }
-    out[i] = s ^ msc_flips<D>(u0, u1, u2, r[i], thr);
+    out[i] = s ^ msc_flips<D, true>(u0, u1, u2, r[i], thr);
   }
   return out;
 }
@@ -652,7 +657,7 @@ __device__ __forceinline__ void unit(G8& g, uint32_t nb, const G8& jx, uint32_t 
     const uint32_t s2 = xor3(b3, b4, b5), c2 = maj3(b3, b4, b5);
     const uint32_t u0 = s1 ^ s2, t = s1 & s2;
     const uint32_t u1 = xor3(c1, c2, t), u2 = maj3(c1, c2, t);
-    w[j] = s ^ msc_flips<3>(u0, u1, u2, r[i], thr);
+    w[j] = s ^ msc_flips<3, false>(u0, u1, u2, r[i], thr);
   }
   g.lo = v4u{w[0], w[1], w[2], w[3]};
   g.hi = v4u{w[4], w[5], w[6], w[7]};

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "spin_device.h"
 #include "spin_heis.h"
 #include "spin_launch.h"
@@ -355,16 +357,19 @@ hipError_t launch_heis_init(float4* S, uint64_t N, uint64_t seed, uint32_t repli
   return hipGetLastError();
 }
 
-// Rows are cut into equal segments of at most 512 sites of the colour, and as many whole ones as 512 threads hold go
-// into a workgroup (with 256 threads and one row each the lanes of 128 < L / 2 < 256 were up to half idle).  Each
+// Rows are cut into equal segments of at most NT sites of the colour, and as many whole ones as NT threads hold go
+// into a workgroup (with one row each the lanes of 128 < L / 2 < 256 were up to half idle).  NT = 512 pays
+// from about 48 MiB in 3D, where rows above and below in one workgroup share more loads (us a sweep, 256 threads and
+// 512: L = 144 22.8 / 22.9, 160 31.4 / 30.7, 200 62.5 / 59.5, 320 444 / 404); below, and in 2D, the smaller one spreads the
+// lattice over more CUs (3D L = 66 6.9 / 7.9, 80 8.3 / 9.2, 128 15.8 / 16.4).  Each
 // XCD takes an eighth of the lattice; beyond the 256 MB memory-side cache all eight go through it together, four
 // planes each at a time, and the planes that are read again stay cached.  us a sweep 3D, the flat order of one thread a
 // site and the kernel before this rule, then now: L = 256 218, 149, 141; 258 389, 244, 194; 300 407, 462, 355;
 // 320 489, 556, 463; 400 1072, 1120, 1066; 520 3571, 4040, 2489.
 hipError_t launch_heis_phase(float4* S, uint32_t d, const HeisArgs& a, hipStream_t stream) {
-  constexpr uint32_t NT = 512;
-  const uint32_t half = a.L / 2u, nseg = (half + NT - 1u) / NT, xw = (half + nseg - 1u) / nseg, rpt = NT / xw;
-  const uint32_t nrows = (uint32_t)(a.N / a.L), blocks = (nrows + rpt - 1u) / rpt * nseg;
+  const uint32_t NT = d == 3 && a.N * sizeof(float4) >= (uint64_t)48 << 20 ? 512 : 256;
+  const uint32_t half = a.L / 2u, nseg = (half + NT - 1u) / NT, xw = (half + nseg - 1u) / nseg;
+  const uint32_t nrows = (uint32_t)(a.N / a.L), rpt = std::min(NT / xw, nrows), blocks = (nrows + rpt - 1u) / rpt * nseg;
   HeisOrder o{1u, blocks / 8u};
   if (d == 3 && a.N * sizeof(float4) > (uint64_t)300 << 20) {
     o.chunk = 4u * a.L / rpt * nseg;

@@ -51,7 +51,6 @@ struct CoarseArgs {
   uint32_t k;        // hits per tile load
   uint32_t replica;
   uint32_t q;        // tile parity of this launch
-  uint32_t look;     // 3D: hits after the first kCoarseAhead look their bounds up
 };
 
 constexpr uint32_t kCoarseNeg = 0x02020202u;
@@ -110,10 +109,6 @@ struct CoarseShape {
   static constexpr uint32_t NG = (D == 3 ? T + 2 : 1) * RR * RW;  // groups of a tile's region
   static constexpr uint32_t PB = 4 * NG;                      // bytes of a colour plane
   static constexpr uint32_t TB = PB * (EA ? 4 : 2);           // bytes of a tile
-  // Accept bounds of two sites by their u (phase_look), 3D: drawn under the loads, thresholds are off the chain; later they
-  // are 27 operations a unit where a lookup is 12.
-  static constexpr bool LOOK = D == 3;
-  static constexpr uint32_t PAIRS = LOOK ? 7 * 7 * 8 : 0;
   // Groups read, NL a thread.  2D: its own and those left and right of the tile's rows; 3D, where a tile's
   // row is one or two groups, whole rows with both (a wavefront's loads of the sides alone touch as many
   // lines again: +-J L = 256, T = 8, k = 1 47.8 us a launch so, 34.7 by rows).  Both: the rows
@@ -141,13 +136,18 @@ struct CoarseShape {
   }
 };
 
-template <int D, int T, bool EA, bool NEVER>
+// LOOK (3D, more hits than kCoarseAhead): the later hits take their accept bounds from a table, two sites by their u
+// (phase_look); drawn under the loads, thresholds are off the chain, after that they are 27 operations a unit where a lookup
+// is 12.  A kernel of its own: with the table and its code in every launch, 3D L = 32, T = 8, 1 hit took 3.6 us a
+// launch, 3.3 without.
+template <int D, int T, bool EA, bool NEVER, bool LOOK>
 __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(int8_t* __restrict__ spins,
                                                                               const uint32_t* __restrict__ Jraw,
                                                                               CoarseArgs a) {
   using S = CoarseShape<D, T, EA, NEVER>;
   constexpr uint32_t RS = 4 * S::RW, PS = RS * S::RR;  // LDS bytes of a row, of a z plane
-  __shared__ __align__(16) char lds[S::TPW * S::TB + S::PAIRS];
+  constexpr uint32_t kPairs = LOOK ? 7 * 7 * 8 : 0;
+  __shared__ __align__(16) char lds[S::TPW * S::TB + kPairs];
   const uint32_t base = lds_addr(lds), tid = threadIdx.x, pairs = base + S::TPW * S::TB;
   const uint32_t L = a.L, GPR = L / 8;
   const uint32_t first = xcd_tile() * S::TPW;  // neighbouring tiles share the lines of their rows: one L2
@@ -162,7 +162,7 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
   const uint32_t w = ((z0 + rz) * L + y0 + ry) * GPR + x0w + cw;
   const uint32_t at = base + slot * S::TB + (D == 3 ? (rz + 1u) * PS : 0u) + (ry + 1u) * RS + 4u * (cw + 1u);
   const bool odd = ((ry + rz) & 1u) != 0;  // colour-0 sites of the row are its odd x (tile edges are even)
-  if (S::LOOK && tid < 49u) lds_store64(pairs + 8u * tid, make_uint2(a.bound[tid % 7u], a.bound[tid / 7u]));
+  if (LOOK && tid < 49u) lds_store64(pairs + 8u * tid, make_uint2(a.bound[tid % 7u], a.bound[tid / 7u]));
   uint2 sp[S::NL + 1];
   uint32_t jw[S::NL + 1];
   auto load = [&](uint32_t n, uint32_t g) {
@@ -281,7 +281,7 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
     constexpr uint32_t kW = 4u + 256u * 4u * (2u * (uint32_t)D + 1u);  // byte 2u of two sites -> 8 (u0 + (2D + 1) u1)
     uint32_t A, r[4];
     philox_lane(w, philox_uniform(hit, a.replica, c, a.keys), a.keys, r);
-    // T = 0 classes hold bound 0 and (a.look) no class has T = 1: the draw 0, the only one those would accept, may count as 1
+    // T = 0 classes hold bound 0 and (LOOK) no class has T = 1: the draw 0, the only one those would accept, may count as 1
 #pragma unroll
     for (int i = 0; i < 4; ++i) r[i] = NEVER ? __builtin_elementwise_max(r[i], 1u) : r[i];
     const uint32_t X = unsat2(c, 0u, A);
@@ -301,7 +301,7 @@ __global__ __launch_bounds__((CoarseShape<D, T, EA, NEVER>::NT)) void k_coarse(i
       }
     h += kCoarseAhead;
     if (h >= a.k) break;
-    if (S::LOOK && a.look) {
+    if (LOOK) {
       for (; h < a.k; ++h) {
         phase_look(0u, a.t * a.k + h);
         phase_look(1u, a.t * a.k + h);
@@ -331,20 +331,25 @@ bool coarse_supported(const Lat& lat, int T) {
 }
 
 template <int D, int T, bool EA, bool NEVER>
-static hipError_t run_coarse(const Lat& lat, const uint32_t* Jn, const CoarseArgs& a, hipStream_t stream) {
+static hipError_t run_coarse(const Lat& lat, const uint32_t* Jn, const CoarseArgs& a, bool look, hipStream_t stream) {
   using S = CoarseShape<D, T, EA, NEVER>;
-  hipLaunchKernelGGL((k_coarse<D, T, EA, NEVER>), dim3((a.tiles + S::TPW - 1) / S::TPW), dim3(S::NT), 0, stream,
-                     lat.spins, Jn, a);
+  const dim3 grid((a.tiles + S::TPW - 1) / S::TPW), block(S::NT);
+  if (look)
+    hipLaunchKernelGGL((k_coarse<D, T, EA, NEVER, D == 3>), grid, block, 0, stream, lat.spins, Jn, a);
+  else
+    hipLaunchKernelGGL((k_coarse<D, T, EA, NEVER, false>), grid, block, 0, stream, lat.spins, Jn, a);
   return hipGetLastError();
 }
 
 template <int D, int T>
-static hipError_t go_coarse(const Lat& lat, const uint32_t* Jn, CoarseArgs a, bool never, hipStream_t stream) {
+static hipError_t go_coarse(const Lat& lat, const uint32_t* Jn, CoarseArgs a, bool never, bool look, hipStream_t stream) {
   const uint32_t B = lat.L / T;
   a.tiles = B / 2 * B * (D == 3 ? B : 1);
   if (lat.J != nullptr)
-    return never ? run_coarse<D, T, true, true>(lat, Jn, a, stream) : run_coarse<D, T, true, false>(lat, Jn, a, stream);
-  return never ? run_coarse<D, T, false, true>(lat, Jn, a, stream) : run_coarse<D, T, false, false>(lat, Jn, a, stream);
+    return never ? run_coarse<D, T, true, true>(lat, Jn, a, look, stream)
+                 : run_coarse<D, T, true, false>(lat, Jn, a, look, stream);
+  return never ? run_coarse<D, T, false, true>(lat, Jn, a, look, stream)
+               : run_coarse<D, T, false, false>(lat, Jn, a, look, stream);
 }
 
 hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, uint32_t k, uint32_t q,
@@ -361,18 +366,19 @@ hipError_t launch_coarse_phase(const Lat& lat, const uint32_t* Jn, uint32_t t, u
   a.replica = lat.replica;
   a.q = q;
   const bool never = acc.never_level > 0;
-  a.look = 1;  // but for a class with T = 1 next to one with T = 0: their bounds coincide
+  // not where a class with T = 1 is next to one with T = 0: their bounds coincide
+  bool look = lat.d == 3 && k > kCoarseAhead;
   if (never)
     for (uint32_t u = 0; u <= 2u * lat.d; ++u)
-      if (acc.T[u] == 1) a.look = 0;
+      if (acc.T[u] == 1) look = false;
   if (lat.d == 2) {
-    if (T == 8) return go_coarse<2, 8>(lat, Jn, a, never, stream);
-    if (T == 16) return go_coarse<2, 16>(lat, Jn, a, never, stream);
-    if (T == 32) return go_coarse<2, 32>(lat, Jn, a, never, stream);
-    return go_coarse<2, 64>(lat, Jn, a, never, stream);
+    if (T == 8) return go_coarse<2, 8>(lat, Jn, a, never, look, stream);
+    if (T == 16) return go_coarse<2, 16>(lat, Jn, a, never, look, stream);
+    if (T == 32) return go_coarse<2, 32>(lat, Jn, a, never, look, stream);
+    return go_coarse<2, 64>(lat, Jn, a, never, look, stream);
   }
-  if (T == 8) return go_coarse<3, 8>(lat, Jn, a, never, stream);
-  return go_coarse<3, 16>(lat, Jn, a, never, stream);
+  if (T == 8) return go_coarse<3, 8>(lat, Jn, a, never, look, stream);
+  return go_coarse<3, 16>(lat, Jn, a, never, look, stream);
 }
 
 }  // namespace spin

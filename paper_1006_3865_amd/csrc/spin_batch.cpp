@@ -636,8 +636,9 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
   // streams, if there are any that no larger member of this call is on: they run in the places that its workgroups leave on the
   // compute units and fill its end, when ever fewer tasks are left.  +-J lattices L = 16 .. 64, 410 of
   // each, 50 sweeps: 7.01 ms one after another, 6.19 side by side; behind one 3D L = 128 member 850 us a call, beside it
-  // 750.  Crossing to other streams and back takes 15 to 45 us, so classes that are estimated shorter than that
-  // follow one another (4 lattices each of 16^3 and 64^2, 2 sweeps: 51 us side by side, 27 so).
+  // 750.  Crossing to other streams and back takes 15 to 45 us, so classes that are estimated shorter than 25
+  // follow one another (4 lattices each of 16^3 and 64^2, estimates of 2.7, 14 and 27 us: 26, 45 and 68 us one after another,
+  // 44, 52 and 53 side by side).
   std::vector<size_t> by_time(classes.size());
   std::vector<double> est(classes.size(), 0.0);  // us: one lattice in a workgroup 3 attempts a ns, the chip 1600
   double rest = 0.0;
@@ -654,7 +655,7 @@ static int batch_run(spin_batch* b, const int* n, const double* beta, int every,
   }
   std::stable_sort(by_time.begin(), by_time.end(), [&](size_t x, size_t y) { return est[x] > est[y]; });
   if (!classes.empty()) rest -= est[by_time[0]];
-  const bool side = rest >= 40.0;
+  const bool side = rest >= 25.0;
   std::vector<int> streams;  // of the further classes, in turn
   for (int a = 0; side && a < spin_batch::kAux; ++a)
     if (!used[a]) streams.push_back(a);
